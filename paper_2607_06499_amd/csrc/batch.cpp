@@ -38,7 +38,8 @@ constexpr int kAreas = 4;  // area 0: the full member set; 1..3: subset ring
 struct Layout {
   size_t cnt_roll[3], cnt_p[kPlanKinds], cnt_all;  // table counts n
   size_t roll_slot[3], roll_pref[3][4];
-  size_t p_slot[kPlanKinds], compact[kPlanKinds], cc[kPlanKinds], dyn_cnt[kPlanKinds], dyn_adj[kPlanKinds];
+  size_t p_slot[kPlanKinds], compact[kPlanKinds], one[kPlanKinds], dyn_cnt[kPlanKinds], dyn_adj[kPlanKinds],
+      dyn_lab[kPlanKinds];
   size_t all_slot, update, finish;
   size_t ints = 0;
   void make(int n) {
@@ -58,9 +59,10 @@ struct Layout {
     for (int kd = 0; kd < kPlanKinds; ++kd) {
       p_slot[kd] = take(n);
       compact[kd] = take(n + 1);
-      cc[kd] = take(n + 1);
+      one[kd] = take(n + 1);
       dyn_cnt[kd] = take(n + 1);
       dyn_adj[kd] = take(n + 1);
+      dyn_lab[kd] = take(n + 1);
     }
     all_slot = take(n);
     update = take(n + 1);
@@ -102,7 +104,7 @@ struct ce_mppi_batch {
   hipEvent_t up_done = nullptr;
   // totals of the full member set (upper bounds of any subset): grid sizes
   int roll_total[3][4] = {};
-  int compact_total[kPlanKinds] = {}, update_total = 0, n_p[kPlanKinds] = {}, win_total = 0;
+  int compact_total[kPlanKinds] = {}, update_total = 0, n_p[kPlanKinds] = {}, lab_total[kPlanKinds] = {};
   ce_mppi_batch_tuning tune{8, 8, 4, 4};
 };
 
@@ -168,7 +170,7 @@ void fill_tables(const ce_mppi_batch* B, const int* members, int count, int* h) 
     h[L.cnt_p[kd]] = (int)lp[kd].size();
     copy(lp[kd], L.p_slot[kd]);
     prefix(lp[kd], L.compact[kd], [](const ce_mppi_planner* P) { return (P->c.K + 255) / 256; });
-    prefix(lp[kd], L.cc[kd], [](const ce_mppi_planner*) { return 1; });
+    prefix(lp[kd], L.one[kd], [](const ce_mppi_planner*) { return 1; });
     // the DBSCAN tables are written on the device by kb_plan
   }
   h[L.cnt_all] = count;
@@ -191,22 +193,24 @@ void area_tabs(const ce_mppi_batch* B, Area& a) {
     const int* sl = d + L.p_slot[kd];
     const int* nk = d + L.cnt_p[kd];
     T.compact[kd] = Tab{sl, d + L.compact[kd], nk};
-    T.cc[kd] = Tab{sl, d + L.cc[kd], nk};
+    T.one[kd] = Tab{sl, d + L.one[kd], nk};
     T.cnt[kd] = Tab{sl, d + L.dyn_cnt[kd], nk};
     T.adj[kd] = Tab{sl, d + L.dyn_adj[kd], nk};
+    T.lab[kd] = Tab{sl, d + L.dyn_lab[kd], nk};
     T.plan.slot[kd] = sl;
     T.plan.n[kd] = nk;
     T.plan.pref_cnt[kd] = d + L.dyn_cnt[kd];
     T.plan.pref_adj[kd] = d + L.dyn_adj[kd];
+    T.plan.pref_lab[kd] = d + L.dyn_lab[kd];
     T.has[kd] = B->n_p[kd] > 0;
     T.grid_compact[kd] = std::max(1, std::min(B->compact_total[kd], 4 * cus));
-    T.grid_cc[kd] = std::max(1, std::min(B->n_p[kd], cus));
+    T.grid_one[kd] = std::max(1, std::min(B->n_p[kd], cus));
+    // one labelling block per CU fits the LDS of the angular windows
+    T.grid_lab[kd] = std::max(1, std::min(B->lab_total[kd], cus));
   }
   T.update = Tab{d + L.all_slot, d + L.update, d + L.cnt_all};
   T.finish = Tab{d + L.all_slot, d + L.finish, d + L.cnt_all};
   T.grid_tile = B->tune.tile_blocks_per_cu * cus;
-  // count-and-place blocks of the angular windows: two per CU fit its LDS
-  T.grid_win = std::max(1, std::min(B->win_total, 2 * cus));
   T.grid_update = std::max(1, std::min(B->update_total, 4 * cus));
   T.grid_finish = std::max(1, std::min(B->n, cus));
   T.colg = B->tune.colg;
@@ -298,7 +302,7 @@ ce_status ce_mppi_batch_create(ce_mppi_planner* const* planners, int32_t n, ce_m
     // 2-D members on the angular windows (their path when the batch is
     // made) form a group of their own
     B->p_kind[i] = P->c.p == 3 ? 1 : (P->c.dbpath == 0 && P->b.wcnt ? 2 : 0);
-    if (B->p_kind[i] == 2) B->win_total += (P->c.K + kWinPos - 1) / kWinPos;
+    B->lab_total[B->p_kind[i]] += (P->c.K + kChunk - 1) / kChunk;
     B->has_roll[B->roll_kind[i]] = true;
     B->n_p[B->p_kind[i]] += 1;
     for (int ri = 0; ri < 4; ++ri) {

@@ -207,14 +207,10 @@ __device__ __forceinline__ bool win_ring(const Cfg& c, float2 z) {
   const float n2 = __builtin_fmaf(z.y, z.y, z.x * z.x);
   return n2 >= c.w_r2lo && n2 <= c.w_r2hi;
 }
-// bucket and slot of point `rank`: the slot is its arrival order in the
-// bucket (any order serves: no result depends on the order inside a bucket)
-__device__ __forceinline__ void win_bin(const Cfg& c, const Bufs& b, float2 zz, int rank) {
-  const int bkt = win_ring(c, zz) ? win_bucket(win_u(c, zz)) : kWinBins;
-  const int slot = atomicAdd(&b.wcnt[bkt], 1);
-  b.wkey[rank] = (bkt << kWinShift) | slot;
+// bucket of feature zz, kWinBins off the ring
+__device__ __forceinline__ int win_bin(const Cfg& c, float2 zz) {
+  return win_ring(c, zz) ? win_bucket(win_u(c, zz)) : kWinBins;
 }
-__device__ __forceinline__ void win_bin(const Cfg&, const Bufs&, float4, int) {}
 
 template <int P, bool BIN = false>
 __device__ __forceinline__ void compact_body(const Cfg& c, const Bufs& b, int bx, int by, int nbx) {
@@ -249,6 +245,9 @@ __device__ __forceinline__ void compact_body(const Cfg& c, const Bufs& b, int bx
     ct->smin_all = s_tot[P_SMIN_ALL];
     ct->smin_feas = s_tot[P_SMIN_FEAS];
     ct->M = 0;
+    ct->n_trees = 0;
+    ct->tree_overflow = 0;
+    ct->stat_direct = 0;
     ct->sel = -1;
     for (int i = 0; i < 3; ++i) ct->ref[i] = T.ref[i];
     // Eq. (17) for o*, once per replan on the clustering branch (the
@@ -301,16 +300,20 @@ __device__ __forceinline__ void compact_body(const Cfg& c, const Bufs& b, int bx
     gg = make_float4(g[0], g[1], g[2], 0.f);
   }
   reinterpret_cast<ZT*>(b.z)[rank] = zz;
-  if constexpr (BIN) win_bin(c, b, zz, rank);
   reinterpret_cast<ZT*>(b.gv)[rank] = gg;
   b.vidx[rank] = k;
   b.Sv[rank] = Sk;
-  b.ncount[rank] = 0;
-  b.mcn[rank] = kInt32Max;
-  b.root[rank] = -1;
-  b.label[rank] = -1;
-  if ((rank & 63) == 0) b.hookmask[rank >> 6] = 0ull;
-  if (rank < kMaxTrees) b.tadj[rank] = 0ull;  // rows of trees 0 .. min(V, 64) - 1
+  if constexpr (BIN) {
+    // the labelling blocks of the window path write everything else
+    b.wkey[rank] = win_bin(c, zz) << kWinShift;
+  } else {
+    b.ncount[rank] = 0;
+    b.mcn[rank] = kInt32Max;
+    b.root[rank] = -1;
+    b.label[rank] = -1;
+    if ((rank & 63) == 0) b.hookmask[rank >> 6] = 0ull;
+    if (rank < kMaxTrees) b.tadj[rank] = 0ull;  // rows of trees 0 .. min(V, 64) - 1
+  }
 }
 
 template <int P, bool BIN>
@@ -1123,120 +1126,129 @@ __device__ void uf_fallback(const Cfg& c, const Bufs& b, const float* zin, int V
   __syncthreads();
 }
 
-// Cluster statistics of Alg. 1 [Cluster stats] over one labelling chunk:
-// count, cost sum, direction sums (for Eq. (16)) and minimum cost of every
-// cluster.  Thread t holds the chunk's points a0 + u * kFinThreads + t (u
-// ascending) and sums them in that order; the thread sums go through an xor
-// butterfly within the wave, the wave results are added in wave order and
-// the chunks in ascending order, so every run gives the same totals.  The
-// running totals live in the cluster arrays: thread j < kStatClusters keeps
-// clusters j, j + kStatClusters, ...
-template <int P>
-__device__ void chunk_stats(const Bufs& b, bool first, int M, const int (&lab)[kLabBatch],
-                            const float (&Sa)[kLabBatch], const typename ZVec<P>::T (&ga)[kLabBatch],
-                            float (*s_red)[kStatClusters][6], float (*s_tot)[6]) {
+// Cluster statistics of Alg. 1 [Cluster stats]: count, cost sum, direction
+// sums (for Eq. (16)) and minimum cost.  The points are taken in chunks of
+// kChunk, one per thread of a labelling block: chunk_reduce sums clusters
+// c0 .. c0 + ncl - 1 over a chunk, each wave by an xor butterfly, the wave
+// results in wave order; the chunks are added in ascending order.  Every path
+// takes this order, so the totals do not depend on the path or on how the
+// chunks were spread over blocks.  use(j, f, v) receives field f of cluster
+// c0 + j on one thread each.
+template <int P, typename F>
+__device__ __forceinline__ void chunk_reduce(int c0, int ncl, int lab, float S, typename ZVec<P>::T g,
+                                             float (*s_red)[kStatClusters][6], F&& use) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  for (int c0 = 0; c0 < M; c0 += kStatClusters) {
-    const int ncl = min(kStatClusters, M - c0);
-    for (int j = 0; j < ncl; ++j) {
+  for (int j = 0; j < ncl; ++j) {
+    const bool in = lab == c0 + j;
+    const int n = __popcll(__ballot(in));
+    float sS = in ? S : 0.f, g0 = in ? g.x : 0.f, g1 = in ? g.y : 0.f, g2 = 0.f, mn = in ? S : INFINITY;
+    if constexpr (P == 3) g2 = in ? g.z : 0.f;
+    if (n) {  // wave-uniform
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        sS += __shfl_xor(sS, off, kWave);
+        g0 += __shfl_xor(g0, off, kWave);
+        g1 += __shfl_xor(g1, off, kWave);
+        if constexpr (P == 3) g2 += __shfl_xor(g2, off, kWave);
+        mn = fminf(mn, __shfl_xor(mn, off, kWave));
+      }
+    }
+    if (lane == 0) {
+      float* r = s_red[w][j];
+      r[0] = sS;
+      r[1] = g0;
+      r[2] = g1;
+      r[3] = g2;
+      r[4] = mn;
+      r[5] = (float)n;
+    }
+  }
+  __syncthreads();
+  const int j = threadIdx.x / kStatFields, f = threadIdx.x % kStatFields;
+  if (j < ncl && f < 6) {
+    float v = s_red[0][j][f];
+#pragma unroll
+    for (int q = 1; q < kFinThreads / kWave; ++q) v = f == 4 ? fminf(v, s_red[q][j][f]) : v + s_red[q][j][f];
+    use(j, f, v);
+  }
+  __syncthreads();
+}
+static_assert(kStatClusters * kStatFields <= kFinThreads, "one thread per cluster and field");
+
+// at most kStatClusters clusters: the sums of chunk q go to the statistics
+// array, and the selection adds the chunks
+template <int P>
+__device__ __forceinline__ void chunk_stats(const Bufs& b, int q, int M, int lab, float S, typename ZVec<P>::T g,
+                                            float (*s_red)[kStatClusters][6]) {
+  float* out = b.stat + (size_t)q * (kStatClusters * kStatFields);
+  chunk_reduce<P>(0, M, lab, S, g, s_red, [&](int j, int f, float v) { out[j * kStatFields + f] = v; });
+}
+
+// more clusters: one block takes every chunk (first: the chunk starts the
+// sums), with the running sums in the cluster arrays, then the means: cost
+// (Alg. 1 [Cluster stats]) and normalised direction (Eq. (16))
+template <int P>
+__device__ void chunk_stats_many(const Bufs& b, bool first, int M, int lab, float S, typename ZVec<P>::T g,
+                                 float (*s_red)[kStatClusters][6]) {
+  for (int c0 = 0; c0 < M; c0 += kStatClusters)
+    chunk_reduce<P>(c0, min(kStatClusters, M - c0), lab, S, g, s_red, [&](int j, int f, float v) {
       const int cl = c0 + j;
-      float sS = 0.f, g0 = 0.f, g1 = 0.f, g2 = 0.f, mn = INFINITY;
-      int n = 0;
-#pragma unroll
-      for (int u = 0; u < kLabBatch; ++u) {
-        const bool in = lab[u] == cl;
-        n += __popcll(__ballot(in));
-        if (in) {
-          sS += Sa[u];
-          g0 += ga[u].x;
-          g1 += ga[u].y;
-          if constexpr (P == 3) g2 += ga[u].z;
-          mn = fminf(mn, Sa[u]);
-        }
+      if (f == 5) {
+        b.c_size[cl] = (first ? 0 : b.c_size[cl]) + (int)v;
+      } else {
+        float* p = f == 0 ? b.c_cost + cl : (f == 4 ? b.c_smin + cl : b.c_dir + 4 * cl + (f - 1));
+        *p = first ? v : (f == 4 ? fminf(*p, v) : *p + v);
       }
-      if (n) {  // wave-uniform
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-          sS += __shfl_xor(sS, off, kWave);
-          g0 += __shfl_xor(g0, off, kWave);
-          g1 += __shfl_xor(g1, off, kWave);
-          if constexpr (P == 3) g2 += __shfl_xor(g2, off, kWave);
-          mn = fminf(mn, __shfl_xor(mn, off, kWave));
-        }
-      }
-      if (lane == 0) {
-        float* r = s_red[w][j];
-        r[0] = sS;
-        r[1] = g0;
-        r[2] = g1;
-        r[3] = g2;
-        r[4] = mn;
-        r[5] = (float)n;
-      }
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < ncl) {
-      const int j = threadIdx.x, cl = c0 + j;
-      float sS = 0.f, g0 = 0.f, g1 = 0.f, g2 = 0.f, mn = INFINITY;
-      int n = 0;
-      if (!first) {
-        sS = b.c_cost[cl];
-        g0 = b.c_dir[4 * cl];
-        g1 = b.c_dir[4 * cl + 1];
-        g2 = b.c_dir[4 * cl + 2];
-        mn = b.c_smin[cl];
-        n = b.c_size[cl];
-      }
-      for (int v = 0; v < kFinThreads / kWave; ++v) {
-        const float* r = s_red[v][j];
-        sS += r[0];
-        g0 += r[1];
-        g1 += r[2];
-        g2 += r[3];
-        mn = fminf(mn, r[4]);
-        n += (int)r[5];
-      }
-      b.c_cost[cl] = sS;
-      b.c_dir[4 * cl] = g0;
-      b.c_dir[4 * cl + 1] = g1;
-      b.c_dir[4 * cl + 2] = g2;
-      b.c_smin[cl] = mn;
-      b.c_size[cl] = n;
-      if (c0 == 0) {  // the first kStatClusters clusters' totals stay in LDS for the means
-        s_tot[j][0] = sS;
-        s_tot[j][1] = g0;
-        s_tot[j][2] = g1;
-        s_tot[j][3] = g2;
-        s_tot[j][5] = (float)n;
-      }
-    }
-    __syncthreads();
+    });
+}
+
+struct ClusterMean {
+  float cost;
+  float4 dir;
+};
+template <int P>
+__device__ __forceinline__ ClusterMean cluster_mean(const Cfg& c, float sc, float sx, float sy, float sz, float n) {
+  const float vx = sx / n, vy = sy / n, vz = P == 3 ? sz / n : 0.f;
+  const float nv = sqrtf(__builtin_fmaf(vz, vz, __builtin_fmaf(vy, vy, vx * vx))) + c.norm_eps;
+  ClusterMean m;
+  m.cost = sc / n;
+  m.dir = make_float4(vx / nv, vy / nv, P == 3 ? vz / nv : 0.f, 0.f);
+  return m;
+}
+
+template <int P>
+__device__ void direct_means(const Cfg& c, const Bufs& b, int M) {
+  for (int cl = threadIdx.x; cl < M; cl += kFinThreads) {
+    float4* d = reinterpret_cast<float4*>(b.c_dir) + cl;
+    const float4 v = *d;
+    const ClusterMean m = cluster_mean<P>(c, b.c_cost[cl], v.x, v.y, v.z, (float)b.c_size[cl]);
+    b.c_cost[cl] = m.cost;
+    *d = m.dir;
   }
 }
 
-// Point data of one labelling chunk (points a0 + u * kFinThreads + threadIdx.x):
-// neighbour count, the point whose root gives the label (itself if core,
-// its lowest-index core neighbour if border, -1 if noise), and with stats
-// its cost and direction.
+// Point data of point a for the labels: neighbour count, the point whose root
+// gives the label (itself if core, its lowest-index core neighbour if border,
+// -1 if noise), and with stats its cost and direction.
 template <int P>
-__device__ __forceinline__ void label_loads(const Cfg& c, const Bufs& b, int a0, int V, bool stats,
-                                            int (&nc)[kLabBatch], int (&x)[kLabBatch], float (&Sa)[kLabBatch],
-                                            typename ZVec<P>::T (&ga)[kLabBatch]) {
+__device__ __forceinline__ void label_loads(const Cfg& c, const Bufs& b, int a, int V, bool stats, int& nc, int& x,
+                                            float& Sa, typename ZVec<P>::T& ga) {
   using ZT = typename ZVec<P>::T;
   const ZT* gv = reinterpret_cast<const ZT*>(b.gv);
-#pragma unroll
-  for (int u = 0; u < kLabBatch; ++u) {
-    const int a = a0 + u * kFinThreads + threadIdx.x;
-    nc[u] = a < V ? b.ncount[a] : 0;
-    const int mc = a < V ? b.mcn[a] : kInt32Max;
-    x[u] = a >= V ? -1 : (nc[u] >= c.min_pts ? a : (mc != kInt32Max ? mc : -1));
-    Sa[u] = (stats && a < V) ? b.Sv[a] : 0.f;
-    ga[u] = (stats && a < V) ? gv[a] : ZT{};
-  }
+  nc = a < V ? b.ncount[a] : 0;
+  const int mc = a < V ? b.mcn[a] : kInt32Max;
+  x = a >= V ? -1 : (nc >= c.min_pts ? a : (mc != kInt32Max ? mc : -1));
+  Sa = (stats && a < V) ? b.Sv[a] : 0.f;
+  ga = (stats && a < V) ? gv[a] : ZT{};
 }
 
+// Block bx labels the points bx * kChunk .. and sums their cluster
+// statistics.  Every block forms the closure of the tree graph by itself (one
+// wave, a few steps): one block over all points took 16.4 us at 19,000 points
+// where this takes the time of one chunk.  With more trees than the graph
+// holds, block 0 alone runs the union-find and takes every chunk.
 template <int P>
-__device__ __forceinline__ void tree_cc_body(const Cfg& c, const Bufs& b, int bx, int by, int nbx, const float* __restrict__ zin, int Vin, int* mout, int* lab_out, int* cnt_out) {
+__device__ __forceinline__ void tree_cc_body(const Cfg& c, const Bufs& b, int bx, const float* __restrict__ zin, int Vin, int* mout, int* lab_out, int* cnt_out) {
   using ZT = typename ZVec<P>::T;
   __shared__ int s_woff[kMaxWords];
   __shared__ unsigned long long s_rm[kMaxWords];
@@ -1244,30 +1256,25 @@ __device__ __forceinline__ void tree_cc_body(const Cfg& c, const Bufs& b, int bx
   __shared__ int s_tc[kMaxTrees];
   __shared__ int s_M;
   __shared__ float s_red[kFinThreads / kWave][kStatClusters][6];
-  __shared__ float s_tot[kStatClusters][6];
   const int V = dbscan_V(b, zin, Vin);
-  // the first labelling chunk's point data and roots do not depend on the
-  // tree numbering or the closure: they are requested first, so their loads
-  // overlap those steps (the union-find fallback rewrites the roots; it
-  // reloads them)
+  if (bx > 0 && bx * kChunk >= V) return;
+  // the chunk's point data and roots do not depend on the tree numbering or
+  // the closure: they are requested first, so their loads overlap those steps
   const bool stats_pts = zin == nullptr;
-  int nc0[kLabBatch], x0[kLabBatch], r0[kLabBatch];
-  float S0[kLabBatch];
-  ZT g0[kLabBatch];
-  label_loads<P>(c, b, 0, V, stats_pts, nc0, x0, S0, g0);
+  const int a0 = bx * kChunk + (int)threadIdx.x;
+  int nc, x;
+  float Sa;
+  ZT ga;
+  label_loads<P>(c, b, a0, V, stats_pts, nc, x, Sa, ga);
   unsigned long long rw[1];
   int wlo, whi;
   root_words<kFinThreads, 1>(b, V, rw, wlo, whi);
   const unsigned long long tadj0 = threadIdx.x < kMaxTrees ? b.tadj[threadIdx.x] : 0ull;
-#pragma unroll
-  for (int u = 0; u < kLabBatch; ++u) r0[u] = x0[u] >= 0 ? b.root[x0[u]] : -1;
+  const int r0 = x >= 0 ? b.root[x] : -1;
   const int R = V > 0 ? tree_prefix_of<kFinThreads, 1>(rw, wlo, whi, s_woff, s_rm) : 0;
   const bool overflow = R > kMaxTrees;
-  if (threadIdx.x == 0) {
-    b.ctrl->n_trees = R;
-    b.ctrl->tree_overflow = overflow ? 1 : 0;
-    s_M = R <= 1 ? R : 0;
-  }
+  if (overflow && bx > 0) return;
+  if (threadIdx.x == 0) s_M = R <= 1 ? R : 0;
   if (threadIdx.x < kMaxTrees) s_tc[threadIdx.x] = 0;
   __syncthreads();
   if (R >= 2 && !overflow) {
@@ -1305,11 +1312,9 @@ __device__ __forceinline__ void tree_cc_body(const Cfg& c, const Bufs& b, int bx
     // exact fallback; clusters = components ranked by their root (lowest core
     // index), the number of each root parked in label[root]
     uf_fallback<P>(c, b, zin, V);
-#pragma unroll
-    for (int u = 0; u < kLabBatch; ++u) r0[u] = x0[u] >= 0 ? b.root[x0[u]] : -1;
     int base = 0;
-    for (int a0 = 0; a0 < V; a0 += kFinThreads) {
-      const int a = a0 + threadIdx.x;
+    for (int q0 = 0; q0 < V; q0 += kFinThreads) {
+      const int a = q0 + threadIdx.x;
       const int isr = (a < V && b.ncount[a] >= c.min_pts && b.root[a] == a) ? 1 : 0;
       int tot;
       const int ex = block_excl_scan<kFinThreads>(isr, &tot);
@@ -1321,75 +1326,50 @@ __device__ __forceinline__ void tree_cc_body(const Cfg& c, const Bufs& b, int bx
     __syncthreads();
   }
   const int M = s_M;
-  if (threadIdx.x == 0) {
-    b.ctrl->M = M;
+  const bool direct = M > kStatClusters;  // (only after the union-find)
+  if (bx == 0 && threadIdx.x == 0) {
+    Ctrl* ct = b.ctrl;
+    ct->n_trees = R;
+    ct->tree_overflow = overflow ? 1 : 0;
+    ct->M = M;
+    ct->stat_direct = direct ? 1 : 0;
     if (mout) *mout = M;
   }
   // labels: core -> cluster of its tree (or component), border -> cluster of
-  // its lowest-index core neighbour, noise -> -1.  In the fallback the
-  // cluster number of a root sits in label[root] and is never overwritten
-  // (a root's own label is that same number).  Each thread takes kLabBatch
-  // points at a time and issues all their loads before any store.  On the
-  // feasible set of a replan the cluster statistics follow, chunk by chunk.
+  // its lowest-index core neighbour, noise -> -1.  On the feasible set of a
+  // replan the cluster statistics follow.
   const bool stats = stats_pts && M > 0;
-  for (int a0 = 0; a0 < V; a0 += kFinThreads * kLabBatch) {
-    int nc[kLabBatch], x[kLabBatch], r[kLabBatch], lab[kLabBatch];
-    float Sa[kLabBatch];
-    ZT ga[kLabBatch];
-    if (a0 == 0) {
-#pragma unroll
-      for (int u = 0; u < kLabBatch; ++u) {
-        nc[u] = nc0[u];
-        x[u] = x0[u];
-        r[u] = r0[u];
-        Sa[u] = S0[u];
-        ga[u] = g0[u];
-      }
-    } else {
-      label_loads<P>(c, b, a0, V, stats_pts, nc, x, Sa, ga);
-#pragma unroll
-      for (int u = 0; u < kLabBatch; ++u) r[u] = x[u] >= 0 ? b.root[x[u]] : -1;
+  if (!overflow) {
+    const int lab = r0 < 0 ? -1 : (R == 1 ? 0 : s_tc[tree_id(s_rm, s_woff, r0)]);
+    if (a0 < V) {
+      b.label[a0] = lab;
+      if (lab_out) lab_out[a0] = lab;
+      if (cnt_out) cnt_out[a0] = nc;
     }
-#pragma unroll
-    for (int u = 0; u < kLabBatch; ++u) {
-      if (r[u] < 0) lab[u] = -1;
-      else if (overflow) lab[u] = b.label[r[u]];
-      else lab[u] = R == 1 ? 0 : s_tc[tree_id(s_rm, s_woff, r[u])];
-    }
-#pragma unroll
-    for (int u = 0; u < kLabBatch; ++u) {
-      const int a = a0 + u * kFinThreads + threadIdx.x;
-      if (a >= V) continue;
-      const bool core = nc[u] >= c.min_pts;
-      if (!(overflow && core && r[u] == a)) b.label[a] = lab[u];
-      if (lab_out) lab_out[a] = lab[u];
-      if (cnt_out) cnt_out[a] = nc[u];
-    }
-    if (stats) chunk_stats<P>(b, a0 == 0, M, lab, Sa, ga, s_red, s_tot);
+    if (stats) chunk_stats<P>(b, bx, M, lab, Sa, ga, s_red);
+    return;
   }
-  // means: cost (Alg. 1 [Cluster stats]) and normalised direction (Eq. (16)),
-  // from the totals in LDS (clusters past kStatClusters from global memory)
-  if (stats && (int)threadIdx.x < kStatClusters) {
-    for (int cl = threadIdx.x; cl < M; cl += kStatClusters) {
-      const bool lds = cl < kStatClusters;
-      const float cnt = lds ? s_tot[cl][5] : (float)b.c_size[cl];
-      const float sx = lds ? s_tot[cl][1] : b.c_dir[4 * cl], sy = lds ? s_tot[cl][2] : b.c_dir[4 * cl + 1];
-      const float sz = lds ? s_tot[cl][3] : b.c_dir[4 * cl + 2];
-      const float sc = lds ? s_tot[cl][0] : b.c_cost[cl];
-      const float vx = sx / cnt, vy = sy / cnt;
-      const float vz = P == 3 ? sz / cnt : 0.f;
-      const float nv = sqrtf(__builtin_fmaf(vz, vz, __builtin_fmaf(vy, vy, vx * vx))) + c.norm_eps;
-      b.c_cost[cl] = sc / cnt;
-      b.c_dir[4 * cl] = vx / nv;
-      b.c_dir[4 * cl + 1] = vy / nv;
-      b.c_dir[4 * cl + 2] = P == 3 ? vz / nv : 0.f;
+  // The cluster number of a root sits in label[root] and is never overwritten
+  // (a root's own label is that same number).
+  for (int q = 0; q * kChunk < V; ++q) {
+    const int a = q * kChunk + (int)threadIdx.x;
+    label_loads<P>(c, b, a, V, stats_pts, nc, x, Sa, ga);
+    const int r = x >= 0 ? b.root[x] : -1;
+    const int lab = r < 0 ? -1 : b.label[r];
+    if (a < V) {
+      if (!(nc >= c.min_pts && r == a)) b.label[a] = lab;
+      if (lab_out) lab_out[a] = lab;
+      if (cnt_out) cnt_out[a] = nc;
     }
+    if (stats && direct) chunk_stats_many<P>(b, q == 0, M, lab, Sa, ga, s_red);
+    else if (stats) chunk_stats<P>(b, q, M, lab, Sa, ga, s_red);
   }
+  if (stats && direct) direct_means<P>(c, b, M);
 }
 
 template <int P>
 __global__ __launch_bounds__(kFinThreads) void k_tree_cc(Cfg c, Bufs b, const float* __restrict__ zin, int Vin, int* mout, int* lab_out, int* cnt_out) {
-  tree_cc_body<P>(c, b, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, zin, Vin, mout, lab_out, cnt_out);
+  tree_cc_body<P>(c, b, (int)blockIdx.x, zin, Vin, mout, lab_out, cnt_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1408,23 +1388,29 @@ __global__ __launch_bounds__(kFinThreads) void k_tree_cc(Cfg c, Bufs b, const fl
 // end, and the points off the ring, are decided by the distance test: the
 // same FP32 expression as in every other DBSCAN pass, so the neighbour graph
 // is the same, and so are the counts, the core flags and the labels.
-//  bin    (in the compaction) each feature's bucket and its slot there
-//  count  (K1, every block of k_wdbscan) the sorted order by bucket; count
-//         = ring points of the inner window (two bucket starts) + hits among
-//         the boundary buckets and the off-ring points: exact; the lowest
-//         core index of every bucket
-//  cc     (K2, the last block of k_wdbscan to finish K1) core buckets at most
-//         w_g apart hold core points that are neighbours for certain, so a
-//         run of such buckets is connected; two adjacent runs more than w_gout apart are not, and
-//         runs in between are linked if one core pair across the gap is;
-//         off-ring core points join through their own tests (union-find).
-//         The lowest-index core neighbour of a non-core point is a range
-//         minimum of the bucket minima over its inner window, then its
-//         boundary buckets and the off-ring points.  Components are
-//         numbered by their lowest core index; labels and cluster
-//         statistics as in k_tree_cc.
-// Work: O(V) window lookups and O(V * points of the boundary buckets) tests,
-// against V^2 / 2 pair tests for the bitmap; one launch instead of four.
+//  bin    (in the compaction) each feature's bucket
+//  label  (k_wlabel, replans) every block counts the points of every bucket in
+//         LDS and finds the buckets whose points are core for certain: the
+//         ring points of the window that all their points share already
+//         number minPts.  Only the points of the other buckets (the open
+//         points) and off the ring get exact counts, by every block for
+//         itself.  Core buckets at most w_g apart hold core points that are
+//         neighbours for certain, so a run of such buckets is connected; two
+//         adjacent runs more than w_gout apart are not; off-ring core points
+//         join through their own tests.  The lowest-index core neighbour of a
+//         non-core point is a range minimum of the bucket minima over its
+//         inner window, then its boundary buckets and the off-ring points.
+//         Components are numbered by their lowest core index.  Each block then
+//         labels its own chunk of points and sums their cluster statistics.
+//  Feature sets that leave more open than a block resolves for itself (a gap
+//  between the two bounds, many open or off-ring points, many clusters) take
+//  the general form in the same launch: each block counts its own points
+//  exactly and the last block to finish forms the components and labels.
+//  Stage calls and the neighbour-count diagnostics, which report exact counts
+//  of every point, use the sorted count-and-place pass (wcount_body).
+// Work: O(V) bucket lookups and O(V * points of the boundary buckets) tests
+// at most, against V^2 / 2 pair tests for the bitmap; one launch instead of
+// four.
 
 __device__ __forceinline__ int wmod(int j) { return j & (kWinBins - 1); }
 
@@ -1466,24 +1452,12 @@ __device__ __forceinline__ void win_pos(const int* __restrict__ ws, int j0, int 
   }
 }
 
-// the bucket of sorted position r (ring positions): the last bucket whose
-// start is at most r
-__device__ __forceinline__ int win_bucket_of(const int* s_start, int r) {
-  int lo = 0, hi = kWinBins - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (s_start[mid] <= r) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
 // unwrapped bucket range [lo, hi] (at most kWinBins buckets) holds bucket j
 __device__ __forceinline__ bool win_in(int j, int lo, int hi) { return hi >= lo && wmod(j - lo) <= hi - lo; }
 
 constexpr int kWinZone = 4096;    // zone points a count block keeps in LDS
 
-// K1: counts and the sorted order.  Block i takes the sorted positions
+// Counts and the sorted order (stage calls and diagnostics).  Block i takes the sorted positions
 // [i POS, i POS + POS) (sorted by bucket, then slot; off-ring points last),
 // two threads per position.
 //  - every block scans the bucket counts into LDS (block 0 publishes them);
@@ -1500,7 +1474,7 @@ constexpr int kWinZone = 4096;    // zone points a count block keeps in LDS
 // block.  Writes the counts, the sorted features, indices and counts, and
 // the lowest core index of every bucket (as kWinMaxK - index, an atomic
 // maximum over zero-initialised words).  Called for count blocks bx that
-// hold points (bx < ceil(V / POS)).
+// hold points (bx < ceil(V / POS)), on keys that hold slots (k_wbin).
 __device__ __forceinline__ void wcount_body(const Cfg& c, const Bufs& b, const float* __restrict__ zin, int V,
                                             int bx) {
   constexpr int NT = kFinThreads, POS = kWinPos, PER = kWinBins / NT;
@@ -1746,22 +1720,20 @@ __device__ __forceinline__ void wcount_body(const Cfg& c, const Bufs& b, const f
   }
 }
 
-// lowest index among the core neighbours of zk at sorted positions [p0, p1)
-// (global sorted arrays)
-__device__ __forceinline__ int win_core_min(float2 zk, const Bufs& b, int p0, int p1, float r2, int min_pts,
-                                            int m) {
-  const float2* zs = reinterpret_cast<const float2*>(b.zs);
-  int q = p0;
-  for (; q + 2 <= p1; q += 2) {
-    const float2 a = zs[q], d = zs[q + 1];
-    const int na = b.wnc[q], nd = b.wnc[q + 1];
-    const int ia = b.sid[q], id = b.sid[q + 1];
-    if (na >= min_pts && ZVec<2>::d2(zk, a) <= r2) m = min(m, ia);
-    if (nd >= min_pts && ZVec<2>::d2(zk, d) <= r2) m = min(m, id);
+// Points in bucket order (ring points by bucket, then the off-ring points):
+// position q holds point id(q).  LIST false: the arrays of the sorted
+// count-and-place pass; true: a list of the calling block.
+template <bool LIST>
+struct WinPts {
+  const Bufs& b;
+  const float2* src;          // features by index
+  const unsigned short* lst;  // LIST: index by position
+  __device__ __forceinline__ int id(int q) const { return LIST ? (int)lst[q] : b.sid[q]; }
+  __device__ __forceinline__ float2 z(int q) const {
+    return LIST ? src[lst[q]] : reinterpret_cast<const float2*>(b.zs)[q];
   }
-  if (q < p1 && b.wnc[q] >= min_pts && ZVec<2>::d2(zk, zs[q]) <= r2) m = min(m, b.sid[q]);
-  return m;
-}
+  __device__ __forceinline__ int nc(int q) const { return LIST ? b.ncount[lst[q]] : b.wnc[q]; }
+};
 
 constexpr int kNoCore = kWinMaxK;  // above every index (V <= kWinMaxK)
 
@@ -1773,10 +1745,10 @@ constexpr int kNoCore = kWinMaxK;  // above every index (V <= kWinMaxK)
 // holds a lower core index or there are off-ring points (LDS only); then
 // the core points of the boundary buckets and the off-ring points are
 // tested (every point for an off-ring zk).
-__device__ int win_mcn_wave(const Cfg& c, const Bufs& b, const int* s_bmin, const int* ws, float2 zk, bool ring,
-                            int nring, int V) {
+template <bool LIST>
+__device__ int win_mcn_wave(const Cfg& c, const WinPts<LIST>& pts, const int* s_bmin, const int* ws, float2 zk,
+                            bool ring, int nring, int V) {
   const int lane = (int)(threadIdx.x & (kWave - 1));
-  const float2* zs = reinterpret_cast<const float2*>(b.zs);
   const float r2 = c.eps2;
   int m = kNoCore, mb = -1, mbnd = kNoCore;
   WinRange r{};
@@ -1847,12 +1819,12 @@ __device__ int win_mcn_wave(const Cfg& c, const Bufs& b, const int* s_bmin, cons
     for (int u = 0; u < 4; ++u) {
       const int e = e0 + u * kWave;
       qq[u] = e < tot ? at(e) : -1;
-      nq[u] = qq[u] >= 0 ? b.wnc[qq[u]] : 0;
-      zq[u] = qq[u] >= 0 ? zs[qq[u]] : make_float2(0.f, 0.f);
+      nq[u] = qq[u] >= 0 ? pts.nc(qq[u]) : 0;
+      zq[u] = qq[u] >= 0 ? pts.z(qq[u]) : make_float2(0.f, 0.f);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      if (nq[u] >= c.min_pts && ZVec<2>::d2(zk, zq[u]) <= r2) mt = min(mt, b.sid[qq[u]]);
+      if (nq[u] >= c.min_pts && ZVec<2>::d2(zk, zq[u]) <= r2) mt = min(mt, pts.id(qq[u]));
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) mt = min(mt, __shfl_xor(mt, off, kWave));
@@ -1890,86 +1862,107 @@ __device__ __forceinline__ void win_union(int* parent, int x, int y) {
   }
 }
 
-// Point data of one labelling chunk of the window path (points a0 + u *
-// kFinThreads + threadIdx.x): neighbour count and key; with stats the cost
-// and direction.
-__device__ __forceinline__ void win_label_keys(const Bufs& b, int a0, int V, int (&nc)[kLabBatch],
-                                               int (&key)[kLabBatch]) {
+// Neighbour counts and keys of the points a0 + u * kFinThreads + threadIdx.x,
+// and with stats their costs and directions.
+template <int LB>
+__device__ __forceinline__ void win_label_keys(const Bufs& b, int a0, int V, int (&nc)[LB],
+                                               int (&key)[LB]) {
 #pragma unroll
-  for (int u = 0; u < kLabBatch; ++u) {
+  for (int u = 0; u < LB; ++u) {
     const int a = a0 + u * kFinThreads + threadIdx.x;
     nc[u] = a < V ? b.ncount[a] : 0;
     key[u] = a < V ? b.wkey[a] : -1;
   }
 }
-__device__ __forceinline__ void win_label_stats(const Bufs& b, int a0, int V, bool stats, float (&Sa)[kLabBatch],
-                                                float2 (&ga)[kLabBatch]) {
+template <int LB>
+__device__ __forceinline__ void win_label_stats(const Bufs& b, int a0, int V, bool stats, float (&Sa)[LB],
+                                                float2 (&ga)[LB]) {
   const float2* gv = reinterpret_cast<const float2*>(b.gv);
 #pragma unroll
-  for (int u = 0; u < kLabBatch; ++u) {
+  for (int u = 0; u < LB; ++u) {
     const int a = a0 + u * kFinThreads + threadIdx.x;
     Sa[u] = (stats && a < V) ? b.Sv[a] : 0.f;
     ga[u] = (stats && a < V) ? gv[a] : float2{};
   }
 }
 
-// K2: one 1024-thread block.  Runs of core buckets, the links across their
-// gaps and the off-ring core points give the components; the lowest-index
-// core neighbour of each non-core point (one wave per point) gives the
-// border rule; labels and cluster statistics as in k_tree_cc.  Clears the
-// bucket counts and minima for the next call.
+// The thread index as a value the compiler cannot see through: addresses that
+// follow from it are not carried across the items of a persistent loop (they
+// cost the batched kernel 60 registers and put others in scratch memory).
+__device__ __forceinline__ int item_thread() {
+  int t = (int)threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Components and labels by one 1024-thread block from exact counts.  Runs of
+// core buckets, the links across their gaps and the off-ring core points give
+// the components; the lowest-index core neighbour of each non-core point (one
+// wave per point) gives the border rule; labels as in k_tree_cc.  LIST false:
+// after the sorted count-and-place pass (stage calls), bucket minima in
+// b.wbmin; clears the bucket counts and minima for the next call.  LIST true:
+// the general form of a replan's labelling, bucket starts ws and the point
+// list lst of this block, the off-ring points' keys holding their position;
+// the cluster statistics follow.
+struct WccLds {
+  int lab[kWinBins];              // bucket -> run, then cluster label (-1: no core point)
+  int bmin[kWinBins];             // lowest core index of each bucket (kNoCore: none)
+  int run[kWinMaxRuns];           // run -> lowest core index, then cluster label
+  short mj[kWinMaxRuns], mp[kWinMaxRuns];  // gaps that may link two runs
+  unsigned bits[kWinMaxK / 32];
+  int boff[kWinMaxK / 32];
+  int ncl[kFinThreads];           // non-core points of one labelling round, then their results
+  float red[kFinThreads / kWave][kStatClusters][6];
+  int nmaybe;
+};
+
+template <bool LIST>
 __device__ __forceinline__ void wcc_body(const Cfg& c, const Bufs& b, const float* __restrict__ zin, int V,
-                                         int* mout, int* lab_out, int* cnt_out) {
+                                         int* mout, int* lab_out, int* cnt_out, WccLds& L, const int* ws,
+                                         const unsigned short* lst) {
   using ZT = float2;
   constexpr int PER = kWinBins / kFinThreads;  // buckets per thread
   constexpr int NBW = kWinMaxK / 32;           // words of the component-minimum bitmap
   constexpr int BPT = (NBW + kFinThreads - 1) / kFinThreads;  // of them per thread
   constexpr int NW = kFinThreads / kWave;
+  constexpr int LB = LIST ? 1 : kLabBatch;     // points per thread and labelling round
   static_assert(kWinMaxRuns <= kFinThreads, "one run per thread");
-  __shared__ int s_lab[kWinBins];              // bucket -> run, then cluster label (-1: no core point)
-  __shared__ int s_bmin[kWinBins];             // lowest core index of each bucket (kNoCore: none)
-  __shared__ int s_run[kWinMaxRuns];           // run -> lowest core index, then cluster label
-  __shared__ short s_mj[kWinMaxRuns], s_mp[kWinMaxRuns];  // gaps that may link two runs
-  __shared__ unsigned s_bits[NBW];
-  __shared__ int s_boff[NBW];
-  __shared__ int s_nmaybe;
-  __shared__ int s_ncl[kFinThreads];          // non-core points of one labelling round, then their results
-  __shared__ float s_red[NW][kStatClusters][6];
-  __shared__ float s_tot[kStatClusters][6];
-  const int t = (int)threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
-  if (V == 0) {
-    if (t == 0) {
-      b.ctrl->n_trees = 0;
-      b.ctrl->tree_overflow = 0;
-      b.ctrl->M = 0;
-      if (mout) *mout = 0;
-    }
-    return;
-  }
-  const bool stats_pts = zin == nullptr;
+  const int t = LIST ? item_thread() : (int)threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
+  const bool stats_pts = LIST;
   const float2* zsrc = reinterpret_cast<const float2*>(zin ? zin : b.z);
-  const float2* zs = reinterpret_cast<const float2*>(b.zs);
-  const int* ws = b.wstart;
+  const WinPts<LIST> pts{b, zsrc, lst};
   const float r2 = c.eps2;
   // every independent operand first: the bucket minima and the first
   // labelling chunk's point data
   const int nring = ws[kWinBins];
   int bm[PER];
+  if constexpr (LIST) {
+    for (int i = 0; i < PER; ++i) L.bmin[t * PER + i] = kInt32Max;
+    __syncthreads();
+    for (int a = t; a < V; a += kFinThreads) {
+      const int bk = b.wkey[a] >> kWinShift;
+      if (bk < kWinBins && b.ncount[a] >= c.min_pts) atomicMin(&L.bmin[bk], a);
+    }
+    __syncthreads();
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int v = b.wbmin[t * PER + i];
-    bm[i] = v ? kWinMaxK - v : kInt32Max;
+    for (int i = 0; i < PER; ++i) bm[i] = L.bmin[t * PER + i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int v = b.wbmin[t * PER + i];
+      bm[i] = v ? kWinMaxK - v : kInt32Max;
+    }
   }
-  int nc[kLabBatch], key[kLabBatch];
+  int nc[LB], key[LB];
   win_label_keys(b, 0, V, nc, key);
   const int noff = V - nring;
-  s_run[t] = kInt32Max;
+  L.run[t] = kInt32Max;
 #pragma unroll
   for (int i = 0; i < BPT; ++i)
-    if (t * BPT + i < NBW) s_bits[t * BPT + i] = 0u;
-  if (t == 0) s_nmaybe = 0;
+    if (t * BPT + i < NBW) L.bits[t * BPT + i] = 0u;
+  if (t == 0) L.nmaybe = 0;
 #pragma unroll
-  for (int i = 0; i < PER; ++i) s_bmin[t * PER + i] = min(bm[i], kNoCore);
+  for (int i = 0; i < PER; ++i) L.bmin[t * PER + i] = min(bm[i], kNoCore);
   // the core bucket before each core bucket (cyclic) and the gap to it
   int mine = -1;
 #pragma unroll
@@ -2002,35 +1995,35 @@ __device__ __forceinline__ void wcc_body(const Cfg& c, const Bufs& b, const floa
     if (bm[i] != kInt32Max) {
       cum += st[i];
       const int run = nst == 0 ? 0 : (cum > 0 ? cum - 1 : nst - 1);
-      s_lab[j] = run;
-      atomicMin(&s_run[run], bm[i]);
+      L.lab[j] = run;
+      atomicMin(&L.run[run], bm[i]);
       if (st[i] && nR >= 2 && j - prv[i] <= c.w_gout) {
-        const int q = atomicAdd(&s_nmaybe, 1);
-        s_mj[q] = (short)j;
-        s_mp[q] = (short)prv[i];
+        const int q = atomicAdd(&L.nmaybe, 1);
+        L.mj[q] = (short)j;
+        L.mp[q] = (short)prv[i];
       }
     } else {
-      s_lab[j] = -1;
+      L.lab[j] = -1;
     }
   }
   __syncthreads();
-  const int nmaybe = s_nmaybe;
+  const int nmaybe = L.nmaybe;
   const bool uf = nmaybe > 0 || noff > 0;
   const int stride = kWinMaxRuns + c.K;
   int* parent = b.wuf;
   int* cmin = b.wuf + stride;
   int* olab = b.wuf + 2 * stride;
-  const int nn = nR + noff;  // union-find nodes: runs, then off-ring points by sorted position
+  const int nn = nR + noff;  // union-find nodes: runs, then off-ring points by position
   if (uf) {
     for (int i = t; i < nn; i += kFinThreads) {
       parent[i] = i;
-      cmin[i] = i < nR ? s_run[i]
-                       : (b.wnc[nring + i - nR] >= c.min_pts ? b.sid[nring + i - nR] : kInt32Max);
+      cmin[i] = i < nR ? L.run[i]
+                       : (pts.nc(nring + i - nR) >= c.min_pts ? pts.id(nring + i - nR) : kInt32Max);
     }
     __syncthreads();
     // a gap that may link two runs: core pairs across it, one wave per gap
     for (int gi = wv; gi < nmaybe; gi += NW) {
-      const int j = s_mj[gi], pj = s_mp[gi];
+      const int j = L.mj[gi], pj = L.mp[gi];
       int a0, a1, a2, a3, c0, c1, c2, c3;
       win_pos(ws, j - c.w_gout, pj, a0, a1, a2, a3);
       win_pos(ws, j, pj + c.w_gout, c0, c1, c2, c3);
@@ -2041,33 +2034,33 @@ __device__ __forceinline__ void wcc_body(const Cfg& c, const Bufs& b, const floa
       for (int ia0 = 0; ia0 < na && !hit; ia0 += kWave) {
         const int ia = ia0 + lane;
         const int pa = ia < a1 - a0 ? a0 + ia : a2 + ia - (a1 - a0);
-        const bool ca = ia < na && b.wnc[pa] >= c.min_pts;
-        const float2 za = ia < na ? zs[pa] : make_float2(0.f, 0.f);
+        const bool ca = ia < na && pts.nc(pa) >= c.min_pts;
+        const float2 za = ia < na ? pts.z(pa) : make_float2(0.f, 0.f);
         const unsigned long long acore = __ballot(ca);
         for (int ib0 = 0; ib0 < nb && !hit && acore; ib0 += kWave) {
           const int ib = ib0 + lane;
           const int pb = ib < c1 - c0 ? c0 + ib : c2 + ib - (c1 - c0);
-          const bool cb = ib < nb && b.wnc[pb] >= c.min_pts;
-          const float2 zb = ib < nb ? zs[pb] : make_float2(0.f, 0.f);
+          const bool cb = ib < nb && pts.nc(pb) >= c.min_pts;
+          const float2 zb = ib < nb ? pts.z(pb) : make_float2(0.f, 0.f);
           bool h = false;
           unsigned long long am = acore;
           while (am) {
-            const int L = __ffsll((long long)am) - 1;
+            const int ln = __ffsll((long long)am) - 1;
             am &= am - 1ull;
-            const float2 zl = make_float2(__shfl(za.x, L, kWave), __shfl(za.y, L, kWave));
+            const float2 zl = make_float2(__shfl(za.x, ln, kWave), __shfl(za.y, ln, kWave));
             h |= cb && ZVec<2>::d2(zl, zb) <= r2;
           }
           hit = __ballot(h) != 0ull;
         }
       }
-      if (hit && lane == 0) win_union(parent, s_lab[wmod(pj)], s_lab[j]);
+      if (hit && lane == 0) win_union(parent, L.lab[wmod(pj)], L.lab[j]);
     }
     // off-ring core points: every core neighbour, the whole block on each
     // (a thread unions each node it meets once in a row)
     for (int o = 0; o < noff; ++o) {
       const int po = nring + o;
-      if (b.wnc[po] < c.min_pts) continue;
-      const float2 zo = zs[po];
+      if (pts.nc(po) < c.min_pts) continue;
+      const float2 zo = pts.z(po);
       int prev_node = -1;
       for (int q0 = t; q0 < V; q0 += kFinThreads * 4) {
         int nq[4];
@@ -2075,14 +2068,14 @@ __device__ __forceinline__ void wcc_body(const Cfg& c, const Bufs& b, const floa
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int q = q0 + u * kFinThreads;
-          nq[u] = q < V ? b.wnc[q] : 0;
-          zq[u] = q < V ? zs[q] : make_float2(0.f, 0.f);
+          nq[u] = q < V ? pts.nc(q) : 0;
+          zq[u] = q < V ? pts.z(q) : make_float2(0.f, 0.f);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int q = q0 + u * kFinThreads;
           if (q >= V || q == po || nq[u] < c.min_pts || !(ZVec<2>::d2(zo, zq[u]) <= r2)) continue;
-          const int node = q < nring ? s_lab[b.wkey[b.sid[q]] >> kWinShift] : nR + (q - nring);
+          const int node = q < nring ? L.lab[b.wkey[pts.id(q)] >> kWinShift] : nR + (q - nring);
           if (node != prev_node) win_union(parent, nR + o, node);
           prev_node = node;
         }
@@ -2097,10 +2090,10 @@ __device__ __forceinline__ void wcc_body(const Cfg& c, const Bufs& b, const floa
     __syncthreads();
     for (int i = t; i < nn; i += kFinThreads) {
       const int m = ld_wg(&cmin[i]);
-      if (ld_wg(&parent[i]) == i && m != kInt32Max) atomicOr(&s_bits[m >> 5], 1u << (m & 31));
+      if (ld_wg(&parent[i]) == i && m != kInt32Max) atomicOr(&L.bits[m >> 5], 1u << (m & 31));
     }
   } else if (nR > kWave && t < nR) {
-    atomicOr(&s_bits[s_run[t] >> 5], 1u << (s_run[t] & 31));
+    atomicOr(&L.bits[L.run[t] >> 5], 1u << (L.run[t] & 31));
   }
   __syncthreads();
   // clusters are the components ranked by their lowest core index
@@ -2111,94 +2104,97 @@ __device__ __forceinline__ void wcc_body(const Cfg& c, const Bufs& b, const floa
     M = nR;
     int r = 0;
     if (t < nR) {
-      const int mv = s_run[t];
-      for (int j = 0; j < nR; ++j) r += s_run[j] < mv ? 1 : 0;
+      const int mv = L.run[t];
+      for (int j = 0; j < nR; ++j) r += L.run[j] < mv ? 1 : 0;
     }
     __syncthreads();
-    if (t < nR) s_run[t] = r;
+    if (t < nR) L.run[t] = r;
   } else {
     int npop = 0;
 #pragma unroll
-    for (int i = 0; i < BPT; ++i) npop += t * BPT + i < NBW ? __popc(s_bits[t * BPT + i]) : 0;
+    for (int i = 0; i < BPT; ++i) npop += t * BPT + i < NBW ? __popc(L.bits[t * BPT + i]) : 0;
     int boff = block_excl_scan<kFinThreads>(npop, &M);
 #pragma unroll
     for (int i = 0; i < BPT; ++i)
       if (t * BPT + i < NBW) {
-        s_boff[t * BPT + i] = boff;
-        boff += __popc(s_bits[t * BPT + i]);
+        L.boff[t * BPT + i] = boff;
+        boff += __popc(L.bits[t * BPT + i]);
       }
     __syncthreads();
     auto rank_of = [&](int x) {
       const int w = x >> 5, bit = x & 31;
-      return s_boff[w] + __popc(s_bits[w] & (bit ? (0xffffffffu >> (32 - bit)) : 0u));
+      return L.boff[w] + __popc(L.bits[w] & (bit ? (0xffffffffu >> (32 - bit)) : 0u));
     };
-    if (t < nR) s_run[t] = rank_of(uf ? ld_wg(&cmin[win_find(parent, t)]) : s_run[t]);
+    if (t < nR) L.run[t] = rank_of(uf ? ld_wg(&cmin[win_find(parent, t)]) : L.run[t]);
     if (uf)
       for (int o = t; o < noff; o += kFinThreads)
-        olab[o] = b.wnc[nring + o] >= c.min_pts ? rank_of(ld_wg(&cmin[win_find(parent, nR + o)])) : -1;
+        olab[o] = pts.nc(nring + o) >= c.min_pts ? rank_of(ld_wg(&cmin[win_find(parent, nR + o)])) : -1;
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int j = t * PER + i;
-    if (s_lab[j] >= 0) s_lab[j] = s_run[s_lab[j]];
+    if (L.lab[j] >= 0) L.lab[j] = L.run[L.lab[j]];
   }
+  const bool direct = M > kStatClusters;
   if (t == 0) {
-    b.ctrl->n_trees = nR;
-    b.ctrl->tree_overflow = 0;
-    b.ctrl->M = M;
+    Ctrl* ct = b.ctrl;
+    ct->n_trees = nR;
+    ct->tree_overflow = 0;
+    ct->M = M;
+    ct->stat_direct = direct ? 1 : 0;
     if (mout) *mout = M;
   }
   __syncthreads();
   // labels: core -> its component, border -> the component of its
   // lowest-index core neighbour, noise -> -1; statistics as in k_tree_cc
   const bool stats = stats_pts && M > 0;
-  for (int a0 = 0; a0 < V; a0 += kFinThreads * kLabBatch) {
-    int lab[kLabBatch];
+  for (int a0 = 0; a0 < V; a0 += kFinThreads * LB) {
+    int lab[LB];
     if (a0 > 0) win_label_keys(b, a0, V, nc, key);
     // (requested here, used by the statistics after the border rule)
-    float Sa[kLabBatch];
-    ZT ga[kLabBatch];
-    win_label_stats(b, a0, V, stats_pts && M > 0, Sa, ga);
+    float Sa[LB];
+    ZT ga[LB];
+    win_label_stats(b, a0, V, stats, Sa, ga);
     // non-core points: the key of their lowest-index core neighbour (none:
     // noise).  They are listed in LDS, kFinThreads at a time, and every wave
     // takes list entries in turn, one point per wave.
     int mync = 0;
 #pragma unroll
-    for (int u = 0; u < kLabBatch; ++u) mync += (a0 + u * kFinThreads + t < V && nc[u] < c.min_pts) ? 1 : 0;
+    for (int u = 0; u < LB; ++u) mync += (a0 + u * kFinThreads + t < V && nc[u] < c.min_pts) ? 1 : 0;
     int nnc;
     const int ncb = block_excl_scan<kFinThreads>(mync, &nnc);
     for (int base = 0; base < nnc; base += kFinThreads) {
       int r = ncb;
 #pragma unroll
-      for (int u = 0; u < kLabBatch; ++u) {
+      for (int u = 0; u < LB; ++u) {
         const int a = a0 + u * kFinThreads + t;
         if (a < V && nc[u] < c.min_pts) {
-          if (r >= base && r < base + kFinThreads) s_ncl[r - base] = a;
+          if (r >= base && r < base + kFinThreads) L.ncl[r - base] = a;
           ++r;
         }
       }
       __syncthreads();
       const int n_this = min(kFinThreads, nnc - base);
       for (int i = wv; i < n_this; i += NW) {
-        const int a = s_ncl[i];
+        const int a = L.ncl[i];
         const int ka = b.wkey[a];
-        const int m = win_mcn_wave(c, b, s_bmin, ws, zsrc[a], (ka >> kWinShift) < kWinBins, nring, V);
+        const int m = win_mcn_wave<LIST>(c, pts, L.bmin, ws, zsrc[a], (ka >> kWinShift) < kWinBins, nring, V);
         if (lane == 0) {
           b.mcn[a] = m == kInt32Max ? m : (m & (kWinMaxK - 1));
-          s_ncl[i] = m;
+          L.ncl[i] = m;
         }
       }
       __syncthreads();
       // each owner takes its points' results
       r = ncb;
 #pragma unroll
-      for (int u = 0; u < kLabBatch; ++u) {
+      for (int u = 0; u < LB; ++u) {
         const int a = a0 + u * kFinThreads + t;
         if (a < V && nc[u] < c.min_pts) {
           if (r >= base && r < base + kFinThreads) {
             // (the neighbour's bucket when known, else its key)
-            const int m = s_ncl[r - base], mbk = (m >> kWinShift) - 1;
+            const int m = L.ncl[r - base], mbk = (m >> kWinShift) - 1;
             key[u] = m == kInt32Max ? -1 : (mbk >= 0 ? mbk << kWinShift : b.wkey[m]);
           }
           ++r;
@@ -2207,82 +2203,654 @@ __device__ __forceinline__ void wcc_body(const Cfg& c, const Bufs& b, const floa
       __syncthreads();
     }
 #pragma unroll
-    for (int u = 0; u < kLabBatch; ++u) {
+    for (int u = 0; u < LB; ++u) {
       const int bk = key[u] >> kWinShift;
-      lab[u] = key[u] < 0 ? -1 : (bk < kWinBins ? s_lab[bk] : olab[key[u] & (kWinMaxK - 1)]);
+      lab[u] = key[u] < 0 ? -1 : (bk < kWinBins ? L.lab[bk] : olab[key[u] & (kWinMaxK - 1)]);
     }
 #pragma unroll
-    for (int u = 0; u < kLabBatch; ++u) {
+    for (int u = 0; u < LB; ++u) {
       const int a = a0 + u * kFinThreads + t;
       if (a >= V) continue;
       b.label[a] = lab[u];
       if (lab_out) lab_out[a] = lab[u];
       if (cnt_out) cnt_out[a] = nc[u];
     }
-    if (stats) chunk_stats<2>(b, a0 == 0, M, lab, Sa, ga, s_red, s_tot);
-  }
-  if (stats && t < kStatClusters) {
-    for (int cl = t; cl < M; cl += kStatClusters) {
-      const bool lds = cl < kStatClusters;
-      const float cnt = lds ? s_tot[cl][5] : (float)b.c_size[cl];
-      const float sx = lds ? s_tot[cl][1] : b.c_dir[4 * cl], sy = lds ? s_tot[cl][2] : b.c_dir[4 * cl + 1];
-      const float sc = lds ? s_tot[cl][0] : b.c_cost[cl];
-      const float vx = sx / cnt, vy = sy / cnt;
-      const float nv = sqrtf(__builtin_fmaf(vy, vy, vx * vx)) + c.norm_eps;
-      b.c_cost[cl] = sc / cnt;
-      b.c_dir[4 * cl] = vx / nv;
-      b.c_dir[4 * cl + 1] = vy / nv;
-      b.c_dir[4 * cl + 2] = 0.f;
-    }
-  }
-  // the bucket counts and minima start from zero at the next call
+    if (stats)
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    b.wcnt[t * PER + i] = 0;
-    b.wbmin[t * PER + i] = 0;
+      for (int u = 0; u < LB; ++u) {
+        const int q = a0 / kChunk + u;
+        if (q * kChunk >= V) break;
+        if (direct) chunk_stats_many<2>(b, q == 0, M, lab[u], Sa[u], ga[u], L.red);
+        else chunk_stats<2>(b, q, M, lab[u], Sa[u], ga[u], L.red);
+      }
   }
-  if (t == 0) b.wcnt[kWinBins] = 0;
+  if (stats && direct) direct_means<2>(c, b, M);
+  if constexpr (!LIST) {
+    // the bucket counts and minima start from zero at the next call
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      b.wcnt[t * PER + i] = 0;
+      b.wbmin[t * PER + i] = 0;
+    }
+    if (t == 0) b.wcnt[kWinBins] = 0;
+  }
 }
 
-// The window path in one launch: every block counts and places its share of
-// the sorted positions (K1); the last block to finish, known from a
-// completion ticket taken after a device-scope fence, then runs K2 on what
-// every block wrote.  With no points only block 0 runs (K2's empty case).
-__global__ __launch_bounds__(kFinThreads) void k_wdbscan(Cfg c, Bufs b, const float* __restrict__ zin, int Vin,
-                                                         int* mout, int* lab_out, int* cnt_out) {
-  __shared__ int s_last;
-  const int V = dbscan_V(b, zin, Vin);
-  if (V == 0) {
-    if (blockIdx.x == 0) wcc_body(c, b, zin, 0, mout, lab_out, cnt_out);
-    return;
-  }
-  const int nblk = (V + kWinPos - 1) / kWinPos;
-  if ((int)blockIdx.x >= nblk) return;
-  wcount_body(c, b, zin, V, (int)blockIdx.x);
-  // every wave waits for its stores and atomics to reach the L2 of its XCD;
-  // then one wave writes that L2 back (device-scope release) and takes a
-  // ticket.  The block that takes the last one invalidates its caches
-  // (device-scope acquire) and reads what every block wrote.
+// Completion ticket: true in every thread of the last of nblk blocks to call
+// it, which then sees what every block wrote before.  Every wave waits for its
+// stores and atomics to reach the L2 of its XCD; then one wave writes that L2
+// back (device-scope release) and takes a ticket, and the block that takes the
+// last one invalidates its caches (device-scope acquire).
+__device__ __forceinline__ bool last_block(int* ticket, int nblk, int* s_last) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    s_last = __hip_atomic_fetch_add(&b.ctrl->wticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nblk - 1;
-    if (s_last) {
+    const int l = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nblk - 1;
+    if (l) {
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      b.ctrl->wticket = 0;  // for the next call
+      *ticket = 0;  // for the next call
+    }
+    *s_last = l;
+  }
+  __syncthreads();
+  return *s_last != 0;
+}
+
+// Stage calls: every block counts and places its share of the sorted
+// positions; the last block to finish then forms components and labels.
+__global__ __launch_bounds__(kFinThreads) void k_wdbscan(Cfg c, Bufs b, const float* __restrict__ zin, int V,
+                                                         int* mout, int* lab_out, int* cnt_out) {
+  __shared__ int s_last;
+  __shared__ WccLds L;
+  const int nblk = (V + kWinPos - 1) / kWinPos;
+  if ((int)blockIdx.x >= nblk) return;
+  wcount_body(c, b, zin, V, (int)blockIdx.x);
+  if (!last_block(&b.ctrl->wticket, nblk, &s_last)) return;
+  wcc_body<false>(c, b, zin, V, mout, lab_out, cnt_out, L, b.wstart, nullptr);
+}
+
+// bucket and slot of every point: the slot is its arrival order in the bucket
+// (any order serves: no result depends on it); zin null: the features of the
+// last replan
+__global__ __launch_bounds__(256) void k_wbin(Cfg c, Bufs b, const float* __restrict__ zin, int Vin) {
+  const int a = (int)blockIdx.x * 256 + (int)threadIdx.x;
+  if (a >= dbscan_V(b, zin, Vin)) return;
+  const int bkt = win_bin(c, reinterpret_cast<const float2*>(zin ? zin : b.z)[a]);
+  const int slot = atomicAdd(&b.wcnt[bkt], 1);
+  b.wkey[a] = (bkt << kWinShift) | slot;
+}
+
+// exact counts of the last replan's features, and the cleared bucket arrays
+// (diagnostics)
+__global__ __launch_bounds__(kFinThreads) void k_wcount(Cfg c, Bufs b) {
+  const int V = dbscan_V(b, nullptr, 0);
+  if ((int)blockIdx.x * kWinPos >= V) return;
+  wcount_body(c, b, nullptr, V, (int)blockIdx.x);
+}
+__global__ __launch_bounds__(256) void k_wclear(Bufs b) {
+  const int i = (int)blockIdx.x * 256 + (int)threadIdx.x;
+  if (i <= kWinBins) b.wcnt[i] = 0;
+  if (i < kWinBins) b.wbmin[i] = 0;
+}
+
+// ---------------------------------------------------------------------------
+// Labelling of a replan's feasible set on the angular windows.
+struct WinFast {
+  int bmin[kWinBins];            // lowest index, then lowest core index, of each bucket (kNoCore: none)
+  int lab[kWinBins];             // bucket -> run, then cluster label (-1: no core point)
+  unsigned char open[kWinBins];  // the bucket's points are open
+  unsigned char zone[kWinBins];  // a boundary bucket of an open point
+  int run[kWave], rank[kWave];   // runs: lowest core index; cluster number
+  // open ring points: index, feature, bucket, count, label if not core
+  int uk[kOpenMax], ub[kOpenMax], uc[kOpenMax], ul[kOpenMax];
+  float2 uz[kOpenMax];
+  // points of the boundary buckets: index, bucket | (open position + 1) << 16
+  int zk[kZoneMax], zb[kZoneMax];
+  float2 zz[kZoneMax];
+  // off-ring points: index, count, label, feature
+  int ok[kOffMax], oc[kOffMax], ol[kOffMax];
+  float2 oz[kOffMax];
+  unsigned long long omin[kOffMax];
+  // components when off-ring points are core: nodes are the runs, then the
+  // off-ring points
+  int parent[kWave + kOffMax], cmin[kWave + kOffMax];
+  float red[kFinThreads / kWave][kStatClusters][6];
+  int nopen, nu, nz, no, nmaybe, M;
+};
+struct WinGeneral {
+  int cursor[kWinBins + 1];
+  int own[kFinThreads];
+  int last;
+};
+struct WinLds {
+  int start[kWinBins + 2];  // first position of each bucket; [kWinBins]: ring points
+  union {
+    WinFast f;
+    WinGeneral g;
+    WccLds cc;
+  };
+};
+
+__device__ __forceinline__ int lds_find(int* parent, int x) {
+  while (true) {
+    const int p = ld_wg(&parent[x]);
+    if (p == x) return x;
+    x = p;
+  }
+}
+
+// ring points of the buckets lo..hi (unwrapped, at most kWinBins of them)
+__device__ __forceinline__ int win_npts(const int* start, int lo, int hi) {
+  if (hi < lo) return 0;
+  const int m = wmod(lo), x = m + (hi - lo) + 1;
+  return x <= kWinBins ? start[x] - start[m] : start[kWinBins] - start[m] + start[x - kWinBins];
+}
+// ring points that are neighbours of every point of bucket j for certain: the
+// part of the inner window that the points of the bucket share
+__device__ __forceinline__ int win_sure(const Cfg& c, const int* start, int j) {
+  return win_npts(start, (int)ceilf((float)(j + 1) - c.w_in), (int)floorf((float)j + c.w_in) - 1);
+}
+
+// The general form: every block counts its own points exactly (ring points of
+// the inner window from the bucket starts; when these are too few, distance
+// tests against the boundary buckets and the off-ring points from a point list
+// in bucket order that each block makes for itself), and the last block to
+// finish forms components and labels.
+__device__ __forceinline__ void win_general(const Cfg& c, const Bufs& b, int V, int bx, WinLds& L) {
+  const int t = item_thread();
+  const float2* z = reinterpret_cast<const float2*>(b.z);
+  const int nring = L.start[kWinBins];
+  const float r2 = c.eps2;
+  unsigned short* lst = reinterpret_cast<unsigned short*>(b.wzone) + (size_t)bx * c.K;
+  __syncthreads();  // the fast form's arrays are no longer read
+  for (int i = t; i <= kWinBins; i += kFinThreads) L.g.cursor[i] = i < kWinBins ? L.start[i] : nring;
+  __syncthreads();
+  for (int a = t; a < V; a += kFinThreads)
+    lst[atomicAdd(&L.g.cursor[b.wkey[a] >> kWinShift], 1)] = (unsigned short)a;
+  __syncthreads();
+  const int a = bx * kChunk + t;
+  const int bk = a < V ? b.wkey[a] >> kWinShift : 0;
+  int n = 0;
+  if (a < V && bk < kWinBins) {
+    const float2 zk = z[a];
+    const WinRange r = win_range(c, win_u(c, zk));
+    n = win_npts(L.start, r.sl, r.sh);
+    if (n < c.min_pts) {
+      int p[6];
+      win_pos(L.start, r.lb0, r.lb1, p[0], p[1], p[2], p[3]);
+      int q0, q1, q2, q3;
+      win_pos(L.start, r.rb0, r.rb1, q0, q1, q2, q3);
+      auto hits = [&](int e0, int e1) {
+        for (int e = e0; e < e1; e += 4) {
+          float2 zq[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) zq[u] = e + u < e1 ? z[lst[e + u]] : make_float2(1e30f, 1e30f);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) n += ZVec<2>::d2(zk, zq[u]) <= r2 ? 1 : 0;
+        }
+      };
+      hits(p[0], p[1]);
+      hits(p[2], p[3]);
+      hits(q0, q1);
+      hits(q2, q3);
+      hits(nring, V);
+    }
+  }
+  // the block's off-ring points: every point, the whole block on each
+  int nown;
+  const int at = block_excl_scan<kFinThreads>(a < V && bk == kWinBins ? 1 : 0, &nown);
+  if (a < V && bk == kWinBins) L.g.own[at] = a;
+  __syncthreads();
+  for (int i = 0; i < nown; ++i) {
+    const int ao = L.g.own[i];
+    const float2 zo = z[ao];
+    int h = 0;
+    for (int q = t; q < V; q += kFinThreads) h += ZVec<2>::d2(zo, z[q]) <= r2 ? 1 : 0;
+    int tot;
+    (void)block_excl_scan<kFinThreads>(h, &tot);
+    if (a == ao) n = tot;
+  }
+  if (a < V) b.ncount[a] = n;
+  if (!last_block(&b.ctrl->wticket, (V + kChunk - 1) / kChunk, &L.g.last)) return;
+  for (int q = nring + t; q < V; q += kFinThreads) b.wkey[lst[q]] = (kWinBins << kWinShift) | (q - nring);
+  __syncthreads();
+  wcc_body<true>(c, b, nullptr, V, nullptr, nullptr, nullptr, L.cc, L.start, lst);
+}
+
+// Block bx of the labelling: the solution over the buckets, then its own
+// chunk; false (for the whole block) where the set needs the general form.  Bound by latency: a chain of about ten barriers and three load
+// rounds, the same at every size up to the passes over the keys (a key and two
+// LDS updates per 1,024 points).
+__device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, WinLds& L) {
+  constexpr int NT = kFinThreads, PER = kWinBins / NT, KB = 8, NW = NT / kWave;
+  WinFast& F = L.f;
+  const int t = item_thread(), lane = t & (kWave - 1), wv = t / kWave;
+  const float2* z = reinterpret_cast<const float2*>(b.z);
+  // the first keys and the block's own records are requested with the control
+  // words (every array holds K entries)
+  int key0[KB];
+#pragma unroll
+  for (int u = 0; u < KB; ++u) key0[u] = u * NT + t < c.K ? b.wkey[u * NT + t] : 0;
+  const int a = bx * kChunk + t, ac = min(a, c.K - 1);
+  const int keya = b.wkey[ac];
+  const float Sa = b.Sv[ac];
+  const float2 ga = reinterpret_cast<const float2*>(b.gv)[ac];
+  const int V = dbscan_V(b, nullptr, 0);
+  if (bx * kChunk >= V) return true;
+  const bool own = a < V;
+  const float r2 = c.eps2;
+
+  // points and lowest index of every bucket
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    L.start[t * PER + i] = 0;
+    F.bmin[t * PER + i] = kNoCore;
+  }
+  reinterpret_cast<int*>(F.open)[t] = 0;
+  reinterpret_cast<int*>(F.zone)[t] = 0;
+  static_assert(PER == 4, "one word of flags per thread");
+  if (t < kWave) F.run[t] = kInt32Max;
+  if (t < kOffMax) {
+    F.oc[t] = 0;
+    F.omin[t] = ~0ull;
+  }
+  if (t == 0) F.nopen = F.nu = F.nz = F.no = F.nmaybe = 0;
+  __syncthreads();
+  for (int k0 = 0; k0 < V; k0 += NT * KB) {
+    int key[KB];
+#pragma unroll
+    for (int u = 0; u < KB; ++u) {
+      const int k = k0 + u * NT + t;
+      key[u] = k0 == 0 ? key0[u] : (k < V ? b.wkey[k] : 0);
+    }
+#pragma unroll
+    for (int u = 0; u < KB; ++u) {
+      const int k = k0 + u * NT + t, bk = key[u] >> kWinShift;
+      if (k < V && bk < kWinBins) {
+        atomicAdd(&L.start[bk], 1);
+        // (later rounds hold higher indices: most read the minimum and go on)
+        if (k < F.bmin[bk]) atomicMin(&F.bmin[bk], k);
+      }
     }
   }
   __syncthreads();
-  if (!s_last) return;
-  wcc_body(c, b, zin, V, mout, lab_out, cnt_out);
+  int cnt[PER], sum = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    cnt[i] = L.start[t * PER + i];
+    sum += cnt[i];
+  }
+  int nring;
+  int off = block_excl_scan<NT>(sum, &nring);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    L.start[t * PER + i] = off;
+    off += cnt[i];
+  }
+  if (t == 0) L.start[kWinBins] = nring;
+  __syncthreads();
+  const int noff = V - nring;
+  if (noff > kOffMax) return false;
+  // buckets that the counts leave open, and the boundary buckets of their
+  // points (those of every position in the bucket)
+  bool open[PER];
+  int nopen = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int j = t * PER + i;
+    open[i] = cnt[i] > 0 && win_sure(c, L.start, j) < c.min_pts;
+    if (open[i]) {
+      nopen += cnt[i];
+      F.open[j] = 1;
+      // (the coordinate of a point at the end of the circle may round past it)
+      const float lo = (float)j, hi = (float)(j + 1) + 1e-2f;
+      for (int q = (int)floorf(lo - c.w_out); q < (int)ceilf(hi - c.w_in); ++q) F.zone[wmod(q)] = 1;
+      for (int q = (int)floorf(lo + c.w_in); q <= (int)floorf(hi + c.w_out); ++q) F.zone[wmod(q)] = 1;
+    }
+  }
+  if (nopen) atomicAdd(&F.nopen, nopen);
+  __syncthreads();
+  if (F.nopen > kOpenMax) return false;
+  int mine_u = -1;  // the own point's place among the open or the off-ring points
+  if (F.nopen > 0 || noff > 0) {
+    // list the open points, the points of their boundary buckets and the
+    // off-ring points
+    for (int k0 = 0; k0 < V; k0 += NT * KB) {
+      int key[KB];
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        const int k = k0 + u * NT + t;
+        key[u] = k0 == 0 ? key0[u] : (k < V ? b.wkey[k] : 0);
+      }
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        const int k = k0 + u * NT + t, bk = key[u] >> kWinShift;
+        if (k >= V) continue;
+        if (bk == kWinBins) {
+          const int o = atomicAdd(&F.no, 1);
+          F.ok[o] = k;
+          F.oz[o] = z[k];
+          if (k == a) mine_u = o;
+          continue;
+        }
+        const bool op = F.open[bk] != 0, zn = F.zone[bk] != 0;
+        if (!op && !zn) continue;
+        const float2 zk = z[k];
+        int up = -1;
+        if (op) {
+          up = atomicAdd(&F.nu, 1);
+          F.uk[up] = k;
+          F.ub[up] = bk;
+          F.uz[up] = zk;
+          if (k == a) mine_u = up;
+        }
+        if (zn) {
+          const int zp = atomicAdd(&F.nz, 1);
+          if (zp < kZoneMax) {
+            F.zk[zp] = k;
+            F.zb[zp] = bk | ((up + 1) << 16);
+            F.zz[zp] = zk;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    if (F.nz > kZoneMax) return false;
+    // exact counts: open points, one wave each; off-ring points against every
+    // point, the whole block
+    for (int i = wv; i < F.nu; i += NW) {
+      const float2 zi = F.uz[i];
+      const WinRange r = win_range(c, win_u(c, zi));
+      int n = win_npts(L.start, r.sl, r.sh);
+      for (int e0 = 0; e0 < F.nz; e0 += kWave) {
+        const int e = e0 + lane;
+        bool h = false;
+        if (e < F.nz) {
+          const int bk = F.zb[e] & 0xffff;
+          h = (win_in(bk, r.lb0, r.lb1) || win_in(bk, r.rb0, r.rb1)) && ZVec<2>::d2(zi, F.zz[e]) <= r2;
+        }
+        n += __popcll(__ballot(h));
+      }
+      n += __popcll(__ballot(lane < noff && ZVec<2>::d2(zi, F.oz[min(lane, kOffMax - 1)]) <= r2));
+      if (lane == 0) F.uc[i] = n;
+    }
+    for (int o = 0; o < noff; ++o) {
+      const float2 zo = F.oz[o];
+      int n = 0;
+      for (int k0 = 0; k0 < V; k0 += NT * KB) {
+        float2 zq[KB];
+#pragma unroll
+        for (int u = 0; u < KB; ++u) zq[u] = z[min(k0 + u * NT + t, V - 1)];
+#pragma unroll
+        for (int u = 0; u < KB; ++u)
+          n += __popcll(__ballot(k0 + u * NT + t < V && ZVec<2>::d2(zo, zq[u]) <= r2));
+      }
+      if (lane == 0) atomicAdd(&F.oc[o], n);
+    }
+    // lowest core index of the open buckets
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (open[i]) F.bmin[t * PER + i] = kNoCore;
+    __syncthreads();
+    for (int i = t; i < F.nu; i += NT)
+      if (F.uc[i] >= c.min_pts) atomicMin(&F.bmin[F.ub[i]], F.uk[i]);
+    __syncthreads();
+  }
+  // runs of core buckets: the core bucket before each core bucket (cyclic) and
+  // the gap to it
+  int bm[PER], mine = -1;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    bm[i] = F.bmin[t * PER + i];
+    if (bm[i] != kNoCore) mine = t * PER + i;
+  }
+  int last;
+  int pv = block_excl_max<NT>(mine, &last);
+  int st[PER], prv[PER], nst_mine = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int j = t * PER + i;
+    st[i] = 0;
+    prv[i] = 0;
+    if (bm[i] != kNoCore) {
+      prv[i] = pv >= 0 ? pv : last - kWinBins;
+      st[i] = j - prv[i] > c.w_g ? 1 : 0;
+      pv = j;
+    }
+    nst_mine += st[i];
+  }
+  int nst;
+  int cum = block_excl_scan<NT>(nst_mine, &nst);
+  const int nR = last < 0 ? 0 : max(nst, 1);
+  if (nR > kWave) return false;
+  int run_of[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int j = t * PER + i;
+    run_of[i] = -1;
+    if (bm[i] != kNoCore) {
+      cum += st[i];
+      run_of[i] = nst == 0 ? 0 : (cum > 0 ? cum - 1 : nst - 1);
+      atomicMin(&F.run[run_of[i]], bm[i]);
+      if (st[i] && nR >= 2 && j - prv[i] <= c.w_gout) atomicAdd(&F.nmaybe, 1);
+    }
+    F.lab[j] = run_of[i];
+  }
+  __syncthreads();
+  if (F.nmaybe > 0) return false;
+  bool ocore = false;
+  for (int o = 0; o < noff; ++o) ocore |= F.oc[o] >= c.min_pts;
+  // clusters: the components ranked by their lowest core index
+  if (!ocore) {
+    // the runs are the components; their minima are distinct
+    if (t < nR) {
+      const int mv = F.run[t];
+      int r = 0;
+      for (int j = 0; j < nR; ++j) r += F.run[j] < mv ? 1 : 0;
+      F.rank[t] = r;
+    }
+    if (t < kOffMax) F.ol[t] = -1;
+    if (t == 0) F.M = nR;
+  } else {
+    const int nn = kWave + noff;
+    if (t < nn) {
+      F.parent[t] = t;
+      F.cmin[t] = t < kWave ? (t < nR ? F.run[t] : kInt32Max)
+                            : (F.oc[t - kWave] >= c.min_pts ? F.ok[t - kWave] : kInt32Max);
+    }
+    __syncthreads();
+    for (int o = 0; o < noff; ++o) {
+      if (F.oc[o] < c.min_pts) continue;
+      const float2 zo = F.oz[o];
+      for (int k = t; k < V; k += NT) {
+        const int bk = b.wkey[k] >> kWinShift;
+        if (bk < kWinBins && !F.open[bk] && ZVec<2>::d2(zo, z[k]) <= r2)
+          win_union(F.parent, F.lab[bk], kWave + o);
+      }
+      for (int i = t; i < F.nu; i += NT)
+        if (F.uc[i] >= c.min_pts && ZVec<2>::d2(zo, F.uz[i]) <= r2) win_union(F.parent, F.lab[F.ub[i]], kWave + o);
+      if (t < noff && F.oc[t] >= c.min_pts && ZVec<2>::d2(zo, F.oz[t]) <= r2)
+        win_union(F.parent, kWave + t, kWave + o);
+    }
+    __syncthreads();
+    if (t < nn && F.cmin[t] != kInt32Max) {
+      const int rt = win_find(F.parent, t), m = ld_wg(&F.cmin[t]);
+      if (rt != t) atomicMin(&F.cmin[rt], m);
+    }
+    __syncthreads();
+    int r = -1, M = 0;
+    if (t < nn) {
+      const int mv = F.cmin[win_find(F.parent, t)];
+      const bool node = F.cmin[t] != kInt32Max;
+      r = 0;
+      for (int j = 0; j < nn; ++j) {
+        const bool head = F.parent[j] == j && F.cmin[j] != kInt32Max;
+        M += head ? 1 : 0;
+        r += head && F.cmin[j] < mv ? 1 : 0;
+      }
+      if (!node) r = -1;
+    }
+    if (t < nR) F.rank[t] = r;
+    if (t >= kWave && t < nn) F.ol[t - kWave] = r;
+    if (t == 0) F.M = M;
+  }
+  __syncthreads();
+  const int M = F.M;
+  if (M > kStatClusters) return false;
+#pragma unroll
+  for (int i = 0; i < PER; ++i)
+    if (run_of[i] >= 0) F.lab[t * PER + i] = F.rank[run_of[i]];
+  __syncthreads();
+  // border rule: the lowest-index core neighbour of every open point that is
+  // not core (one wave each) and of every off-ring point that is not
+  for (int i = wv; i < F.nu; i += NW) {
+    if (F.uc[i] >= c.min_pts) continue;
+    const float2 zi = F.uz[i];
+    const WinRange r = win_range(c, win_u(c, zi));
+    int m = kNoCore, lb = -1;
+    auto take = [&](int k, int l) {
+      if (k < m) {
+        m = k;
+        lb = l;
+      }
+    };
+    for (int j = r.sl + lane; j <= r.sh; j += kWave) take(F.bmin[wmod(j)], F.lab[wmod(j)]);
+    for (int e = lane; e < F.nz; e += kWave) {
+      const int bk = F.zb[e] & 0xffff, up = (F.zb[e] >> 16) - 1;
+      if ((win_in(bk, r.lb0, r.lb1) || win_in(bk, r.rb0, r.rb1)) && (up < 0 || F.uc[up] >= c.min_pts) &&
+          ZVec<2>::d2(zi, F.zz[e]) <= r2)
+        take(F.zk[e], F.lab[bk]);
+    }
+    if (lane < noff && F.oc[lane] >= c.min_pts && ZVec<2>::d2(zi, F.oz[lane]) <= r2) take(F.ok[lane], F.ol[lane]);
+    int mm = m;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) mm = min(mm, __shfl_xor(mm, d, kWave));
+    // (an index belongs to one lane unless none was found)
+    if (m == mm && (mm != kNoCore || lane == 0)) F.ul[i] = mm == kNoCore ? -1 : lb;
+  }
+  for (int o = 0; o < noff; ++o) {
+    if (F.oc[o] >= c.min_pts) continue;
+    const float2 zo = F.oz[o];
+    unsigned long long m = ~0ull;
+    auto take = [&](int k, int l) {
+      const unsigned long long v = ((unsigned long long)(unsigned)k << 32) | (unsigned)l;
+      m = v < m ? v : m;
+    };
+    for (int k = t; k < V; k += NT) {
+      const int bk = b.wkey[k] >> kWinShift;
+      if (bk < kWinBins && !F.open[bk] && ZVec<2>::d2(zo, z[k]) <= r2) {
+        take(k, F.lab[bk]);
+        break;  // (ascending: the first is the lowest)
+      }
+    }
+    for (int i = t; i < F.nu; i += NT)
+      if (F.uc[i] >= c.min_pts && ZVec<2>::d2(zo, F.uz[i]) <= r2) take(F.uk[i], F.lab[F.ub[i]]);
+    if (t < noff && F.oc[t] >= c.min_pts && ZVec<2>::d2(zo, F.oz[t]) <= r2) take(F.ok[t], F.ol[t]);
+    if (m != ~0ull) atomicMin(&F.omin[o], m);
+  }
+  __syncthreads();
+  // the block's own chunk
+  const int bk = keya >> kWinShift;
+  int lab = -1, n = 0;
+  if (own) {
+    if (bk == kWinBins) {
+      n = F.oc[mine_u];
+      lab = n >= c.min_pts ? F.ol[mine_u] : (F.omin[mine_u] == ~0ull ? -1 : (int)(unsigned)F.omin[mine_u]);
+    } else if (F.open[bk]) {
+      n = F.uc[mine_u];
+      lab = n >= c.min_pts ? F.lab[bk] : F.ul[mine_u];
+    } else {
+      n = win_sure(c, L.start, bk);
+      lab = F.lab[bk];
+    }
+    b.label[a] = lab;
+    b.ncount[a] = n;
+  }
+  if (bx == 0 && t == 0) {
+    Ctrl* ct = b.ctrl;
+    ct->n_trees = nR;
+    ct->tree_overflow = 0;
+    ct->M = M;
+    ct->stat_direct = 0;
+  }
+  if (M > 0) chunk_stats<2>(b, bx, M, lab, Sa, ga, F.red);
+  return true;
 }
 
-// bucket and slot of caller features (stage calls; replans bin in the compaction)
-__global__ __launch_bounds__(256) void k_wbin(Cfg c, Bufs b, const float* __restrict__ zin, int V) {
-  const int a = (int)blockIdx.x * 256 + (int)threadIdx.x;
-  if (a >= V) return;
-  win_bin(c, b, reinterpret_cast<const float2*>(zin)[a], a);
+__device__ __forceinline__ void wlabel_body(const Cfg& c, const Bufs& b, int bx, WinLds& L) {
+  if (!win_fast(c, b, bx, L)) win_general(c, b, dbscan_V(b, nullptr, 0), bx, L);
+}
+
+__global__ __launch_bounds__(kFinThreads) void k_wlabel(Cfg c, Bufs b) {
+  __shared__ WinLds L;
+  wlabel_body(c, b, (int)blockIdx.x, L);
+}
+
+// ---------------------------------------------------------------------------
+// Statistics of cluster threadIdx.x from the chunk sums (chunks in ascending
+// order; pre: the first kStatBatch chunks of field threadIdx.x % kStatFields of
+// cluster threadIdx.x / kStatFields, requested ahead), or from the cluster
+// arrays when one block has summed them.  publish: also write the cluster
+// arrays.
+struct ClusterStat {
+  float cost, smin;
+  float4 dir;
+};
+__device__ __forceinline__ float (*stat_lds())[kStatFields] {
+  __shared__ float s_tot[kStatClusters][kStatFields];
+  return s_tot;
+}
+__device__ __forceinline__ ClusterStat cluster_stats(const Cfg& c, const Bufs& b, int M, int V,
+                                                     const float (&pre)[kStatBatch], bool publish) {
+  ClusterStat r;
+  r.cost = r.smin = INFINITY;
+  r.dir = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int t = threadIdx.x;
+  if (M > kStatClusters) {  // b.ctrl->stat_direct
+    r.cost = b.c_cost[t < M ? t : 0];
+    r.smin = b.c_smin[t < M ? t : 0];
+    r.dir = reinterpret_cast<const float4*>(b.c_dir)[t < M ? t : 0];
+    return r;
+  }
+  float (*s_tot)[kStatFields] = stat_lds();
+  const int nch = (V + kChunk - 1) / kChunk, f = t % kStatFields;
+  for (int i = t; i < M * kStatFields; i += kUpdThreads) {
+    float v = 0.f;
+    for (int q0 = 0; q0 < nch; q0 += kStatBatch) {
+      float x[kStatBatch];
+#pragma unroll
+      for (int q = 0; q < kStatBatch; ++q)
+        x[q] = (q0 == 0 && i == t) ? pre[q]
+                                   : b.stat[(size_t)min(q0 + q, nch - 1) * (kStatClusters * kStatFields) + i];
+#pragma unroll
+      for (int q = 0; q < kStatBatch; ++q) {
+        if (q0 + q >= nch) break;
+        v = q0 + q == 0 ? x[q] : (f == 4 ? fminf(v, x[q]) : v + x[q]);
+      }
+    }
+    s_tot[i / kStatFields][f] = v;
+  }
+  __syncthreads();
+  if (t < M) {
+    const float* v = s_tot[t];
+    const ClusterMean m = c.p == 2 ? cluster_mean<2>(c, v[0], v[1], v[2], v[3], v[5])
+                                   : cluster_mean<3>(c, v[0], v[1], v[2], v[3], v[5]);
+    r.cost = m.cost;
+    r.smin = v[4];
+    r.dir = m.dir;
+    if (publish) {
+      b.c_cost[t] = m.cost;
+      reinterpret_cast<float4*>(b.c_dir)[t] = m.dir;
+      b.c_size[t] = (int)v[5];
+      b.c_smin[t] = v[4];
+    }
+  }
+  return r;
+}
+// size of a cluster (after cluster_stats)
+__device__ __forceinline__ int cluster_size(const Bufs& b, int M, int cl) {
+  return M > kStatClusters ? b.c_size[cl] : (int)stat_lds()[cl][5];
 }
 
 // ---------------------------------------------------------------------------
@@ -2296,8 +2864,8 @@ struct Sel {
   float margin, smin, v[3], vh[3];
 };
 
-// The statistics of cluster threadIdx.x come preloaded (pre_*: requested by
-// the caller before the branch was known); further clusters are loaded here.
+// The statistics of cluster threadIdx.x come loaded; further clusters are
+// loaded here.
 __device__ __forceinline__ Sel select_cluster(const Cfg& c, const Bufs& b, int M, float pre_cost, float pre_mn,
                                               float4 pre_dir) {
   __shared__ float s_k1[kUpdThreads / kWave], s_k2[kUpdThreads / kWave], s_m1[kUpdThreads / kWave];
@@ -2378,7 +2946,7 @@ __device__ __forceinline__ Sel select_cluster(const Cfg& c, const Bufs& b, int M
   for (int w = 1; w < kUpdThreads / kWave; ++w) combine(k1, k2, i1, m1, s_k1[w], s_k2[w], s_i1[w], s_m1[w]);
   if (i1 >= M) {  // no key compared below +inf (infinite or NaN keys): the lowest cluster
     i1 = 0;
-    m1 = b.c_smin[0];
+    m1 = M > kStatClusters ? b.c_smin[0] : stat_lds()[0][4];
   }
   s.sel = i1;
   s.smin = m1;
@@ -2451,10 +3019,12 @@ __device__ __forceinline__ void update_body(const Cfg& c, const Bufs& b, UpdLds&
   const float S_all = b.S[ac];
   const int lab_v = b.label[ac], k_v = b.vidx[ac];
   const float S_v = b.Sv[ac];
-  // and the statistics of cluster threadIdx.x, for the selection
-  const int cq = (int)threadIdx.x < c.mcap ? (int)threadIdx.x : 0;
-  const float pre_cost = b.c_cost[cq], pre_mn = b.c_smin[cq];
-  const float4 pre_dir = reinterpret_cast<const float4*>(b.c_dir)[cq];
+  // and the statistics of the first clusters and chunks, for the selection
+  const int nchunk_k = (c.K + kChunk - 1) / kChunk;
+  float pre[kStatBatch];
+#pragma unroll
+  for (int q = 0; q < kStatBatch; ++q)
+    pre[q] = b.stat[(size_t)min(q, nchunk_k - 1) * (kStatClusters * kStatFields) + threadIdx.x];
   const int branch = ct->branch;
   const bool bad = ct->nonfinite != 0;
   const int NM = c.NM;
@@ -2475,8 +3045,11 @@ __device__ __forceinline__ void update_body(const Cfg& c, const Bufs& b, UpdLds&
     }
   }
   Sel s;
+  int sel_n = 0;
   if (branch == 0 && (a0 < ncand || bx == 0)) {
-    s = select_cluster(c, b, M, pre_cost, pre_mn, pre_dir);
+    const ClusterStat cs = cluster_stats(c, b, M, ncand, pre, bx == 0);
+    s = select_cluster(c, b, M, cs.cost, cs.smin, cs.dir);
+    sel_n = s.sel >= 0 ? cluster_size(b, M, s.sel) : 0;
   } else {
     s.sel = -1;
     s.rule = 0;
@@ -2497,7 +3070,7 @@ __device__ __forceinline__ void update_body(const Cfg& c, const Bufs& b, UpdLds&
       cw->v_obs[i] = s.v[i];
       cw->v_hat[i] = s.vh[i];
     }
-    cw->sel_size = s.sel >= 0 ? b.c_size[s.sel] : 0;
+    cw->sel_size = sel_n;
     cw->smin_sel = s.smin;
   }
   const int sel = s.sel;
@@ -2657,30 +3230,31 @@ __global__ __launch_bounds__(kFinThreads) void kb_plan(CSlotStatic st, PlanOut o
     const int n = *o.n[kd];
     if (n == 0) continue;
     const int q = threadIdx.x;
-    int ncnt = 0, nadj = 0;
+    int ncnt = 0, nadj = 0, nlab = 0;
     if (q < n) {
       const SlotStatic& S = *(const SlotStatic*)(st + o.slot[kd][q]);
       const Ctrl* ct = S.b.ctrl;
       const int V = ct->branch == 0 ? ct->n_feas : 0;
-      if (kd == 2) {
-        // angular windows: the count-and-place blocks
-        ncnt = (V + kWinPos - 1) / kWinPos;
-      } else {
+      nlab = (V + kChunk - 1) / kChunk;
+      if (kd != 2) {
         const int nt = ntiles_of(V);
         ncnt = nt * ((nt + o.colg - 1) / o.colg);
         nadj = nt * ((nt + kColGroup - 1) / kColGroup);
       }
     }
-    int t1, t2;
+    int t1, t2, t3;
     const int e1 = block_excl_scan<kFinThreads>(ncnt, &t1);
     const int e2 = block_excl_scan<kFinThreads>(nadj, &t2);
+    const int e3 = block_excl_scan<kFinThreads>(nlab, &t3);
     if (q < n) {
       o.pref_cnt[kd][q] = e1;
       o.pref_adj[kd][q] = e2;
+      o.pref_lab[kd][q] = e3;
     }
     if (q == 0) {
       o.pref_cnt[kd][n] = t1;
       o.pref_adj[kd][n] = t2;
+      o.pref_lab[kd][n] = t3;
     }
   }
 }
@@ -2742,31 +3316,22 @@ __global__ __launch_bounds__(kTile) void kb_tree_adj(CSlotStatic st, Tab t) {
   });
 }
 
-// angular windows of the 2-D members: the count-and-place blocks of every
-// member, then one block per member for the components and labels (the two
-// phases of k_wdbscan as two launches)
-__global__ __launch_bounds__(kFinThreads) void kb_wcount(CSlotStatic st, Tab t) {
+// angular windows of the 2-D members: the labelling blocks of every member
+__global__ __launch_bounds__(kFinThreads) void kb_wlabel(CSlotStatic st, Tab t) {
   __shared__ int s_pref[kMaxBatch + 1];
+  __shared__ WinLds L;
   for_each_item<kFinThreads>(t, s_pref, [&](int slot, int local) {
     CEMPPI_SLOT(slot);
-    wcount_body(c, b, nullptr, dbscan_V(b, nullptr, 0), local);
-  });
-}
-
-__global__ __launch_bounds__(kFinThreads) void kb_wcc(CSlotStatic st, Tab t) {
-  __shared__ int s_pref[kMaxBatch + 1];
-  for_each_item<kFinThreads>(t, s_pref, [&](int slot, int) {
-    CEMPPI_SLOT(slot);
-    wcc_body(c, b, nullptr, dbscan_V(b, nullptr, 0), nullptr, nullptr, nullptr);
+    wlabel_body(c, b, local, L);
   });
 }
 
 template <int P>
 __global__ __launch_bounds__(kFinThreads) void kb_tree_cc(CSlotStatic st, Tab t) {
   __shared__ int s_pref[kMaxBatch + 1];
-  for_each_item<kFinThreads>(t, s_pref, [&](int slot, int) {
+  for_each_item<kFinThreads>(t, s_pref, [&](int slot, int local) {
     CEMPPI_SLOT(slot);
-    tree_cc_body<P>(c, b, 0, 0, 0, nullptr, 0, nullptr, nullptr, nullptr);
+    tree_cc_body<P>(c, b, local, nullptr, 0, nullptr, nullptr, nullptr);
   });
 }
 
@@ -2814,10 +3379,11 @@ template <int P>
 static void launch_dbscan_p(Launcher& L, const Cfg& c, const Bufs& b, const float* zin, int Vin,
                             int ntile, int* lab_out, int* cnt_out, int* mout) {
   if (P == 2 && use_window(c, b)) {
-    // grid sized for every point the call may have (K for a replan)
-    const int cap = ntile * kTile;
-    L(k_wdbscan, dim3((cap + kWinPos - 1) / kWinPos), dim3(kFinThreads), c, b, zin, Vin, mout,
-      lab_out, cnt_out);
+    if (zin)
+      L(k_wdbscan, dim3((Vin + kWinPos - 1) / kWinPos), dim3(kFinThreads), c, b, zin, Vin, mout, lab_out,
+        cnt_out);
+    else
+      L(k_wlabel, dim3((c.K + kChunk - 1) / kChunk), dim3(kFinThreads), c, b);
     return;
   }
   const int ngrp = (ntile + kColGroup - 1) / kColGroup;
@@ -2847,7 +3413,8 @@ static void launch_dbscan_p(Launcher& L, const Cfg& c, const Bufs& b, const floa
     L(k_mcn<P, 1>, ctiles, tb, c, b, zin, Vin);
     L(k_tree_adj<P, 1>, tiles, tb, c, b, zin, Vin);
   }
-  L(k_tree_cc<P>, dim3(1), dim3(kFinThreads), c, b, zin, Vin, mout, lab_out, cnt_out);
+  L(k_tree_cc<P>, dim3((ntile * kTile + kChunk - 1) / kChunk), dim3(kFinThreads), c, b, zin, Vin, mout, lab_out,
+    cnt_out);
 }
 
 // Everything between the rollouts and the final combination, as one chain
@@ -2900,6 +3467,16 @@ void launch_stage_dbscan(Launcher& L, const Cfg& c, const Bufs& b, const float* 
 }
 
 
+// Exact neighbour counts of the last replan's features on the window path
+// (diagnostics: a replan only needs the core flags, and leaves the counts of
+// core points anywhere between minPts and the count).
+void launch_window_counts(Launcher& L, const Cfg& c, const Bufs& b) {
+  if (!use_window(c, b)) return;
+  L(k_wbin, dim3((c.K + 255) / 256), dim3(256), c, b, (const float*)nullptr, 0);
+  L(k_wcount, dim3((c.K + kWinPos - 1) / kWinPos), dim3(kFinThreads), c, b);
+  L(k_wclear, dim3((kWinBins + 256) / 256), dim3(256), b);
+}
+
 template <int P>
 static void launch_batch_dbscan(Launcher& L, const CSlotStatic cst, const BatchTabs& T, int kd) {
   const dim3 tb(kTile);
@@ -2933,14 +3510,11 @@ void launch_batch_post(Launcher& L, const SlotStatic* st, const SlotIO* io, cons
     else L(kb_compact<2, true>, dim3(T.grid_compact[2]), dim3(256), cst, T.compact[2]);
   }
   L(kb_plan, dim3(1), dim3(kFinThreads), cst, T.plan);
-  if (T.has[2]) {
-    L(kb_wcount, dim3(T.grid_win), dim3(kFinThreads), cst, T.cnt[2]);
-    L(kb_wcc, dim3(T.grid_cc[2]), dim3(kFinThreads), cst, T.cc[2]);
-  }
+  if (T.has[2]) L(kb_wlabel, dim3(T.grid_lab[2]), dim3(kFinThreads), cst, T.lab[2]);
   for (int kd = 0; kd < 2; ++kd) {
     if (!T.has[kd]) continue;
-    if (kd == 0) L(kb_sort<2>, dim3(T.grid_cc[0]), dim3(kFinThreads), cst, T.cc[0]);
-    else L(kb_sort<3>, dim3(T.grid_cc[1]), dim3(kFinThreads), cst, T.cc[1]);
+    if (kd == 0) L(kb_sort<2>, dim3(T.grid_one[0]), dim3(kFinThreads), cst, T.one[0]);
+    else L(kb_sort<3>, dim3(T.grid_one[1]), dim3(kFinThreads), cst, T.one[1]);
   }
   for (int kd = 0; kd < 2; ++kd) {
     if (!T.has[kd]) continue;
@@ -2954,8 +3528,8 @@ void launch_batch_post(Launcher& L, const SlotStatic* st, const SlotIO* io, cons
   }
   for (int kd = 0; kd < 2; ++kd) {
     if (!T.has[kd]) continue;
-    if (kd == 0) L(kb_tree_cc<2>, dim3(T.grid_cc[0]), dim3(kFinThreads), cst, T.cc[0]);
-    else L(kb_tree_cc<3>, dim3(T.grid_cc[1]), dim3(kFinThreads), cst, T.cc[1]);
+    if (kd == 0) L(kb_tree_cc<2>, dim3(T.grid_lab[0]), dim3(kFinThreads), cst, T.lab[0]);
+    else L(kb_tree_cc<3>, dim3(T.grid_lab[1]), dim3(kFinThreads), cst, T.lab[1]);
   }
   L(kb_update, dim3(T.grid_update), dim3(kUpdThreads), cst, T.update);
   L(kb_finish, dim3(T.grid_finish), dim3(kFinThreads), cst, cio, T.finish);

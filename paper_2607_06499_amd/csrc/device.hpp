@@ -68,7 +68,16 @@ constexpr int kLabBatch = 8;   // points per thread per labelling pass
 constexpr int kRecBatch = 4;   // partial records per thread in flight at once
 constexpr int kFinRows = 8;    // update-partial rows per wave in flight at once (final combination)
 constexpr int kFinChunks = (kMaxNM + 1 + 63) / 64;  // 64-element chunks of a partial row, at most
-constexpr int kStatClusters = 64;  // clusters per statistics pass of the labelling block
+constexpr int kChunk = kFinThreads;  // points per labelling block, and per chunk of the cluster statistics
+constexpr int kStatClusters = 64;  // clusters whose chunk sums are kept (more: one block sums them all)
+constexpr int kStatBatch = 8;      // chunks whose sums the selection requests at once
+constexpr int kStatFields = 8;     // floats per (chunk, cluster): cost, direction, minimum cost, count
+// replans on the angular windows: points whose neighbourhood the bucket
+// counts leave open, and the points their boundary buckets hold, that every
+// labelling block resolves by itself; off-ring points likewise
+constexpr int kOpenMax = 512;
+constexpr int kZoneMax = 2048;
+constexpr int kOffMax = 16;
 
 constexpr int kInt32Max = 0x7fffffff;
 
@@ -96,6 +105,7 @@ struct Ctrl {
   uint32_t status;
   uint32_t step_used;
   int32_t wticket;  // completion ticket of the window DBSCAN launch (zero between calls)
+  int32_t stat_direct;  // the cluster arrays hold the final statistics (more than kStatClusters clusters)
 };
 
 // Scalar configuration (kernel argument).
@@ -172,6 +182,7 @@ struct Bufs {
   unsigned long long* coremask;  // [ceil(K/64)] core flags
   unsigned long long* hookmask;  // [ceil(K/64)] core neighbour of lower index found
   // cluster statistics
+  float* stat;     // [ceil(K/kChunk)][kStatClusters][kStatFields] chunk sums per cluster
   float* c_cost;   // [mcap] mean cost
   float* c_dir;    // [mcap][4] normalised mean direction
   int* c_size;     // [mcap]
@@ -181,11 +192,12 @@ struct Bufs {
   // the sorted features and their indices use zs and sid
   int* wcnt;       // [kWinBins + 1] points per bucket (the last: off the ring); zero between calls
   int* wstart;     // [kWinBins + 2] first sorted position of each bucket; [kWinBins] = ring points
-  int* wkey;       // [K] bucket << kWinShift | slot, by compacted index
+  int* wkey;       // [K] bucket << kWinShift (| slot in stage calls), by compacted index
   int* wbmin;      // [kWinBins] kWinMaxK - lowest core index in each bucket (0 if none); zero between calls
   int* wnc;        // [K] neighbour counts by sorted position
   int* wuf;        // [3][kWinMaxRuns + K] union-find parents, component minima, off-ring labels
-  int* wzone;      // [ceil(K / kWinPos)][K] indices of a count block's zone when it exceeds LDS
+  int* wzone;      // [ceil(K / kWinPos)][K] indices of a count block's zone when it exceeds LDS; in
+                   // replans, a labelling block's point list in bucket order (16-bit, K per block)
   float* upart;    // [nblk_upd][NM + 1]
   float* Unew;     // [N][m] updated sequence before the shift
 };
@@ -249,25 +261,25 @@ __device__ __forceinline__ void for_each_item(const Tab& t, int* s_pref, F&& f) 
 
 // Tables of the batched post-rollout phases.  Index kd is the group of
 // planners: p = 2 on the sorted distance passes (0), p = 3 (1), p = 2 on the
-// angular windows (2).  Static tables for compaction and for the tree
-// closure, components and statistics (one item per planner); the DBSCAN
-// tables are filled on the device from each planner's feasible count
-// (PlanOut).  Update and finish run over every planner of the batch.
+// angular windows (2).  Static tables for compaction and for the spatial sort
+// (one item per planner); the DBSCAN tables are filled on the device from
+// each planner's feasible count (PlanOut).  Update and finish run over every planner of the batch.
 constexpr int kPlanKinds = 3;
 struct PlanOut {
   const int* slot[kPlanKinds];  // planners of each group
   const int* n[kPlanKinds];     // their counts (device memory)
-  int* pref_cnt[kPlanKinds];    // count and lowest-core-neighbour tiles (group 2: count blocks)
+  int* pref_cnt[kPlanKinds];    // count and lowest-core-neighbour tiles
   int* pref_adj[kPlanKinds];    // tree-adjacency tiles
+  int* pref_lab[kPlanKinds];    // labelling blocks
   int colg;                     // column tiles per count/mcn item
 };
 
 struct BatchTabs {
-  Tab compact[kPlanKinds], cnt[kPlanKinds], adj[kPlanKinds], cc[kPlanKinds];
+  Tab compact[kPlanKinds], cnt[kPlanKinds], adj[kPlanKinds], one[kPlanKinds], lab[kPlanKinds];
   Tab update, finish;
   PlanOut plan;
-  int grid_compact[kPlanKinds], grid_cc[kPlanKinds], grid_update, grid_finish;
-  int grid_tile, grid_win;
+  int grid_compact[kPlanKinds], grid_one[kPlanKinds], grid_lab[kPlanKinds], grid_update, grid_finish;
+  int grid_tile;
   int colg;
   int has[kPlanKinds];  // the batch has planners of the group (its phases are launched)
 };
