@@ -39,7 +39,7 @@ extern "C" {
 #define CE_MPPI_ABI_VERSION 1u
 #define CE_MPPI_MAX_CTRL 6        /* m                                          */
 #define CE_MPPI_MAX_OBSTACLES 64  /* n_obs per planner                          */
-#define CE_MPPI_MAX_HORIZON 63    /* N: the N+1 states of a rollout share a wave */
+#define CE_MPPI_MAX_HORIZON 63    /* N: the steps of a rollout share a wave      */
 #define CE_MPPI_MAX_HISTORY 16    /* H                                          */
 #define CE_MPPI_MAX_SAMPLES 65536 /* K                                          */
 #define CE_MPPI_MAX_BATCH 1024    /* planners per batch                         */
@@ -396,7 +396,7 @@ ce_status ce_mppi_time_rollout(ce_mppi_planner* planner, const float* x_t, const
  * A batch runs one replan of each of its planners (Alg. 1 for every member,
  * each exactly as ce_mppi_replan would run it) as one graph launch.  Every
  * phase of the replan is one persistent kernel per planner kind (rollout
- * kind: unicycle on 32 or 64 lanes, arm; DBSCAN kind: 2-D on the angular
+ * kind: unicycle, arm; DBSCAN kind: 2-D on the angular
  * windows, 2-D on sorted distance passes, 3-D) whose fixed grid loops over
  * the work items of all members; the DBSCAN work tables are sized on the
  * device from each member's feasible count.  The results of a member are
@@ -424,8 +424,9 @@ typedef struct ce_mppi_batch_io {
 typedef struct ce_mppi_batch_tuning {
   int32_t colg;               /* column tiles per DBSCAN count item: 1,2,4 or 8 */
   int32_t tile_blocks_per_cu; /* persistent blocks per CU, tiled DBSCAN: 1..16  */
-  int32_t roll_blocks_per_cu; /* persistent blocks per CU, rollouts: 1..8       */
-  int32_t roll_per_wave;      /* rollouts per wave per work item: 1, 2, 4 or 8  */
+  int32_t roll_blocks_per_cu; /* persistent blocks per CU, rollouts: 1..8 (a    */
+                              /* batch replan gives unicycle items a block each) */
+  int32_t roll_per_wave;      /* arm rollouts per wave per work item: 1,2,4,8   */
 } ce_mppi_batch_tuning;
 
 /* Create a batch of n distinct planners (1 <= n <= CE_MPPI_MAX_BATCH) on the

@@ -23,7 +23,7 @@
 #include "planner.hpp"
 
 namespace cemppi {
-void launch_batch_rollout(Launcher& L, int kind, int r, const SlotStatic* st, const SlotIO* io, Tab t,
+void launch_batch_rollout(Launcher& L, int kind, int r, bool loop, const SlotStatic* st, const SlotIO* io, Tab t,
                           int grid);
 void launch_batch_post(Launcher& L, const SlotStatic* st, const SlotIO* io, const BatchTabs& T);
 }  // namespace cemppi
@@ -32,12 +32,13 @@ using namespace cemppi;
 
 namespace {
 
+constexpr int kRollKinds = 2;  // rollout kernels: unicycle, arm
 constexpr int kAreas = 4;  // area 0: the full member set; 1..3: subset ring
 
 // Offsets (in ints) of every table inside an area, for n member capacity.
 struct Layout {
-  size_t cnt_roll[3], cnt_p[kPlanKinds], cnt_all;  // table counts n
-  size_t roll_slot[3], roll_pref[3][4];
+  size_t cnt_roll[kRollKinds], cnt_p[kPlanKinds], cnt_all;  // table counts n
+  size_t roll_slot[kRollKinds], roll_pref[kRollKinds][4];
   size_t p_slot[kPlanKinds], compact[kPlanKinds], one[kPlanKinds], dyn_cnt[kPlanKinds], dyn_adj[kPlanKinds],
       dyn_lab[kPlanKinds];
   size_t all_slot, update, finish;
@@ -49,10 +50,10 @@ struct Layout {
       o += k;
       return r;
     };
-    for (int k = 0; k < 3; ++k) cnt_roll[k] = take(1);
+    for (int k = 0; k < kRollKinds; ++k) cnt_roll[k] = take(1);
     for (int kd = 0; kd < kPlanKinds; ++kd) cnt_p[kd] = take(1);
     cnt_all = take(1);
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < kRollKinds; ++k) {
       roll_slot[k] = take(n);
       for (int ri = 0; ri < 4; ++ri) roll_pref[k][ri] = take(n + 1);
     }
@@ -82,7 +83,7 @@ struct Area {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   BatchTabs T{};
-  Tab roll[3][4] = {};
+  Tab roll[kRollKinds][4] = {};
 };
 
 }  // namespace
@@ -91,7 +92,7 @@ struct ce_mppi_batch {
   int n = 0, device = 0, cus = 256;
   std::vector<ce_mppi_planner*> pl;
   std::vector<int> roll_kind, p_kind;
-  bool has_roll[3] = {false, false, false};
+  bool has_roll[kRollKinds] = {};
   void* d_st_mem = nullptr;
   SlotStatic* d_st = nullptr;
   Layout lay;
@@ -103,7 +104,7 @@ struct ce_mppi_batch {
   bool upload_pending = false;
   hipEvent_t up_done = nullptr;
   // totals of the full member set (upper bounds of any subset): grid sizes
-  int roll_total[3][4] = {};
+  int roll_total[kRollKinds][4] = {};
   int compact_total[kPlanKinds] = {}, update_total = 0, n_p[kPlanKinds] = {}, lab_total[kPlanKinds] = {};
   ce_mppi_batch_tuning tune{8, 8, 4, 4};
 };
@@ -124,8 +125,13 @@ struct DeviceGuard {
 int r_index(int r) { return r == 1 ? 0 : r == 2 ? 1 : r == 4 ? 2 : 3; }
 
 int rollout_kind(const ce_mppi_planner* P) {
-  if (P->c.dyn != 0) return 2;
-  return P->c.seg == 32 ? 0 : 1;
+  return P->c.dyn != 0 ? 1 : 0;
+}
+
+// work items of a member's rollouts (arm: r rounds per item)
+int roll_items(const ce_mppi_planner* P, int r) {
+  const int rpb = P->c.rpb * (P->c.dyn != 0 ? r : 1);
+  return (P->c.K + rpb - 1) / rpb;
 }
 
 void drop_graph(Area& a) {
@@ -142,7 +148,7 @@ void drop_graphs(ce_mppi_batch* B) {
 // Host tables of one member list (slot indices) in the area layout.
 void fill_tables(const ce_mppi_batch* B, const int* members, int count, int* h) {
   const Layout& L = B->lay;
-  std::vector<int> lr[3], lp[kPlanKinds];
+  std::vector<int> lr[kRollKinds], lp[kPlanKinds];
   for (int q = 0; q < count; ++q) {
     const int s = members[q];
     lr[B->roll_kind[s]].push_back(s);
@@ -155,14 +161,13 @@ void fill_tables(const ce_mppi_batch* B, const int* members, int count, int* h) 
   auto copy = [&](const std::vector<int>& list, size_t off) {
     std::copy(list.begin(), list.end(), h + off);
   };
-  for (int k = 0; k < 3; ++k) {
+  for (int k = 0; k < kRollKinds; ++k) {
     h[L.cnt_roll[k]] = (int)lr[k].size();
     copy(lr[k], L.roll_slot[k]);
     for (int ri = 0; ri < 4; ++ri) {
       const int r = 1 << ri;
       prefix(lr[k], L.roll_pref[k][ri], [r](const ce_mppi_planner* P) {
-        const int rpb = kRollWaves * (kWave / P->c.seg) * r;
-        return (P->c.K + rpb - 1) / rpb;
+        return roll_items(P, r);
       });
     }
   }
@@ -184,7 +189,7 @@ void fill_tables(const ce_mppi_batch* B, const int* members, int count, int* h) 
 void area_tabs(const ce_mppi_batch* B, Area& a) {
   const Layout& L = B->lay;
   int* d = a.d_tab;
-  for (int k = 0; k < 3; ++k)
+  for (int k = 0; k < kRollKinds; ++k)
     for (int ri = 0; ri < 4; ++ri)
       a.roll[k][ri] = Tab{d + L.roll_slot[k], d + L.roll_pref[k][ri], d + L.cnt_roll[k]};
   BatchTabs& T = a.T;
@@ -224,10 +229,14 @@ hipError_t build_graph(ce_mppi_batch* B, Area& a) {
   if (e != hipSuccess) return e;
   Launcher L(nullptr, a.graph);
   const int ri = r_index(B->tune.roll_per_wave);
-  for (int k = 0; k < 3; ++k) {
+  for (int k = 0; k < kRollKinds; ++k) {
     if (!B->has_roll[k]) continue;
-    const int grid = std::max(1, std::min(B->roll_total[k][ri], B->tune.roll_blocks_per_cu * B->cus));
-    launch_batch_rollout(L, k, B->tune.roll_per_wave, B->d_st, a.d_io, a.roll[k][ri], grid);
+    const int items = B->roll_total[k][ri];
+    const bool loop = &a != &B->area[0];
+    // (blocks per CU are counted in blocks of kRollThreads)
+    const int cap = B->tune.roll_blocks_per_cu * B->cus * (k == 0 ? kRollThreads / kUniThreads : 1);
+    const int grid = std::max(1, k == 0 && !loop ? items : std::min(items, cap));
+    launch_batch_rollout(L, k, B->tune.roll_per_wave, loop, B->d_st, a.d_io, a.roll[k][ri], grid);
   }
   launch_batch_post(L, B->d_st, a.d_io, a.T);
   if (L.err != hipSuccess) {
@@ -306,8 +315,7 @@ ce_status ce_mppi_batch_create(ce_mppi_planner* const* planners, int32_t n, ce_m
     B->has_roll[B->roll_kind[i]] = true;
     B->n_p[B->p_kind[i]] += 1;
     for (int ri = 0; ri < 4; ++ri) {
-      const int rpb = kRollWaves * (kWave / P->c.seg) * (1 << ri);
-      B->roll_total[B->roll_kind[i]][ri] += (P->c.K + rpb - 1) / rpb;
+      B->roll_total[B->roll_kind[i]][ri] += roll_items(P, 1 << ri);
     }
     B->compact_total[B->p_kind[i]] += (P->c.K + 255) / 256;
     B->update_total += P->c.nblk_upd;

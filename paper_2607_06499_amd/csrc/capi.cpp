@@ -175,12 +175,25 @@ void build_cfg(const ce_mppi_config* u, Cfg& c) {
   c.K = u->num_samples;
   c.NM = c.N * c.m;
   c.B = (c.NM + 3) / 4;
-  // lanes per rollout: the unicycle keeps x_0..x_N in lanes 0..N, the arm
-  // keeps u_j and x_{j+1} in lane j
-  c.seg = (c.dyn == CE_DYN_UNICYCLE ? c.N + 1 <= 32 : c.N <= 32) ? 32 : 64;
-  c.rpb = kRollWaves * (64 / c.seg);
+  // the arm keeps u_j and x_{j+1} in lane j
+  if (c.dyn == CE_DYN_UNICYCLE) {
+    // More lanes of fewer steps shorten the one wave that a small launch is
+    // bound by; fewer lanes of more steps take fewer instructions, which bound
+    // a large one.  Measured, us a launch with 8 / 16 / 32 lanes: N = 30
+    // K = 1,024 5.9 / 5.2 / -, K = 16,384 6.7 / 6.4 / -, K = 65,536 12.4 / 14.1
+    // / -; N = 50 K = 1,024 6.3 / 5.4 / 4.8, K = 8,192 6.9 / 6.0 / 5.8,
+    // K = 65,536 20.2 / 17.0 / 20.7.  The line for N > 32 lies at 4,096 because
+    // from there on a batch, which takes its members' layouts, loses more to
+    // the extra instructions than a single launch gains.
+    const int lanes = c.N <= 32 ? (c.K <= 16384 ? 16 : 8) : (c.K <= 4096 ? 32 : 16);
+    const int steps = 2 * ((c.N + 2 * lanes - 1) / (2 * lanes));
+    c.seg = uni_code(lanes, steps);
+    c.rpb = kUniThreads / lanes;
+  } else {
+    c.seg = c.N <= 32 ? 32 : 64;
+    c.rpb = kRollWaves * (64 / c.seg);
+  }
   c.nblk_roll = (c.K + c.rpb - 1) / c.rpb;
-  c.roll_r = 1;
   // every rollout state lies within max|v| N dt of the start position (the
   // clamped speed bounds each step's displacement)
   {
@@ -342,18 +355,6 @@ ce_status ce_mppi_create(const ce_mppi_config* cfg, ce_mppi_planner** out) {
   if (!P) return fail(CE_ENOMEM, "host allocation failed");
   P->cfg = *cfg;
   build_cfg(cfg, P->c);
-  {
-    // Two rollout rounds per wave halve the per-block prologue when the
-    // unicycle launch still has at least two blocks per compute unit; a
-    // smaller grid (or the arm, whose waves are long) runs one round.
-    int cus = 256;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device) != hipSuccess ||
-        cus < 1)
-      cus = 256;
-    Cfg& cm = P->c;
-    const int blocks2 = (cm.K + 2 * cm.rpb - 1) / (2 * cm.rpb);
-    cm.roll_r = (cm.dyn == CE_DYN_UNICYCLE && blocks2 >= 2 * cus) ? 2 : 1;
-  }
   const Cfg& c = P->c;
   const size_t K = (size_t)c.K, NM = (size_t)c.NM, p = (size_t)c.p;
   const size_t zs = c.p == 2 ? 2 : 4;
@@ -366,8 +367,7 @@ ce_status ce_mppi_create(const ce_mppi_config* cfg, ce_mppi_planner** out) {
   const size_t o_pT = cv.take<float>(K * p), o_pF = cv.take<float>(K * p), o_g = cv.take<float>(K * p);
   // (plus the chunks of the last row that the update kernel reads past its end)
   const size_t o_eps = cv.take<float>(K * NM + (size_t)kFinChunks * kWave);
-  // room for the groups of the widest block (kMaxR rounds of 2 rollouts per wave)
-  const size_t o_part = cv.take<float>((size_t)(c.npart + kMaxRpb * kMaxR / kGroup) * kPart);
+  const size_t o_part = cv.take<float>((size_t)c.npart * kPart);
   const size_t o_vidx = cv.take<int>(K), o_z = cv.take<float>(K * zs), o_gv = cv.take<float>(K * zs);
   const size_t o_Sv = cv.take<float>(K);
   const size_t o_zs = cv.take<float>(K * zs), o_sid = cv.take<int>(K);

@@ -1886,15 +1886,6 @@ __device__ __forceinline__ void win_label_stats(const Bufs& b, int a0, int V, bo
   }
 }
 
-// The thread index as a value the compiler cannot see through: addresses that
-// follow from it are not carried across the items of a persistent loop (they
-// cost the batched kernel 60 registers and put others in scratch memory).
-__device__ __forceinline__ int item_thread() {
-  int t = (int)threadIdx.x;
-  asm volatile("" : "+v"(t));
-  return t;
-}
-
 // Components and labels by one 1024-thread block from exact counts.  Runs of
 // core buckets, the links across their gaps and the off-ring core points give
 // the components; the lowest-index core neighbour of each non-core point (one

@@ -15,12 +15,20 @@ constexpr int kMaxSpheres = 16;
 constexpr int kMaxNM = kMaxHorizon * kMaxCtrl;
 constexpr int kWave = 64;
 
-// rollout kernel: 512 threads = 8 waves; a wave holds one rollout (64-lane
-// segment) or two (32-lane segments) when N + 1 <= 32.
+// arm rollout kernel: 512 threads = 8 waves; a wave holds one rollout (64-lane
+// segment) or two (32-lane segments) when N <= 32.
 constexpr int kRollThreads = 512;
 constexpr int kRollWaves = kRollThreads / 64;
-constexpr int kMaxRpb = 2 * kRollWaves;  // rollouts per block at one round per wave
-constexpr int kMaxR = 8;                 // rollout rounds per wave (batched form)
+// unicycle rollout kernel: layouts (lanes per rollout, steps per lane), by the
+// code held in Cfg::seg
+constexpr int kUniThreads = 256;
+constexpr int uni_code(int lanes, int steps) { return lanes * 16 + steps; }
+#define CEMPPI_UNI_LAYOUTS(X) \
+  X(uni_code(8, 2), 8, 2)     \
+  X(uni_code(8, 4), 8, 4)     \
+  X(uni_code(16, 2), 16, 2)   \
+  X(uni_code(16, 4), 16, 4)   \
+  X(uni_code(32, 2), 32, 2)
 constexpr int kGroup = 8;                // rollouts per partial record
 // per-block partial record of the rollout reduction (floats)
 constexpr int kPart = 12;
@@ -111,8 +119,9 @@ struct Ctrl {
 // Scalar configuration (kernel argument).
 struct Cfg {
   int dyn, N, K, m, n, p, NM, B;
-  int seg, rpb, nblk_roll;
-  int roll_r;       // rollout rounds per wave of the single-planner launch (1 or 2)
+  int seg;          // arm: lanes per rollout (32 or 64); unicycle: uni_code of its layout
+  int rpb;          // rollouts per block and round
+  int nblk_roll;    // blocks of the single-planner launch
   int npart;        // ceil(K / kGroup) partial records
   float dt, lambda, norm_eps;
   float L[36];
@@ -162,7 +171,7 @@ struct Bufs {
   float* pF;       // [K][p]
   float* g;        // [K][p]
   float* eps;      // [K][N][m]
-  float* part;     // [npart (+ slack)][kPart] rollout-group partial records
+  float* part;     // [npart][kPart] rollout-group partial records
   // compacted feasible set
   int* vidx;       // [K]
   float* z;        // [K][zs] zs = 2 (p = 2) or 4 (p = 3)
@@ -259,6 +268,28 @@ __device__ __forceinline__ void for_each_item(const Tab& t, int* s_pref, F&& f) 
   }
 }
 
+// The planner's slot of item `it` and its item there, for a launch of one block
+// per item (-1: none); every lane of a wave takes a share of the prefix table.
+__device__ __forceinline__ int item_of(const Tab& t, int it, int* local) {
+  const int n = __builtin_amdgcn_readfirstlane(*t.n), lane = (int)(threadIdx.x & (kWave - 1));
+  int q = 0;  // planners whose items end at or before it
+  for (int i = 0; i < n; i += kWave) q += __popcll(__ballot(i + lane < n && t.pref[min(i + lane, n - 1) + 1] <= it));
+  q = __builtin_amdgcn_readfirstlane(q);
+  if (q >= n) return -1;
+  *local = it - __builtin_amdgcn_readfirstlane(t.pref[q]);
+  return __builtin_amdgcn_readfirstlane(t.slot[q]);
+}
+
+// The thread index as a value the compiler cannot see through: addresses that
+// follow from it are not carried across the items of a persistent loop (they
+// cost the labelling kernel of a batch 60 registers and put others in scratch
+// memory, which adds about 25 us to every dispatch).
+__device__ __forceinline__ int item_thread() {
+  int t = (int)threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // Tables of the batched post-rollout phases.  Index kd is the group of
 // planners: p = 2 on the sorted distance passes (0), p = 3 (1), p = 2 on the
 // angular windows (2).  Static tables for compaction and for the spatial sort
@@ -300,7 +331,8 @@ __device__ __forceinline__ void philox(uint32_t c0, uint32_t c1, uint32_t c2, ui
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
     const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
     const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-    const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+    // (three-way xor: v_bitop3_b32)
+    const uint32_t n0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96), n2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
     c0 = n0;
     c1 = lo1;
     c2 = n2;
@@ -312,9 +344,10 @@ __device__ __forceinline__ void philox(uint32_t c0, uint32_t c1, uint32_t c2, ui
   out[3] = c3;
 }
 
-// open-interval uniform (2*(w>>9)+1) * 2^-24, exact in FP32
+// open-interval uniform (2*(w>>9)+1) * 2^-24, exact in FP32: the 24 significant
+// bits stay where they are in the word
 __device__ __forceinline__ float u01(uint32_t w) {
-  return (float)(((w >> 9) << 1) | 1u) * 5.9604644775390625e-8f;
+  return (float)((w & 0xfffffe00u) | 0x100u) * 2.3283064365386963e-10f;
 }
 
 // Box-Muller pair on the hardware transcendentals: r = sqrt(-2 ln u_a) with

@@ -3,13 +3,13 @@
 // leaves a partial record (counts and sums for pruning and the reference
 // point of Eq. (9)-(11)); the next kernel reduces those records.
 //
-// Layout: one rollout per 64-lane segment of a wavefront (two per wave when
-// the N+1 states fit in 32 lanes).  Lane j of a segment owns control u_j and
-// state x_j: the noise of a step is drawn in its lane, the linear parts of the
-// dynamics are prefix sums across lanes (the heading of the unicycle, the joint
-// angles of the arm), and every lane evaluates its own stage cost, collision
-// test and (arm) forward kinematics.  The serial N-step recursion of Eq. (4)
-// thus becomes log2(N) shuffle steps and all work of a step runs in parallel.
+// Layout: a rollout's steps are spread over lanes of a wavefront (the unicycle:
+// 8 lanes of a few steps each; the arm: one step per lane, 32 or 64 lanes).  A
+// lane owns the controls u_j of its steps and the states x_{j+1} they lead to:
+// it draws their noise, the linear parts of the dynamics are prefix sums across
+// lanes (the heading and position of the unicycle, the joint angles of the
+// arm), and it evaluates their stage cost, contacts and (arm) forward
+// kinematics.
 #include "device.hpp"
 #include "launch.hpp"
 
@@ -126,6 +126,35 @@ __device__ __forceinline__ float limit_penalty(const Cfg& c, const float* q) {
   return c.wlim * s;
 }
 
+// An obstacle row and (constant-velocity obstacles) its oldest observation,
+// requested ahead of the prologue by the threads 0 .. n_obs - 1.
+struct ObsRow {
+  float o[4], old[3];
+  int hp;  // H' of Eq. (17) over the ring as it will be after this replan's push
+};
+template <int DYN, int CVM>
+__device__ __forceinline__ ObsRow load_obs(const Cfg& c, const Bufs& b, const float* __restrict__ obs, int n_obs,
+                                           int tid) {
+  constexpr int P = DYN == 0 ? 2 : 3;
+  ObsRow r = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, 0};
+  if (tid < n_obs) {
+#pragma unroll
+    for (int i = 0; i <= P; ++i) r.o[i] = obs[tid * (P + 1) + i];
+    if (CVM == 2 ? c.cv != 0 : CVM == 1) {
+      const Ctrl* ct = b.ctrl;
+      const int cnt = (ct->hs_nobs == n_obs ? ct->hs_count : 0) + 1;
+      r.hp = cnt < c.H ? cnt : c.H;
+      if (r.hp >= 2) {
+        const int h1 = (ct->hs_head - (r.hp - 2) + 2 * c.H) % c.H;
+        const float* old = b.hist + ((size_t)h1 * c.max_obs + tid) * P;
+#pragma unroll
+        for (int i = 0; i < P; ++i) r.old[i] = old[i];
+      }
+    }
+  }
+  return r;
+}
+
 // Prologue run by every block: stages the obstacles, checks the inputs and
 // computes o* (smallest surface clearance, ties to the lowest index) and
 // p(x_t).  Returns through LDS: s_bad, s_closest, s_p0.
@@ -133,37 +162,30 @@ __device__ __forceinline__ float limit_penalty(const Cfg& c, const float* q) {
 // Arm (DYN 1): *s_c0 receives the state part of the stage cost of x_t
 // (with the pose cost, including its contact indicator).
 template <int DYN, int CVM = 2>
-__device__ void prologue(const Cfg& c, const Bufs& b, const float* __restrict__ x_t,
-                         const float* __restrict__ obs, int n_obs, ObsLds& L, int& s_bad,
-                         int& s_closest, float* s_p0, float* s_c0 = nullptr) {
+__device__ __forceinline__ void prologue(const Cfg& c, const float* __restrict__ x_t, const ObsRow& row, int n_obs,
+                                         ObsLds& L, int& s_bad, int& s_closest, float* s_p0,
+                                         float* s_c0 = nullptr) {
   const int tid = threadIdx.x;
-  const int P = DYN == 0 ? 2 : 3;
+  constexpr int P = DYN == 0 ? 2 : 3;
   if (tid == 0) s_bad = 0;
   __syncthreads();
   if (tid < n_obs) {
-    const float* o = obs + tid * (P + 1);
+    const float* o = row.o;
     float ok = 1.f;
+#pragma unroll
     for (int i = 0; i <= P; ++i) ok = isfinite(o[i]) ? ok : 0.f;
     if (ok == 0.f) atomicOr(&s_bad, 1);
     const float R = (DYN == 0 ? c.robot_r : c.rs) + o[P];
     L.o[tid] = make_float4(o[0], o[1], DYN == 0 ? 0.f : o[2], R * R);
     L.r[tid] = o[P];
-    // constant-velocity obstacles: Eq. (17) for every obstacle over the ring
-    // as it will be after this replan's push (the current observation is the
-    // newest entry), telescoped to (o_t - o_{t-H'+1}) / ((H' - 1) dt)
+    // constant-velocity obstacles: Eq. (17) for every obstacle, telescoped to
+    // (o_t - o_{t-H'+1}) / ((H' - 1) dt)
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (CVM == 2 ? c.cv != 0 : CVM == 1) {
-      const Ctrl* ct = b.ctrl;
-      const int cnt = (ct->hs_nobs == n_obs ? ct->hs_count : 0) + 1;
-      const int Hp = cnt < c.H ? cnt : c.H;
-      if (Hp >= 2) {
-        const int h1 = (ct->hs_head - (Hp - 2) + 2 * c.H) % c.H;
-        const float* old = b.hist + ((size_t)h1 * c.max_obs + tid) * P;
-        const float den = (float)(Hp - 1) * c.dt;
-        v.x = (o[0] - old[0]) / den;
-        v.y = (o[1] - old[1]) / den;
-        if (DYN != 0) v.z = (o[2] - old[2]) / den;
-      }
+    if ((CVM == 2 ? c.cv != 0 : CVM == 1) && row.hp >= 2) {
+      const float den = (float)(row.hp - 1) * c.dt;
+      v.x = (o[0] - row.old[0]) / den;
+      v.y = (o[1] - row.old[1]) / den;
+      if (DYN != 0) v.z = (o[2] - row.old[2]) / den;
     }
     L.v[tid] = v;
   }
@@ -251,6 +273,7 @@ __device__ void prologue(const Cfg& c, const Bufs& b, const float* __restrict__ 
 
 // Block 0: push the observation into the history ring and publish the
 // per-replan facts of the prologue.
+template <int NT>
 __device__ void publish(const Cfg& c, const Bufs& b, const float* __restrict__ obs, int n_obs,
                         int bad, int closest, const float* p0, uint32_t step) {
   Ctrl* ct = b.ctrl;
@@ -262,7 +285,7 @@ __device__ void publish(const Cfg& c, const Bufs& b, const float* __restrict__ o
   __syncthreads();
   const int nh = s_nh;
   if (!bad) {
-    for (int t = threadIdx.x; t < n_obs * c.p; t += kRollThreads) {
+    for (int t = threadIdx.x; t < n_obs * c.p; t += NT) {
       const int i = t / c.p, d = t % c.p;
       b.hist[((size_t)nh * c.max_obs + i) * c.p + d] = obs[i * (c.p + 1) + d];
     }
@@ -302,245 +325,331 @@ __device__ __forceinline__ void rollout_contrib(float* rec, bool active, int col
   r4[2] = make_float4(hit ? s0 : 0.f, hit ? s1 : 0.f, hit ? s2 : 0.f, 0.f);
 }
 
-// Partial records of groups of kGroup consecutive rollouts, each summed in
-// rollout order: the grouping (and so every rounding) is the same however
-// the rollouts were spread over waves, blocks or loop rounds.  recs holds the
-// rpb records of the block's rollouts bx*rpb .. bx*rpb+rpb-1.
-__device__ __forceinline__ void write_group_partials(const Bufs& b, float (*recs)[kPart], int rpb, int bx) {
+// Field f of the partial record of kGroup consecutive rollouts, summed in
+// rollout order: the grouping (and so every rounding) is the same however the
+// rollouts were spread over waves, blocks or rounds.
+__device__ __forceinline__ float group_sum(const float (*recs)[kPart], int f) {
+  const bool mn = f == P_SMIN_ALL || f == P_SMIN_FEAS;
+  float acc = mn ? INFINITY : 0.f;
+#pragma unroll
+  for (int r = 0; r < kGroup; ++r) {
+    const float v = recs[r][f];
+    acc = mn ? fminf(acc, v) : acc + v;
+  }
+  return acc;
+}
+
+// The partial records of the rpb records of a block's rollouts bx*rpb ..
+template <int NT>
+__device__ __forceinline__ void write_group_partials(const Cfg& c, const Bufs& b, const float (*recs)[kPart],
+                                                     int rpb, int bx) {
   __syncthreads();
   const int ng = rpb / kGroup;
-  for (int t = threadIdx.x; t < ng * kPart; t += kRollThreads) {
+  for (int t = threadIdx.x; t < ng * kPart; t += NT) {
     const int g = t / kPart, f = t - g * kPart;
-    const bool mn = f == P_SMIN_ALL || f == P_SMIN_FEAS;
-    float acc = mn ? INFINITY : 0.f;
-    for (int r = 0; r < kGroup; ++r) {
-      const float v = recs[g * kGroup + r][f];
-      acc = mn ? fminf(acc, v) : acc + v;
-    }
-    b.part[((size_t)bx * ng + g) * kPart + f] = acc;
+    if (bx * ng + g < c.npart) b.part[((size_t)bx * ng + g) * kPart + f] = group_sum(recs + g * kGroup, f);
   }
 }
 
 // Unicycle perturbation (Eq. (3)) of one control step: e = L g, the clamp to
-// the bounds, and the applied perturbation (clamped control - nominal); all
-// zero when `on` is false.
-__device__ __forceinline__ void perturb_clamp(const Cfg& c, float n0, float n1, float g0, float g1, bool on,
-                                              float& uv, float& uw, float& a0, float& a1) {
+// the bounds (one v_med3_f32: the bounds are ordered) and the applied
+// perturbation (clamped control - nominal).
+__device__ __forceinline__ void perturb_clamp(const Cfg& c, float2 n, float g0, float g1, float& uv, float& uw,
+                                              float& a0, float& a1) {
   const float e0 = c.L[0] * g0;
   const float e1 = c.L[2] * g0 + c.L[3] * g1;
-  const float t0 = n0 + e0, t1 = n1 + e1;
-  const float v = fminf(fmaxf(t0, c.umin[0]), c.umax[0]);
-  const float w = fminf(fmaxf(t1, c.umin[1]), c.umax[1]);
-  uv = on ? v : 0.f;
-  uw = on ? w : 0.f;
-  a0 = on ? (v == t0 ? e0 : v - n0) : 0.f;
-  a1 = on ? (w == t1 ? e1 : w - n1) : 0.f;
+  const float t0 = n.x + e0, t1 = n.y + e1;
+  uv = __builtin_amdgcn_fmed3f(t0, c.umin[0], c.umax[0]);
+  uw = __builtin_amdgcn_fmed3f(t1, c.umin[1], c.umax[1]);
+  a0 = uv == t0 ? e0 : uv - n.x;
+  a1 = uw == t1 ? e1 : uw - n.y;
 }
 
 // ---------------------------------------------------------------------------
 // Unicycle rollouts (Sec. III-A): state (x, y, theta), control (v, omega).
-// R rounds per wave: each wave runs R rollouts per block item, the nominal
-// sequence staying in registers between rounds.  CVM as for the prologue.
-template <int SEG, int R = 1, int CVM = 2>
-__device__ __forceinline__ void rollout_unicycle_body(const Cfg& c, const Bufs& b, int bx, int by,
-                                                      int nbx, const float* __restrict__ x_t,
-                                                      const float* __restrict__ obs, int n_obs) {
-  __shared__ ObsLds L;
-  __shared__ int s_bad, s_closest;
-  __shared__ float s_p0[3];
-  __shared__ __align__(16) float s_rec[kRollWaves * (kWave / SEG) * R][kPart];
-  // With one or two rounds the prologue (obstacles, finiteness, o*) runs
-  // after the first round's noise, dynamics and cost, which do not need it,
-  // so that its loads and barriers overlap that work; nothing is stored
-  // before it has run.  With more rounds it runs first (the late form costs
-  // registers, and so occupancy, in the persistent batched launch).
-  constexpr bool LATE = R <= 2;
-  const uint32_t step = b.ctrl->step_lo;
-  int bad = 0, closest = -1;
-  if constexpr (!LATE) {
-    prologue<0, CVM>(c, b, x_t, obs, n_obs, L, s_bad, s_closest, s_p0);
-    bad = s_bad;
-    closest = s_closest;
-    if (bx == 0) publish(c, b, obs, n_obs, bad, closest, s_p0, step);
-  }
-  const bool cv = CVM == 2 ? c.cv != 0 : CVM == 1;
+//
+// A rollout takes G lanes of a wavefront (8, 16 or 32), a lane C consecutive
+// steps: lane g holds the controls u_j for j = g C .. g C + C - 1, and N <= G C.
+// The recursion of Eq. (4)/(21) is a serial sum over the lane's steps and a
+// scan over the G lanes, and every lane evaluates the noise, cost and contacts
+// of its own steps.  C is even, so a lane uses both halves of each Philox block
+// it draws.  Steps past N follow every state that counts, so they need no
+// masks in the sums.  Bound by VALU issue in large launches and by the latency
+// of one wave in small ones (the layout is chosen for each planner).  Measured
+// against one step per lane, where a scan took six adds per lane and sum, a
+// contact test its LDS read per state and N = 50 left 14 of 64 lanes idle:
+// N = 50, K = 8,192 7.5 -> 6.0 us a launch back to back, K = 65,536 30.1 ->
+// 17.0 us; the 64 planners of a batch 119 -> 61 us.
+template <int G>
+constexpr int uni_per_block() {
+  return kUniThreads / G;
+}
 
-  constexpr int SPW = kWave / SEG;
-  constexpr int RPB = kRollWaves * SPW * R;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int j = lane & (SEG - 1), sgi = lane / SEG;
+// moves within a row of 16 lanes
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+// sum over the lower lanes of the rollout's G (g: lane within them)
+template <int G>
+__device__ __forceinline__ float uni_excl_scan(float v, int g) {
+  if constexpr (G == 32) return seg_excl_scan<32>(v, g);
+  // (rows of 16: with G = 8 they hold two rollouts, and what comes from the
+  // other is left out)
+  const float t1 = dpp_f<0x111>(v);  // row_shr:1
+  v += G == 16 || g >= 1 ? t1 : 0.f;
+  const float t2 = dpp_f<0x112>(v);
+  v += G == 16 || g >= 2 ? t2 : 0.f;
+  const float t4 = dpp_f<0x114>(v);
+  v += G == 16 || g >= 4 ? t4 : 0.f;
+  if constexpr (G == 16) v += dpp_f<0x118>(v);
+  const float e = dpp_f<0x111>(v);
+  return G == 16 || g >= 1 ? e : 0.f;
+}
+// sum and minimum over the rollout's lanes (every lane gets the same value)
+template <int G>
+__device__ __forceinline__ float uni_sum(float v) {
+  v += dpp_f<0xB1>(v);   // quad_perm: neighbour
+  v += dpp_f<0x4E>(v);   // quad_perm: other pair
+  v += dpp_f<0x141>(v);  // row_half_mirror: other quad
+  if constexpr (G >= 16) v += dpp_f<0x140>(v);  // row_mirror: other half row
+  if constexpr (G >= 32) v += __shfl_xor(v, 16, kWave);
+  return v;
+}
+template <int G>
+__device__ __forceinline__ int uni_min(int v) {
+  v = min(v, dpp_i<0xB1>(v));
+  v = min(v, dpp_i<0x4E>(v));
+  v = min(v, dpp_i<0x141>(v));
+  if constexpr (G >= 16) v = min(v, dpp_i<0x140>(v));
+  if constexpr (G >= 32) v = min(v, __shfl_xor(v, 16, kWave));
+  return v;
+}
+
+struct UniLds {
+  ObsLds o;
+  int bad, closest;
+  float p0[3];
+  __align__(16) float rec[kUniThreads / 8][kPart];  // one per rollout
+};
+
+// The bx-th block of rollouts.  The prologue (obstacles, finiteness, o*) runs
+// after the noise, dynamics and cost, which do not need it, on rows requested
+// at the start; nothing is stored before it has run.  CVM as for the prologue.
+template <int G, int C, int CVM>
+__device__ __forceinline__ void rollout_unicycle_body(const Cfg& c, const Bufs& b, int bx, const float* __restrict__ x_t,
+                                                      const float* __restrict__ obs, int n_obs, UniLds& sh) {
+  constexpr int RPB = uni_per_block<G>(), RPW = kWave / G;
+  static_assert(C % 2 == 0 && RPB % kGroup == 0 && RPB <= kUniThreads / 8, "layout");
+  const uint32_t step = b.ctrl->step_lo;
   const int N = c.N;
   const float dt = c.dt;
   const float x0 = x_t[0], y0 = x_t[1], th0 = x_t[2];
-  const float n0 = j < N ? b.U[j * 2] : 0.f, n1 = j < N ? b.U[j * 2 + 1] : 0.f;
-  // Paired rounds (R even): one Philox evaluation per lane serves two
-  // rounds.  A rollout needs ceil(2N/4) counter blocks: at most 32 with
-  // 64-lane segments, at most 16 with 32-lane ones (N <= 31), so the 64
-  // lanes own, in groups of OWN, every block of the SPW rollouts of round
-  // rr and of round rr + 1.  Each lane then takes the words of its own block
-  // (j >> 1) from the owner lane, so every Gaussian is the one
-  // step_gaussians<2> would give.
-  constexpr bool PAIRED = R >= 2 && (R % 2) == 0;
-  constexpr int OWN = SEG == 64 ? 32 : 16;
-  // Rounds go RS at a time.  With paired Philox the two rounds that share an
-  // evaluation also share one instruction stream up to the cost, so their
-  // dependent chains (the DPP scans, the transcendentals) interleave; the
-  // arithmetic of each rollout is unchanged.
-  constexpr int RS = PAIRED ? 2 : 1;
-  for (int r0 = 0; r0 < R; r0 += RS) {
-  int kloc[RS], k[RS];
-  bool inr[RS];
-#pragma unroll
-  for (int s = 0; s < RS; ++s) {
-    kloc[s] = ((r0 + s) * kRollWaves + wave) * SPW + sgi;
-    // one rollout per wave with 64-lane segments: k is wave-uniform (scalar)
-    k[s] = SEG == 64 ? __builtin_amdgcn_readfirstlane(bx * RPB + kloc[s]) : bx * RPB + kloc[s];
-    inr[s] = k[s] < c.K;
-  }
-
+  const bool cv = CVM == 2 ? c.cv != 0 : CVM == 1;
+  const ObsRow row = load_obs<0, CVM>(c, b, obs, n_obs, (int)threadIdx.x);
+  const int tid = item_thread(), lane = tid & (kWave - 1), wave = tid / kWave;
+  const int g = lane & (G - 1), j0 = g * C;
+  const int kloc = wave * RPW + lane / G;
+  const int k = bx * RPB + kloc;
+  const int nv = N - j0;  // the lane's steps below N (if positive)
   // noise, perturbation and clamp (Eq. (3)); applied perturbation kept
-  float uv[RS], uw[RS], a0[RS], a1[RS];
-  if constexpr (PAIRED) {
-    uint32_t pw[4] = {0u, 0u, 0u, 0u};
-    {
-      const int q = lane / OWN, ob = lane % OWN;
-      const int orr = r0 + q / SPW, osg = q % SPW;
-      const int ok = bx * RPB + (orr * kRollWaves + wave) * SPW + osg;
-      if (ok < c.K && ob < c.B) philox((uint32_t)ob, (uint32_t)ok, step, c.stream_id, c.seed_lo, c.seed_hi, pw);
+  float a0[C], a1[C], px[C], py[C];
+  float S;
+  {
+    float uv[C], uw[C];
+#pragma unroll
+    for (int q = 0; q < C; q += 2) {
+      uint32_t w[4];
+      philox((uint32_t)((j0 + q) >> 1), (uint32_t)k, step, c.stream_id, c.seed_lo, c.seed_hi, w);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float2 u = reinterpret_cast<const float2*>(b.U)[min(j0 + q + h, N - 1)];
+        float ga, gb;
+        box_muller(w[2 * h], w[2 * h + 1], ga, gb);
+        perturb_clamp(c, u, ga, gb, uv[q + h], uw[q + h], a0[q + h], a1[q + h]);
+      }
     }
+    // forward simulation, Eq. (4)/(21): th[q] is the heading of x_{j0+q},
+    // px[q], py[q] the position of x_{j0+q+1}
+    float th[C], s = 0.f;
 #pragma unroll
-    for (int s = 0; s < RS; ++s) {
-      const int src = (s * SPW + sgi) * OWN + (j >> 1);
-      uint32_t qw[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) qw[i] = (uint32_t)__shfl((int)pw[i], src, kWave);
-      const bool odd = (j & 1) != 0;
-      float g0, g1;
-      box_muller(odd ? qw[2] : qw[0], odd ? qw[3] : qw[1], g0, g1);
-      perturb_clamp(c, n0, n1, g0, g1, inr[s] && j < N, uv[s], uw[s], a0[s], a1[s]);
+    for (int q = 0; q < C; ++q) {
+      th[q] = s;
+      s = __builtin_fmaf(uw[q], dt, s);
     }
-  } else {
-    uv[0] = uw[0] = a0[0] = a1[0] = 0.f;
-    if (inr[0] && j < N) {
-      float g[2];
-      step_gaussians<2>(c, step, k[0], j, g);
-      perturb_clamp(c, n0, n1, g[0], g[1], true, uv[0], uw[0], a0[0], a1[0]);
+    const float thb = uni_excl_scan<G>(s, g);
+    const float the = th0 + (thb + s);  // heading after the lane's steps
+    float sx = 0.f, sy = 0.f;
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+      th[q] = th0 + (thb + th[q]);
+      float sn, cs;
+      __sincosf(th[q], &sn, &cs);
+      const float d = uv[q] * dt;
+      sx = __builtin_fmaf(d, cs, sx);
+      sy = __builtin_fmaf(d, sn, sy);
+      px[q] = sx;
+      py[q] = sy;
+    }
+    const float bxs = uni_excl_scan<G>(sx, g), bys = uni_excl_scan<G>(sy, g);
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+      px[q] = x0 + (bxs + px[q]);
+      py[q] = y0 + (bys + py[q]);
+    }
+    // cost, Eq. (5): the stage terms of (x_j, u_j) of the lane's steps, and
+    // the terminal term on the lane whose last step is N - 1
+    float qx = 0.f, qy = 0.f, qt = 0.f, qv = 0.f, qw = 0.f;
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+      if (q < nv) {
+        const float ex = (q == 0 ? x0 + bxs : px[q > 0 ? q - 1 : 0]) - c.goal[0];
+        const float ey = (q == 0 ? y0 + bys : py[q > 0 ? q - 1 : 0]) - c.goal[1];
+        const float et = th[q] - c.goal[2];
+        qx = __builtin_fmaf(ex, ex, qx);
+        qy = __builtin_fmaf(ey, ey, qy);
+        qt = __builtin_fmaf(et, et, qt);
+        qv = __builtin_fmaf(uv[q], uv[q], qv);
+        qw = __builtin_fmaf(uw[q], uw[q], qw);
+      }
+    }
+    float l = c.Q[0] * qx + c.Q[1] * qy + c.Q[2] * qt + c.R[0] * qv + c.R[1] * qw;
+    if (nv >= 1 && nv <= C) {
+      float ex = px[0], ey = py[0], et = C > 1 ? th[1] : the;
+#pragma unroll
+      for (int q = 1; q < C; ++q) {
+        const bool at = nv == q + 1;
+        ex = at ? px[q] : ex;
+        ey = at ? py[q] : ey;
+        et = at ? (q + 1 < C ? th[q + 1 < C ? q + 1 : q] : the) : et;
+      }
+      l += c.Qf[0] * sq(ex - c.goal[0]) + c.Qf[1] * sq(ey - c.goal[1]) + c.Qf[2] * sq(et - c.goal[2]);
+    }
+    S = uni_sum<G>(l);
+  }
+  prologue<0, CVM>(c, x_t, row, n_obs, sh.o, sh.bad, sh.closest, sh.p0);
+  const int bad = sh.bad, closest = sh.closest;
+  if (bx == 0) publish<kUniThreads>(c, b, obs, n_obs, bad, closest, sh.p0, step);
+  const bool act = k < c.K && !bad;
+  if (act) {
+    // (rows start at 16-byte boundaries when N is even)
+    float2* ep = reinterpret_cast<float2*>(b.eps) + (size_t)k * N + j0;
+    if ((N & 1) == 0) {
+#pragma unroll
+      for (int q = 0; q < C; q += 2)
+        if (q < nv) reinterpret_cast<float4*>(ep)[q / 2] = make_float4(a0[q], a1[q], a0[q + 1], a1[q + 1]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < C; ++q)
+        if (q < nv) ep[q] = make_float2(a0[q], a1[q]);
     }
   }
-  // forward simulation, Eq. (4)/(21): heading and position are prefix sums
-  float th[RS], sn[RS], cs[RS], px[RS], py[RS], S[RS];
+  // contacts of the lane's states with the obstacles (constant-velocity
+  // obstacles: obstacle i at o_i + j dt v_i for state j)
+  const int n_live = sh.o.n_live;
+  bool touch[C];
 #pragma unroll
-  for (int s = 0; s < RS; ++s) th[s] = th0 + seg_excl_scan<SEG>(uw[s] * dt, j);
-#pragma unroll
-  for (int s = 0; s < RS; ++s) __sincosf(th[s], &sn[s], &cs[s]);
-#pragma unroll
-  for (int s = 0; s < RS; ++s) {
-    px[s] = x0 + seg_excl_scan<SEG>(uv[s] * cs[s] * dt, j);
-    py[s] = y0 + seg_excl_scan<SEG>(uv[s] * sn[s] * dt, j);
-  }
-  // cost, Eq. (5): stage terms in lanes 0..N-1, terminal term in lane N
-#pragma unroll
-  for (int s = 0; s < RS; ++s) {
-    const float lx = sq(px[s] - c.goal[0]), ly = sq(py[s] - c.goal[1]), lth = sq(th[s] - c.goal[2]);
-    const float ls = c.Q[0] * lx + c.Q[1] * ly + c.Q[2] * lth + c.R[0] * uv[s] * uv[s] + c.R[1] * uw[s] * uw[s];
-    const float lt = c.Qf[0] * lx + c.Qf[1] * ly + c.Qf[2] * lth;
-    const float l = !inr[s] ? 0.f : (j < N ? ls : (j == N ? lt : 0.f));
-    S[s] = seg_sum<SEG>(l);
-  }
-
-  if (LATE && r0 == 0) {
-    prologue<0, CVM>(c, b, x_t, obs, n_obs, L, s_bad, s_closest, s_p0);
-    bad = s_bad;
-    closest = s_closest;
-    if (bx == 0) publish(c, b, obs, n_obs, bad, closest, s_p0, step);
-  }
-#pragma unroll
-  for (int s = 0; s < RS; ++s) {
-  const bool act = inr[s] && !bad;
-  if (act && j < N) {
-    float2* ep = reinterpret_cast<float2*>(b.eps + ((size_t)k[s] * N + j) * 2);
-    *ep = make_float2(a0[s], a1[s]);
-  }
-
-  // collision of states 1..N against the obstacles: lowest index hit
-  // pass 1: does this state touch any obstacle?  pass 2 (only in waves with
-  // a contact): the lowest obstacle index touched
-  // (constant-velocity obstacles: obstacle i at o_i + j dt v_i for state j)
-  const bool chk = act && j >= 1 && j <= N;
-  const int n_live = L.n_live;
-  const float tj = (float)j * dt;
-  const float qx = px[s], qy = py[s];
-  bool any = false;
-  if (chk) {
+  for (int q = 0; q < C; ++q) touch[q] = false;
+  for (int i = 0; i < n_live; ++i) {
+    const float4 o = sh.o.live[i];
     if (cv) {
-      for (int i = 0; i < n_live; ++i) {
-        const float4 o = L.live[i], v = L.vlive[i];
-        any |= dist2_2(qx, qy, __builtin_fmaf(tj, v.x, o.x), __builtin_fmaf(tj, v.y, o.y)) <= o.w;
+      const float4 v = sh.o.vlive[i];
+#pragma unroll
+      for (int q = 0; q < C; ++q) {
+        const float tj = (float)(j0 + q + 1) * dt;
+        touch[q] |= dist2_2(px[q], py[q], __builtin_fmaf(tj, v.x, o.x), __builtin_fmaf(tj, v.y, o.y)) <= o.w;
       }
     } else {
-      for (int i = 0; i < n_live; ++i) {
-        const float4 o = L.live[i];
-        any |= dist2_2(qx, qy, o.x, o.y) <= o.w;
-      }
+#pragma unroll
+      for (int q = 0; q < C; ++q) touch[q] |= dist2_2(px[q], py[q], o.x, o.y) <= o.w;
     }
   }
-  int hit = kInt32Max;
-  if (__ballot(any) != 0ull && any) {
-    if (cv) {
+  // the first colliding state of the rollout, and (on its lane) the lowest
+  // obstacle it touches
+  int qf = C;
+#pragma unroll
+  for (int q = C - 1; q >= 0; --q) qf = touch[q] ? q : qf;
+  const bool hit = act && qf < C && qf < nv;
+  int col = 0, first = -1;
+  float pfx = 0.f, pfy = 0.f;
+  if (__ballot(hit) != 0ull) {
+    const int jf = uni_min<G>(hit ? j0 + qf : kInt32Max);
+    col = jf != kInt32Max ? 1 : 0;
+    float hx = px[0], hy = py[0];
+#pragma unroll
+    for (int q = 1; q < C; ++q) {
+      hx = qf == q ? px[q] : hx;
+      hy = qf == q ? py[q] : hy;
+    }
+    int f = -1;
+    if (hit && j0 + qf == jf) {
+      const float tj = (float)(jf + 1) * dt;
       for (int i = n_live - 1; i >= 0; --i) {
-        const float4 o = L.live[i], v = L.vlive[i];
-        hit = dist2_2(qx, qy, __builtin_fmaf(tj, v.x, o.x), __builtin_fmaf(tj, v.y, o.y)) <= o.w
-                  ? L.idx[i] : hit;
-      }
-    } else {
-      for (int i = n_live - 1; i >= 0; --i) {
-        const float4 o = L.live[i];
-        hit = dist2_2(qx, qy, o.x, o.y) <= o.w ? L.idx[i] : hit;
+        const float4 o = sh.o.live[i];
+        float ox = o.x, oy = o.y;
+        if (cv) {
+          const float4 v = sh.o.vlive[i];
+          ox = __builtin_fmaf(tj, v.x, o.x);
+          oy = __builtin_fmaf(tj, v.y, o.y);
+        }
+        f = dist2_2(hx, hy, ox, oy) <= o.w ? sh.o.idx[i] : f;
       }
     }
+    const int src = (lane & ~(G - 1)) + (col ? jf / C : 0);
+    f = __shfl(f, src, kWave);
+    hx = __shfl(hx, src, kWave);
+    hy = __shfl(hy, src, kWave);
+    if (col) {
+      first = f;
+      pfx = hx;
+      pfy = hy;
+    }
   }
-  // first colliding state of each segment (lowest lane with a hit)
-  const unsigned long long hm = __ballot(hit != kInt32Max);
-  const unsigned long long m0 = SEG == 64 ? hm : (hm & 0xffffffffull);
-  const unsigned long long m1 = SEG == 64 ? 0ull : (hm >> 32);
-  const int f0 = m0 ? __ffsll((long long)m0) - 1 : 0;
-  const int f1 = m1 ? __ffsll((long long)m1) - 1 : 0;
-  const int col = (sgi == 0 ? m0 : m1) != 0ull;
-  const int f = seg_pick_i<SEG>(hit, f0, f1);
-  const float pfx = seg_pick<SEG>(qx, f0, f1), pfy = seg_pick<SEG>(qy, f0, f1);
-  const int ln = N < SEG ? N : SEG - 1;
-  const float ptx = seg_bcast<SEG>(qx, ln), pty = seg_bcast<SEG>(qy, ln);
-
-  float src[2];
-  src[0] = c.ref_mode == 1 ? pfx : ptx;
-  src[1] = c.ref_mode == 1 ? pfy : pty;
-  if (j == 0) {
-    const int kk = k[s];
+  // p(x_N): lane (N - 1) / C, step (N - 1) mod C
+  float ptx = px[0], pty = py[0];
+  const int qn = (N - 1) % C;
+#pragma unroll
+  for (int q = 1; q < C; ++q) {
+    ptx = qn == q ? px[q] : ptx;
+    pty = qn == q ? py[q] : pty;
+  }
+  const int srcn = (lane & ~(G - 1)) + (N - 1) / C;
+  ptx = __shfl(ptx, srcn, kWave);
+  pty = __shfl(pty, srcn, kWave);
+  if (g == 0) {
     if (act) {
-      b.S[kk] = S[s];
-      b.col[kk] = col;
-      b.first[kk] = col ? f : -1;
-      b.pT[2 * kk] = ptx;
-      b.pT[2 * kk + 1] = pty;
-      b.pF[2 * kk] = col ? pfx : 0.f;
-      b.pF[2 * kk + 1] = col ? pfy : 0.f;
+      b.S[k] = S;
+      b.col[k] = col;
+      b.first[k] = first;
+      reinterpret_cast<float2*>(b.pT)[k] = make_float2(ptx, pty);
+      reinterpret_cast<float2*>(b.pF)[k] = make_float2(pfx, pfy);
       // unit terminal displacement, Eq. (15)
       const float ex = ptx - x0, ey = pty - y0;
       const float den = __builtin_amdgcn_sqrtf(__builtin_fmaf(ey, ey, ex * ex)) + c.norm_eps;
       const float inv = __builtin_amdgcn_rcpf(den);  // v_sqrt_f32 and one v_rcp_f32
-      b.g[2 * kk] = ex * inv;
-      b.g[2 * kk + 1] = ey * inv;
+      reinterpret_cast<float2*>(b.g)[k] = make_float2(ex * inv, ey * inv);
     }
-    rollout_contrib(s_rec[kloc[s]], act, col, col ? f : -1, closest, S[s], src, 2);
+    const bool fc = c.ref_mode == 1 && col;
+    const float src[2] = {fc ? pfx : ptx, fc ? pfy : pty};
+    rollout_contrib(sh.rec[kloc], act, col, first, closest, S, src, 2);
   }
+  // partial records of the block's groups of kGroup rollouts
+  __syncthreads();
+  constexpr int NG = RPB / kGroup;
+  if (tid < NG * kPart) {
+    const int gr = tid / kPart, f = tid - gr * kPart, at = bx * NG + gr;
+    if (at < c.npart) b.part[(size_t)at * kPart + f] = group_sum(sh.rec + gr * kGroup, f);
   }
-  }
-  write_group_partials(b, s_rec, RPB, bx);
 }
 
-template <int SEG, int CV, int R>
-__global__ __launch_bounds__(kRollThreads) void k_rollout_unicycle(Cfg c, Bufs b, const float* __restrict__ x_t, const float* __restrict__ obs, int n_obs) {
-  rollout_unicycle_body<SEG, R, CV>(c, b, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, x_t, obs, n_obs);
+template <int G, int C, int CV>
+__global__ __launch_bounds__(kUniThreads) void k_rollout_unicycle(Cfg c, Bufs b, const float* __restrict__ x_t, const float* __restrict__ obs, int n_obs) {
+  __shared__ UniLds sh;
+  rollout_unicycle_body<G, C, CV>(c, b, (int)blockIdx.x, x_t, obs, n_obs, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -561,10 +670,10 @@ __device__ __forceinline__ void rollout_arm_body(const Cfg& c, const Bufs& b, in
   __shared__ int s_bad, s_closest;
   __shared__ float s_p0[3], s_c0;
   __shared__ __align__(16) float s_rec[RPB][kPart];
-  prologue<1>(c, b, x_t, obs, n_obs, L, s_bad, s_closest, s_p0, &s_c0);
+  prologue<1>(c, x_t, load_obs<1, 2>(c, b, obs, n_obs, (int)threadIdx.x), n_obs, L, s_bad, s_closest, s_p0, &s_c0);
   const uint32_t step = b.ctrl->step_lo;
   const int bad = s_bad, closest = s_closest;
-  if (bx == 0) publish(c, b, obs, n_obs, bad, closest, s_p0, step);
+  if (bx == 0) publish<kRollThreads>(c, b, obs, n_obs, bad, closest, s_p0, step);
   const float c0 = s_c0;
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -708,7 +817,7 @@ __device__ __forceinline__ void rollout_arm_body(const Cfg& c, const Bufs& b, in
     rollout_contrib(s_rec[kloc], act, col, col ? f : -1, closest, S, src, 3);
   }
   }
-  write_group_partials(b, s_rec, RPB, bx);
+  write_group_partials<kRollThreads>(c, b, s_rec, RPB, bx);
 }
 
 template <int SEG>
@@ -719,14 +828,33 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_arm(Cfg c, Bufs b, con
 // ---------------------------------------------------------------------------
 // Batched rollouts: one persistent launch per rollout kind covers the rollout
 // blocks of every planner of that kind in the batch; R rounds per wave.
-template <int SEG, int R>
-__global__ __launch_bounds__(kRollThreads) void kb_rollout_unicycle(CSlotStatic st, CSlotIO io, Tab t) {
+__device__ __forceinline__ void rollout_unicycle_slot(CSlotStatic st, CSlotIO io, int slot, int local, UniLds& sh) {
+  const SlotStatic& S = *(const SlotStatic*)(st + slot);
+  const SlotIO& I = *(const SlotIO*)(io + slot);
+  // the layout is the member's own (a block-uniform branch)
+  switch (S.c.seg) {
+#define CEMPPI_UNI(seg, G, C) \
+  case seg: rollout_unicycle_body<G, C, 2>(S.c, S.b, local, I.x_t, I.obs, I.n_obs, sh); break;
+    CEMPPI_UNI_LAYOUTS(CEMPPI_UNI)
+#undef CEMPPI_UNI
+  }
+}
+
+// Unicycle items with a block each (the full member set, whose items the host
+// knows): 64 planners of a batch, 15,000 items, 68 us against 76-78 us for
+// persistent blocks, whose registers leave too few waves to cover an item's
+// latency.
+__global__ __launch_bounds__(kUniThreads) void kb_rollout_unicycle(CSlotStatic st, CSlotIO io, Tab t) {
+  __shared__ UniLds sh;
+  int local;
+  const int slot = item_of(t, (int)blockIdx.x, &local);
+  if (slot >= 0) rollout_unicycle_slot(st, io, slot, local, sh);
+}
+// and with persistent blocks (member subsets: the graph serves any of them)
+__global__ __launch_bounds__(kUniThreads) void kb_rollout_unicycle_loop(CSlotStatic st, CSlotIO io, Tab t) {
   __shared__ int s_pref[kMaxBatch + 1];
-  for_each_item<kRollThreads>(t, s_pref, [&](int slot, int local) {
-    const SlotStatic& S = *(const SlotStatic*)(st + slot);
-    const SlotIO& I = *(const SlotIO*)(io + slot);
-    rollout_unicycle_body<SEG, R>(S.c, S.b, local, 0, 0, I.x_t, I.obs, I.n_obs);
-  });
+  __shared__ UniLds sh;
+  for_each_item<kUniThreads>(t, s_pref, [&](int slot, int local) { rollout_unicycle_slot(st, io, slot, local, sh); });
 }
 
 template <int R>
@@ -745,23 +873,24 @@ __global__ __launch_bounds__(kRollThreads) void kb_rollout_arm(CSlotStatic st, C
 
 // ---------------------------------------------------------------------------
 // The same reduction on rollout records already in the planner buffers
-// (records supplied by the caller): grid = nblk_roll blocks of rpb rollouts.
+// (records supplied by the caller): one rollout per thread.
+constexpr int kRedThreads = 256;
 template <int DYN>
-__global__ __launch_bounds__(kRollThreads) void k_reduce_records(Cfg c, Bufs b,
-                                                                 const float* __restrict__ x_t,
-                                                                 const float* __restrict__ obs,
-                                                                 int n_obs) {
+__global__ __launch_bounds__(kRedThreads) void k_reduce_records(Cfg c, Bufs b,
+                                                                const float* __restrict__ x_t,
+                                                                const float* __restrict__ obs,
+                                                                int n_obs) {
   __shared__ ObsLds L;
   __shared__ int s_bad, s_closest;
   __shared__ float s_p0[3];
-  __shared__ __align__(16) float s_rec[kMaxRpb][kPart];
-  prologue<DYN>(c, b, x_t, obs, n_obs, L, s_bad, s_closest, s_p0);
+  __shared__ __align__(16) float s_rec[kRedThreads][kPart];
+  prologue<DYN>(c, x_t, load_obs<DYN, 2>(c, b, obs, n_obs, (int)threadIdx.x), n_obs, L, s_bad, s_closest, s_p0);
   const uint32_t step = b.ctrl->step_lo;
   const int bad = s_bad, closest = s_closest;
-  if (blockIdx.x == 0) publish(c, b, obs, n_obs, bad, closest, s_p0, step);
+  if (blockIdx.x == 0) publish<kRedThreads>(c, b, obs, n_obs, bad, closest, s_p0, step);
   const int P = DYN == 0 ? 2 : 3;
-  if (threadIdx.x < c.rpb) {
-    const int k = blockIdx.x * c.rpb + threadIdx.x;
+  {
+    const int k = blockIdx.x * kRedThreads + threadIdx.x;
     const bool act = k < c.K && !bad;
     int col = 0, f = -1;
     float S = 0.f, src[3] = {0.f, 0.f, 0.f};
@@ -781,7 +910,7 @@ __global__ __launch_bounds__(kRollThreads) void k_reduce_records(Cfg c, Bufs b,
     }
     rollout_contrib(s_rec[threadIdx.x], act, col, f, closest, S, src, P);
   }
-  write_group_partials(b, s_rec, c.rpb, (int)blockIdx.x);
+  write_group_partials<kRedThreads>(c, b, s_rec, kRedThreads, (int)blockIdx.x);
 }
 
 // Philox words and standard normals of every rollout (stage entry point):
@@ -811,52 +940,46 @@ __global__ void k_stage_noise(Cfg c, uint32_t step, uint32_t* __restrict__ words
 
 // ---------------------------------------------------------------------------
 // host-side launchers
-// kind 0: unicycle on 32-lane segments, 1: unicycle on 64 lanes, 2: arm;
-// r: rounds per wave (1, 2, 4 or 8)
-template <int R>
-static void launch_batch_rollout_r(Launcher& L, int kind, CSlotStatic st, CSlotIO io, Tab t, int grid) {
-  if (kind == 0) L(kb_rollout_unicycle<32, R>, dim3(grid), dim3(kRollThreads), st, io, t);
-  else if (kind == 1) L(kb_rollout_unicycle<64, R>, dim3(grid), dim3(kRollThreads), st, io, t);
-  else L(kb_rollout_arm<R>, dim3(grid), dim3(kRollThreads), st, io, t);
-}
-
-void launch_batch_rollout(Launcher& L, int kind, int r, const SlotStatic* st, const SlotIO* io, Tab t,
+// kind 0: unicycle (blocks loop over the items, or have one each), 1: arm (r
+// rounds per wave and work item: 1, 2, 4 or 8)
+void launch_batch_rollout(Launcher& L, int kind, int r, bool loop, const SlotStatic* st, const SlotIO* io, Tab t,
                           int grid) {
   if (grid <= 0) return;
   const CSlotStatic cst = (CSlotStatic)st;
   const CSlotIO cio = (CSlotIO)io;
+  if (kind == 0) {
+    L(loop ? kb_rollout_unicycle_loop : kb_rollout_unicycle, dim3(grid), dim3(kUniThreads), cst, cio, t);
+    return;
+  }
   switch (r) {
-    case 2: launch_batch_rollout_r<2>(L, kind, cst, cio, t, grid); break;
-    case 4: launch_batch_rollout_r<4>(L, kind, cst, cio, t, grid); break;
-    case 8: launch_batch_rollout_r<8>(L, kind, cst, cio, t, grid); break;
-    default: launch_batch_rollout_r<1>(L, kind, cst, cio, t, grid); break;
+    case 2: L(kb_rollout_arm<2>, dim3(grid), dim3(kRollThreads), cst, cio, t); break;
+    case 4: L(kb_rollout_arm<4>, dim3(grid), dim3(kRollThreads), cst, cio, t); break;
+    case 8: L(kb_rollout_arm<8>, dim3(grid), dim3(kRollThreads), cst, cio, t); break;
+    default: L(kb_rollout_arm<1>, dim3(grid), dim3(kRollThreads), cst, cio, t); break;
   }
 }
 
 void launch_rollout(Launcher& L, const Cfg& c, const Bufs& b, const float* x_t, const float* obs,
                     int n_obs) {
-  dim3 grid(c.nblk_roll), block(kRollThreads);
+  const dim3 grid(c.nblk_roll);
   if (c.dyn == 0) {
-    // R rounds per wave: the block count shrinks by R; the partial records
-    // (fixed groups of kGroup rollouts) do not depend on it
-    using KFn = void (*)(Cfg, Bufs, const float*, const float*, int);
-    KFn f;
-    if (c.seg == 32)
-      f = c.roll_r == 2 ? (c.cv ? k_rollout_unicycle<32, 1, 2> : k_rollout_unicycle<32, 0, 2>)
-                        : (c.cv ? k_rollout_unicycle<32, 1, 1> : k_rollout_unicycle<32, 0, 1>);
-    else
-      f = c.roll_r == 2 ? (c.cv ? k_rollout_unicycle<64, 1, 2> : k_rollout_unicycle<64, 0, 2>)
-                        : (c.cv ? k_rollout_unicycle<64, 1, 1> : k_rollout_unicycle<64, 0, 1>);
-    const int rr = c.roll_r == 2 ? 2 : 1;
-    L(f, dim3((c.K + c.rpb * rr - 1) / (c.rpb * rr)), block, c, b, x_t, obs, n_obs);
+    switch (c.seg) {
+#define CEMPPI_UNI(seg, G, C)                                                                                \
+  case seg:                                                                                                  \
+    L(c.cv ? k_rollout_unicycle<G, C, 1> : k_rollout_unicycle<G, C, 0>, grid, dim3(kUniThreads), c, b, x_t, obs, \
+      n_obs);                                                                                                \
+    break;
+      CEMPPI_UNI_LAYOUTS(CEMPPI_UNI)
+#undef CEMPPI_UNI
+    }
   } else {
-    L(c.seg == 32 ? k_rollout_arm<32> : k_rollout_arm<64>, grid, block, c, b, x_t, obs, n_obs);
+    L(c.seg == 32 ? k_rollout_arm<32> : k_rollout_arm<64>, grid, dim3(kRollThreads), c, b, x_t, obs, n_obs);
   }
 }
 
 void launch_reduce_records(Launcher& L, const Cfg& c, const Bufs& b, const float* x_t,
                            const float* obs, int n_obs) {
-  dim3 grid(c.nblk_roll), block(kRollThreads);
+  const dim3 grid((c.K + kRedThreads - 1) / kRedThreads), block(kRedThreads);
   if (c.dyn == 0)
     L(k_reduce_records<0>, grid, block, c, b, x_t, obs, n_obs);
   else
