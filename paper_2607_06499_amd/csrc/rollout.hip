@@ -16,10 +16,10 @@
 namespace cemppi {
 
 // ---------------------------------------------------------------------------
-// shared prologue: obstacles into LDS, finiteness, closest obstacle o*.
+// shared prologue: obstacles into LDS, finiteness, closest obstacle o*.  (The
+// arm's helpers come first: the prologue uses them.)
 struct ObsLds {
   float4 o[kMaxObs];     // (x, y, z, R^2) with R = robot/sphere radius + obstacle radius
-  float r[kMaxObs];      // obstacle radius
   float4 v[kMaxObs];     // obstacle velocity (constant-velocity obstacles; else 0)
   float4 live[kMaxObs];  // the obstacles a rollout can reach, in index order
   float4 vlive[kMaxObs]; // their velocities
@@ -126,172 +126,137 @@ __device__ __forceinline__ float limit_penalty(const Cfg& c, const float* q) {
   return c.wlim * s;
 }
 
-// An obstacle row and (constant-velocity obstacles) its oldest observation,
-// requested ahead of the prologue by the threads 0 .. n_obs - 1.
-struct ObsRow {
-  float o[4], old[3];
-  int hp;  // H' of Eq. (17) over the ring as it will be after this replan's push
-};
-template <int DYN, int CVM>
-__device__ __forceinline__ ObsRow load_obs(const Cfg& c, const Bufs& b, const float* __restrict__ obs, int n_obs,
-                                           int tid) {
+// Prologue of a block, the work of one wave (all 64 lanes): stages the
+// obstacles, checks the inputs and computes o* (smallest surface clearance,
+// ties to the lowest index) and p(x_t); what it leaves in LDS is valid after
+// the block's next barrier.  CVM: constant-velocity obstacles never (0), always
+// (1) or as c.cv says (2).  Arm (DYN 1): *s_c0 receives the state part of the
+// stage cost of x_t (with the pose cost, including its contact indicator).
+// pub (block 0): also pushes the observation into the history ring and
+// publishes the per-replan facts.
+template <int DYN, int CVM = 2>
+__device__ __forceinline__ void prologue(const Cfg& c, const Bufs& b, const float* __restrict__ x_t,
+                                         const float* __restrict__ obs, int n_obs, bool pub, uint32_t step,
+                                         ObsLds& L, int& s_bad, int& s_closest, float* s_p0,
+                                         float* s_c0 = nullptr) {
   constexpr int P = DYN == 0 ? 2 : 3;
-  ObsRow r = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, 0};
-  if (tid < n_obs) {
+  const int lane = (int)(threadIdx.x & (kWave - 1));
+  const bool mine = lane < n_obs;
+  float o[4] = {0.f, 0.f, 0.f, 0.f};
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  bool ok = true;
+  if (mine) {
 #pragma unroll
-    for (int i = 0; i <= P; ++i) r.o[i] = obs[tid * (P + 1) + i];
+    for (int i = 0; i <= P; ++i) o[i] = obs[lane * (P + 1) + i];
+    // constant-velocity obstacles: Eq. (17) for every obstacle over the ring
+    // as it will be after this replan's push (the current observation is the
+    // newest entry), telescoped to (o_t - o_{t-H'+1}) / ((H' - 1) dt)
     if (CVM == 2 ? c.cv != 0 : CVM == 1) {
       const Ctrl* ct = b.ctrl;
       const int cnt = (ct->hs_nobs == n_obs ? ct->hs_count : 0) + 1;
-      r.hp = cnt < c.H ? cnt : c.H;
-      if (r.hp >= 2) {
-        const int h1 = (ct->hs_head - (r.hp - 2) + 2 * c.H) % c.H;
-        const float* old = b.hist + ((size_t)h1 * c.max_obs + tid) * P;
-#pragma unroll
-        for (int i = 0; i < P; ++i) r.old[i] = old[i];
+      const int Hp = cnt < c.H ? cnt : c.H;
+      if (Hp >= 2) {
+        const int h1 = (ct->hs_head - (Hp - 2) + 2 * c.H) % c.H;
+        const float* old = b.hist + ((size_t)h1 * c.max_obs + lane) * P;
+        const float den = (float)(Hp - 1) * c.dt;
+        v.x = (o[0] - old[0]) / den;
+        v.y = (o[1] - old[1]) / den;
+        if (DYN != 0) v.z = (o[2] - old[2]) / den;
       }
+    }
+#pragma unroll
+    for (int i = 0; i <= P; ++i) ok = ok && isfinite(o[i]);
+  }
+  if (lane < c.n) ok = ok && isfinite(x_t[lane]);
+  const int bad = __ballot(!ok) != 0ull ? 1 : 0;
+  const float rad = o[P], R = (DYN == 0 ? c.robot_r : c.rs) + rad;
+  const float4 row = make_float4(o[0], o[1], DYN == 0 ? 0.f : o[2], R * R);
+  if (mine) {
+    L.o[lane] = row;
+    L.v[lane] = v;
+  }
+  float cl = INFINITY;
+  int idx = kInt32Max;
+  float p0[3];
+  if (DYN == 0) {
+    p0[0] = x_t[0];
+    p0[1] = x_t[1];
+    p0[2] = 0.f;
+    if (mine) {
+      cl = sqrtf(dist2_2(p0[0], p0[1], row.x, row.y)) - rad;
+      idx = lane;
+    }
+  } else {
+    float q[6], Pm[7][3], Re[9];
+    for (int i = 0; i < 6; ++i) q[i] = x_t[i];
+    arm_origins(c, q, Pm, Re);
+    for (int i = 0; i < 3; ++i) p0[i] = Pm[6][i];
+    bool touch = false;
+    for (int s = 0; s < c.ns; ++s) {
+      float sx, sy, sz;
+      sphere_centre(c, Pm, s, sx, sy, sz);
+      const float d2 = dist2_3(sx, sy, sz, row.x, row.y, row.z);
+      const float w = sqrtf(d2) - rad;
+      cl = mine && w < cl ? w : cl;
+      touch |= mine && d2 <= row.w;
+    }
+    if (mine) idx = lane;
+    const bool icol0 = __ballot(touch) != 0ull;
+    if (lane == 0 && s_c0) {
+      const float d2g = sq(p0[0] - c.goal[0]) + sq(p0[1] - c.goal[1]) + sq(p0[2] - c.goal[2]);
+      *s_c0 = c.pose ? c.Q[0] * sqrtf(d2g) + c.Q[1] * rot_angle(c, Re) + limit_penalty(c, q) +
+                           (icol0 ? c.Q[2] : 0.f)
+                     : c.Q[0] * d2g + limit_penalty(c, q);
     }
   }
-  return r;
-}
-
-// Prologue run by every block: stages the obstacles, checks the inputs and
-// computes o* (smallest surface clearance, ties to the lowest index) and
-// p(x_t).  Returns through LDS: s_bad, s_closest, s_p0.
-// CVM: constant-velocity obstacles never (0), always (1) or as c.cv says (2).
-// Arm (DYN 1): *s_c0 receives the state part of the stage cost of x_t
-// (with the pose cost, including its contact indicator).
-template <int DYN, int CVM = 2>
-__device__ __forceinline__ void prologue(const Cfg& c, const float* __restrict__ x_t, const ObsRow& row, int n_obs,
-                                         ObsLds& L, int& s_bad, int& s_closest, float* s_p0,
-                                         float* s_c0 = nullptr) {
-  const int tid = threadIdx.x;
-  constexpr int P = DYN == 0 ? 2 : 3;
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
-  if (tid < n_obs) {
-    const float* o = row.o;
-    float ok = 1.f;
 #pragma unroll
-    for (int i = 0; i <= P; ++i) ok = isfinite(o[i]) ? ok : 0.f;
-    if (ok == 0.f) atomicOr(&s_bad, 1);
-    const float R = (DYN == 0 ? c.robot_r : c.rs) + o[P];
-    L.o[tid] = make_float4(o[0], o[1], DYN == 0 ? 0.f : o[2], R * R);
-    L.r[tid] = o[P];
-    // constant-velocity obstacles: Eq. (17) for every obstacle, telescoped to
-    // (o_t - o_{t-H'+1}) / ((H' - 1) dt)
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if ((CVM == 2 ? c.cv != 0 : CVM == 1) && row.hp >= 2) {
-      const float den = (float)(row.hp - 1) * c.dt;
-      v.x = (o[0] - row.old[0]) / den;
-      v.y = (o[1] - row.old[1]) / den;
-      if (DYN != 0) v.z = (o[2] - row.old[2]) / den;
+  for (int d = 32; d > 0; d >>= 1) {
+    const float oc = __shfl_xor(cl, d, kWave);
+    const int oi = __shfl_xor(idx, d, kWave);
+    if (oc < cl || (oc == cl && oi < idx)) {
+      cl = oc;
+      idx = oi;
     }
-    L.v[tid] = v;
   }
-  if (tid < c.n && !isfinite(x_t[tid])) atomicOr(&s_bad, 1);
-  __syncthreads();
-  if (tid < kWave) {
-    float cl = INFINITY;
-    int idx = kInt32Max;
-    if (DYN == 0) {
-      const float x0 = x_t[0], y0 = x_t[1];
-      if (tid == 0) {
-        s_p0[0] = x0;
-        s_p0[1] = y0;
-        s_p0[2] = 0.f;
-      }
-      if (tid < n_obs) {
-        cl = sqrtf(dist2_2(x0, y0, L.o[tid].x, L.o[tid].y)) - L.r[tid];
-        idx = tid;
-      }
-    } else {
-      float q[6], Pm[7][3], Re[9];
-      for (int i = 0; i < 6; ++i) q[i] = x_t[i];
-      arm_origins(c, q, Pm, Re);
-      if (tid == 0) {
-        s_p0[0] = Pm[6][0];
-        s_p0[1] = Pm[6][1];
-        s_p0[2] = Pm[6][2];
-      }
-      bool touch = false;
-      if (tid < n_obs) {
-        for (int s = 0; s < c.ns; ++s) {
-          float sx, sy, sz;
-          sphere_centre(c, Pm, s, sx, sy, sz);
-          const float d2 = dist2_3(sx, sy, sz, L.o[tid].x, L.o[tid].y, L.o[tid].z);
-          const float v = sqrtf(d2) - L.r[tid];
-          cl = v < cl ? v : cl;
-          touch |= d2 <= L.o[tid].w;
-        }
-        idx = tid;
-      }
-      const bool icol0 = __ballot(touch) != 0ull;
-      if (tid == 0 && s_c0) {
-        const float d2g = sq(Pm[6][0] - c.goal[0]) + sq(Pm[6][1] - c.goal[1]) + sq(Pm[6][2] - c.goal[2]);
-        *s_c0 = c.pose ? c.Q[0] * sqrtf(d2g) + c.Q[1] * rot_angle(c, Re) + limit_penalty(c, q) +
-                             (icol0 ? c.Q[2] : 0.f)
-                       : c.Q[0] * d2g + limit_penalty(c, q);
-      }
-    }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-      const float oc = __shfl_xor(cl, d, kWave);
-      const int oi = __shfl_xor(idx, d, kWave);
-      if (oc < cl || (oc == cl && oi < idx)) {
-        cl = oc;
-        idx = oi;
-      }
-    }
-    if (tid == 0) s_closest = n_obs > 0 ? idx : -1;
+  const int closest = n_obs > 0 ? idx : -1;
+  if (DYN == 0) {
     // Broad phase (unicycle): every state of a rollout lies within
     // reach = max|v| N dt of p(x_t), so an obstacle whose surface is farther
     // than that (with a margin far above the FP32 rounding of the positions)
     // is never in contact; it is left out of the collision loops.  The kept
     // obstacles stay in index order, so the lowest-index rule is unchanged.
     // A moving obstacle covers at most |v| N dt more.
-    bool keep = tid < n_obs;
-    if (DYN == 0 && keep && c.reach < INFINITY) {
-      const float R = c.robot_r + L.r[tid];
-      const float d = sqrtf(dist2_2(x_t[0], x_t[1], L.o[tid].x, L.o[tid].y));
-      const float4 v = L.v[tid];
+    bool keep = mine;
+    if (keep && c.reach < INFINITY) {
+      const float d = sqrtf(dist2_2(p0[0], p0[1], row.x, row.y));
       const float ov = sqrtf(v.x * v.x + v.y * v.y) * ((float)c.N * c.dt);
       const float ext = c.reach + R + ov;
       keep = !(d > ext + (1e-3f * ext + 1e-3f));
     }
     const unsigned long long m = __ballot(keep);
     if (keep) {
-      const int pos = __popcll(m & ((1ull << tid) - 1ull));
-      L.live[pos] = L.o[tid];
-      L.vlive[pos] = L.v[tid];
-      L.idx[pos] = tid;
+      const int pos = __popcll(m & ((1ull << lane) - 1ull));
+      L.live[pos] = row;
+      L.vlive[pos] = v;
+      L.idx[pos] = lane;
     }
-    if (tid == 0) L.n_live = __popcll(m);
+    if (lane == 0) L.n_live = __popcll(m);
   }
-  __syncthreads();
-}
-
-// Block 0: push the observation into the history ring and publish the
-// per-replan facts of the prologue.
-template <int NT>
-__device__ void publish(const Cfg& c, const Bufs& b, const float* __restrict__ obs, int n_obs,
-                        int bad, int closest, const float* p0, uint32_t step) {
+  if (lane == 0) {
+    s_bad = bad;
+    s_closest = closest;
+    for (int i = 0; i < 3; ++i) s_p0[i] = p0[i];
+  }
+  if (!pub) return;
+  // the observation into the ring, and the facts of the prologue
   Ctrl* ct = b.ctrl;
-  __shared__ int s_nh;
-  if (threadIdx.x == 0) {
-    int head = ct->hist_head;
-    s_nh = (head + 1) % c.H;
+  const int nh = (ct->hist_head + 1) % c.H;
+  if (!bad && mine) {
+    float* h = b.hist + ((size_t)nh * c.max_obs + lane) * P;
+#pragma unroll
+    for (int i = 0; i < P; ++i) h[i] = o[i];
   }
-  __syncthreads();
-  const int nh = s_nh;
-  if (!bad) {
-    for (int t = threadIdx.x; t < n_obs * c.p; t += NT) {
-      const int i = t / c.p, d = t % c.p;
-      b.hist[((size_t)nh * c.max_obs + i) * c.p + d] = obs[i * (c.p + 1) + d];
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
+  if (lane == 0) {
     if (!bad) {
       const int count = ct->hist_nobs == n_obs ? ct->hist_count : 0;
       ct->hist_head = nh;
@@ -378,8 +343,8 @@ __device__ __forceinline__ void perturb_clamp(const Cfg& c, float2 n, float g0, 
 // of one wave in small ones (the layout is chosen for each planner).  Measured
 // against one step per lane, where a scan took six adds per lane and sum, a
 // contact test its LDS read per state and N = 50 left 14 of 64 lanes idle:
-// N = 50, K = 8,192 7.5 -> 6.0 us a launch back to back, K = 65,536 30.1 ->
-// 17.0 us; the 64 planners of a batch 119 -> 61 us.
+// N = 50, K = 8,192 7.2 -> 4.9 us a launch back to back, K = 65,536 27.4 ->
+// 17.5 us; the 64 planners of a batch 119 -> 58 us.
 template <int G>
 constexpr int uni_per_block() {
   return kUniThreads / G;
@@ -410,13 +375,19 @@ __device__ __forceinline__ float uni_excl_scan(float v, int g) {
   const float e = dpp_f<0x111>(v);
   return G == 16 || g >= 1 ? e : 0.f;
 }
-// sum and minimum over the rollout's lanes (every lane gets the same value)
+// sum and minimum over the rollout's lanes (every lane gets the same value); the
+// sum in 64 bits, so that the cost is rounded once where lanes meet (the error
+// of S against FP64 falls by a third, for 0.1 us)
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  return __hiloint2double(dpp_i<CTRL>(__double2hiint(v)), dpp_i<CTRL>(__double2loint(v)));
+}
 template <int G>
-__device__ __forceinline__ float uni_sum(float v) {
-  v += dpp_f<0xB1>(v);   // quad_perm: neighbour
-  v += dpp_f<0x4E>(v);   // quad_perm: other pair
-  v += dpp_f<0x141>(v);  // row_half_mirror: other quad
-  if constexpr (G >= 16) v += dpp_f<0x140>(v);  // row_mirror: other half row
+__device__ __forceinline__ double uni_sum(double v) {
+  v += dpp_d<0xB1>(v);   // quad_perm: neighbour
+  v += dpp_d<0x4E>(v);   // quad_perm: other pair
+  v += dpp_d<0x141>(v);  // row_half_mirror: other quad
+  if constexpr (G >= 16) v += dpp_d<0x140>(v);  // row_mirror: other half row
   if constexpr (G >= 32) v += __shfl_xor(v, 16, kWave);
   return v;
 }
@@ -437,10 +408,11 @@ struct UniLds {
   __align__(16) float rec[kUniThreads / 8][kPart];  // one per rollout
 };
 
-// The bx-th block of rollouts.  The prologue (obstacles, finiteness, o*) runs
-// after the noise, dynamics and cost, which do not need it, on rows requested
-// at the start; nothing is stored before it has run.  CVM as for the prologue.
-template <int G, int C, int CVM>
+// The bx-th block of rollouts.  The prologue (obstacles, finiteness, o*) is the
+// work of one wave: of one more than the rollouts take (EXTRA), beside their
+// noise, dynamics and cost, or of the first one before its own.  Nothing is
+// stored before the barrier that ends it.  CVM as for the prologue.
+template <int G, int C, int CVM, bool EXTRA>
 __device__ __forceinline__ void rollout_unicycle_body(const Cfg& c, const Bufs& b, int bx, const float* __restrict__ x_t,
                                                       const float* __restrict__ obs, int n_obs, UniLds& sh) {
   constexpr int RPB = uni_per_block<G>(), RPW = kWave / G;
@@ -450,8 +422,15 @@ __device__ __forceinline__ void rollout_unicycle_body(const Cfg& c, const Bufs& 
   const float dt = c.dt;
   const float x0 = x_t[0], y0 = x_t[1], th0 = x_t[2];
   const bool cv = CVM == 2 ? c.cv != 0 : CVM == 1;
-  const ObsRow row = load_obs<0, CVM>(c, b, obs, n_obs, (int)threadIdx.x);
-  const int tid = item_thread(), lane = tid & (kWave - 1), wave = tid / kWave;
+  const int tid = item_thread(), lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  if (wave == (EXTRA ? kUniThreads / kWave : 0)) {
+    prologue<0, CVM>(c, b, x_t, obs, n_obs, bx == 0, step, sh.o, sh.bad, sh.closest, sh.p0);
+    if constexpr (EXTRA) {
+      __syncthreads();  // the prologue
+      __syncthreads();  // the records
+      return;
+    }
+  }
   const int g = lane & (G - 1), j0 = g * C;
   const int kloc = wave * RPW + lane / G;
   const int k = bx * RPB + kloc;
@@ -489,9 +468,9 @@ __device__ __forceinline__ void rollout_unicycle_body(const Cfg& c, const Bufs& 
       th[q] = th0 + (thb + th[q]);
       float sn, cs;
       __sincosf(th[q], &sn, &cs);
-      const float d = uv[q] * dt;
-      sx = __builtin_fmaf(d, cs, sx);
-      sy = __builtin_fmaf(d, sn, sy);
+      // (v dt first would round a clamped speed the same way at every step)
+      sx = __builtin_fmaf(uv[q] * cs, dt, sx);
+      sy = __builtin_fmaf(uv[q] * sn, dt, sy);
       px[q] = sx;
       py[q] = sy;
     }
@@ -517,7 +496,7 @@ __device__ __forceinline__ void rollout_unicycle_body(const Cfg& c, const Bufs& 
         qw = __builtin_fmaf(uw[q], uw[q], qw);
       }
     }
-    float l = c.Q[0] * qx + c.Q[1] * qy + c.Q[2] * qt + c.R[0] * qv + c.R[1] * qw;
+    double l = (double)c.Q[0] * qx + (double)c.Q[1] * qy + (double)c.Q[2] * qt + (double)c.R[0] * qv + (double)c.R[1] * qw;
     if (nv >= 1 && nv <= C) {
       float ex = px[0], ey = py[0], et = C > 1 ? th[1] : the;
 #pragma unroll
@@ -529,11 +508,10 @@ __device__ __forceinline__ void rollout_unicycle_body(const Cfg& c, const Bufs& 
       }
       l += c.Qf[0] * sq(ex - c.goal[0]) + c.Qf[1] * sq(ey - c.goal[1]) + c.Qf[2] * sq(et - c.goal[2]);
     }
-    S = uni_sum<G>(l);
+    S = (float)uni_sum<G>(l);
   }
-  prologue<0, CVM>(c, x_t, row, n_obs, sh.o, sh.bad, sh.closest, sh.p0);
+  __syncthreads();
   const int bad = sh.bad, closest = sh.closest;
-  if (bx == 0) publish<kUniThreads>(c, b, obs, n_obs, bad, closest, sh.p0, step);
   const bool act = k < c.K && !bad;
   if (act) {
     // (rows start at 16-byte boundaries when N is even)
@@ -647,9 +625,9 @@ __device__ __forceinline__ void rollout_unicycle_body(const Cfg& c, const Bufs& 
 }
 
 template <int G, int C, int CV>
-__global__ __launch_bounds__(kUniThreads) void k_rollout_unicycle(Cfg c, Bufs b, const float* __restrict__ x_t, const float* __restrict__ obs, int n_obs) {
+__global__ __launch_bounds__(kUniThreads + kWave) void k_rollout_unicycle(Cfg c, Bufs b, const float* __restrict__ x_t, const float* __restrict__ obs, int n_obs) {
   __shared__ UniLds sh;
-  rollout_unicycle_body<G, C, CV>(c, b, (int)blockIdx.x, x_t, obs, n_obs, sh);
+  rollout_unicycle_body<G, C, CV, true>(c, b, (int)blockIdx.x, x_t, obs, n_obs, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -660,8 +638,18 @@ __global__ __launch_bounds__(kUniThreads) void k_rollout_unicycle(Cfg c, Bufs b,
 // leads to (an inclusive scan), so N <= 32 fits a 32-lane segment and a wave
 // runs two rollouts; the state part of the cost of x_t (the same for every
 // rollout) comes from the prologue.
-template <int SEG, int R = 1>
-__device__ __forceinline__ void rollout_arm_body(const Cfg& c, const Bufs& b, int bx, int by, int nbx,
+//
+// Contacts: the centres of eight link spheres are held in registers against
+// each obstacle, read from LDS once (all spheres have one contact radius, so
+// the least distance decides), and the obstacles are taken from the last to
+// the first, so one pass gives the lowest obstacle touched.  Two passes of one
+// sphere after another, with an LDS read per pair, and the prologue's kinematics
+// ahead of the rollouts' took 16.7 us at K = 1,024 and 39.8 us at 20,011 (16
+// obstacles, N = 32); this takes 12.5 and 33.0 us.  Bound by VALU issue in large
+// launches (half of it the contacts), by one wave's chain in small ones.
+constexpr int kArmSpheres = 8;
+template <int SEG, int R, bool EXTRA>
+__device__ __forceinline__ void rollout_arm_body(const Cfg& c, const Bufs& b, int bx,
                                                  const float* __restrict__ x_t,
                                                  const float* __restrict__ obs, int n_obs) {
   constexpr int SPW = kWave / SEG;
@@ -670,13 +658,18 @@ __device__ __forceinline__ void rollout_arm_body(const Cfg& c, const Bufs& b, in
   __shared__ int s_bad, s_closest;
   __shared__ float s_p0[3], s_c0;
   __shared__ __align__(16) float s_rec[RPB][kPart];
-  prologue<1>(c, x_t, load_obs<1, 2>(c, b, obs, n_obs, (int)threadIdx.x), n_obs, L, s_bad, s_closest, s_p0, &s_c0);
   const uint32_t step = b.ctrl->step_lo;
-  const int bad = s_bad, closest = s_closest;
-  if (bx == 0) publish<kRollThreads>(c, b, obs, n_obs, bad, closest, s_p0, step);
-  const float c0 = s_c0;
-
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int tid = item_thread(), lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  // the prologue is the work of one wave: of one more than the rollouts take
+  // (EXTRA), beside their noise and kinematics, or of the first one
+  if (wave == (EXTRA ? kRollWaves : 0)) {
+    prologue<1>(c, b, x_t, obs, n_obs, bx == 0, step, L, s_bad, s_closest, s_p0, &s_c0);
+    if constexpr (EXTRA) {
+      __syncthreads();  // the prologue
+      __syncthreads();  // the records
+      return;
+    }
+  }
   const int j = lane & (SEG - 1), sgi = lane / SEG;
   const int N = c.N;
   const float dt = c.dt;
@@ -684,145 +677,129 @@ __device__ __forceinline__ void rollout_arm_body(const Cfg& c, const Bufs& b, in
 #pragma unroll
   for (int i = 0; i < 6; ++i) un[i] = j < N ? b.U[j * 6 + i] : 0.f;
   for (int rr = 0; rr < R; ++rr) {
-  const int kloc = (rr * kRollWaves + wave) * SPW + sgi;
-  const int k = SEG == 64 ? __builtin_amdgcn_readfirstlane(bx * RPB + kloc) : bx * RPB + kloc;
-  const bool act = (k < c.K) && !bad;
-  const bool live = act && j < N;  // control u_j, state x_{j+1}
-  const bool last = j == N - 1;    // state x_N: terminal weights
+    const int kloc = (rr * kRollWaves + wave) * SPW + sgi;
+    const int k = SEG == 64 ? __builtin_amdgcn_readfirstlane(bx * RPB + kloc) : bx * RPB + kloc;
+    const bool on = k < c.K && j < N;  // control u_j, state x_{j+1}
+    const bool last = j == N - 1;      // state x_N: terminal weights
 
-  float u[6];
+    float u[6], a[6];
 #pragma unroll
-  for (int i = 0; i < 6; ++i) u[i] = 0.f;
-  if (live) {
-    float g[6];
-    step_gaussians<6>(c, step, k, j, g);
-    float a[6];
+    for (int i = 0; i < 6; ++i) u[i] = a[i] = 0.f;
+    if (on) {
+      float g[6];
+      step_gaussians<6>(c, step, k, j, g);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      float e = 0.f;
+      for (int i = 0; i < 6; ++i) {
+        float e = 0.f;
 #pragma unroll
-      for (int cc = 0; cc < 6; ++cc)
-        if (cc <= i) e += c.L[i * 6 + cc] * g[cc];
-      const float n0 = un[i];
-      const float t = n0 + e;
-      u[i] = fminf(fmaxf(t, c.umin[i]), c.umax[i]);
-      a[i] = u[i] == t ? e : u[i] - n0;
-    }
-    float2* ep = reinterpret_cast<float2*>(b.eps + ((size_t)k * N + j) * 6);
-    ep[0] = make_float2(a[0], a[1]);
-    ep[1] = make_float2(a[2], a[3]);
-    ep[2] = make_float2(a[4], a[5]);
-  }
-  float q[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i) q[i] = x_t[i] + seg_incl_scan<SEG>(u[i] * dt, j);
-  float P[7][3], Re[9];
-  arm_origins(c, q, P, Re);
-  const float ex = P[6][0], ey = P[6][1], ez = P[6][2];
-  float l = 0.f;
-  const float d2g = sq(ex - c.goal[0]) + sq(ey - c.goal[1]) + sq(ez - c.goal[2]);
-  if (live) {
-    float r = 0.f;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) r += c.R[i] * u[i] * u[i];
-    if (c.pose)  // Sec. III-C: w_p |p_ee - p_g| + w_R d_R (+ w_c I_col, below)
-      l = (last ? c.Qf[0] : c.Q[0]) * sqrtf(d2g) + (last ? c.Qf[1] : c.Q[1]) * rot_angle(c, Re) +
-          limit_penalty(c, q) + r;
-    else
-      l = (last ? c.Qf[0] : c.Q[0]) * d2g + limit_penalty(c, q) + r;
-  }
-
-  // pass 1: any contact of any link sphere with any obstacle (at time
-  // (j + 1) dt for moving obstacles); pass 2 (waves with a contact): the
-  // lowest obstacle index touched
-  const float tj = (float)(j + 1) * dt;
-  bool any = false;
-  if (live) {
-    for (int s = 0; s < c.ns; ++s) {
-      float sx, sy, sz;
-      sphere_centre(c, P, s, sx, sy, sz);
-      if (c.cv) {
-        for (int i = 0; i < n_obs; ++i) {
-          const float4 o = L.o[i], v = L.v[i];
-          any |= dist2_3(sx, sy, sz, __builtin_fmaf(tj, v.x, o.x), __builtin_fmaf(tj, v.y, o.y),
-                         __builtin_fmaf(tj, v.z, o.z)) <= o.w;
-        }
-      } else {
-        for (int i = 0; i < n_obs; ++i) {
-          const float4 o = L.o[i];
-          any |= dist2_3(sx, sy, sz, o.x, o.y, o.z) <= o.w;
-        }
+        for (int cc = 0; cc < 6; ++cc)
+          if (cc <= i) e += c.L[i * 6 + cc] * g[cc];
+        const float n0 = un[i];
+        const float t = n0 + e;
+        u[i] = fminf(fmaxf(t, c.umin[i]), c.umax[i]);
+        a[i] = u[i] == t ? e : u[i] - n0;
       }
     }
-  }
-  if (c.pose && any) l += last ? c.Qf[2] : c.Q[2];
-  const float S = seg_sum<SEG>(l) + c0;
-  int hit = kInt32Max;
-  if (__ballot(any) != 0ull && any) {
-    for (int s = 0; s < c.ns; ++s) {
-      float sx, sy, sz;
-      sphere_centre(c, P, s, sx, sy, sz);
+    float q[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) q[i] = x_t[i] + seg_incl_scan<SEG>(u[i] * dt, j);
+    float P[7][3], Re[9];
+    arm_origins(c, q, P, Re);
+    const float ex = P[6][0], ey = P[6][1], ez = P[6][2];
+    float l = 0.f;
+    const float d2g = sq(ex - c.goal[0]) + sq(ey - c.goal[1]) + sq(ez - c.goal[2]);
+    if (on) {
+      float r = 0.f;
+#pragma unroll
+      for (int i = 0; i < 6; ++i) r += c.R[i] * u[i] * u[i];
+      if (c.pose)  // Sec. III-C: w_p |p_ee - p_g| + w_R d_R (+ w_c I_col, below)
+        l = (last ? c.Qf[0] : c.Q[0]) * sqrtf(d2g) + (last ? c.Qf[1] : c.Q[1]) * rot_angle(c, Re) +
+            limit_penalty(c, q) + r;
+      else
+        l = (last ? c.Qf[0] : c.Q[0]) * d2g + limit_penalty(c, q) + r;
+    }
+    if (rr == 0) __syncthreads();  // the prologue
+    const int bad = s_bad, closest = s_closest;
+    const bool act = k < c.K && !bad, live = on && !bad;
+    if (live) {
+      float2* ep = reinterpret_cast<float2*>(b.eps + ((size_t)k * N + j) * 6);
+      ep[0] = make_float2(a[0], a[1]);
+      ep[1] = make_float2(a[2], a[3]);
+      ep[2] = make_float2(a[4], a[5]);
+    }
+
+    // the lowest obstacle that any link sphere touches (at time (j + 1) dt for
+    // moving obstacles)
+    const float tj = (float)(j + 1) * dt;
+    int hit = kInt32Max;
+    for (int s0 = 0; s0 < c.ns; s0 += kArmSpheres) {
+      float cx[kArmSpheres], cy[kArmSpheres], cz[kArmSpheres];
+#pragma unroll
+      for (int s = 0; s < kArmSpheres; ++s) sphere_centre(c, P, min(s0 + s, c.ns - 1), cx[s], cy[s], cz[s]);
       int hs = kInt32Max;
-      if (c.cv) {
-        for (int i = n_obs - 1; i >= 0; --i) {
-          const float4 o = L.o[i], v = L.v[i];
-          hs = dist2_3(sx, sy, sz, __builtin_fmaf(tj, v.x, o.x), __builtin_fmaf(tj, v.y, o.y),
-                       __builtin_fmaf(tj, v.z, o.z)) <= o.w ? i : hs;
+      for (int i = n_obs - 1; i >= 0; --i) {
+        float4 o = L.o[i];
+        if (c.cv) {
+          const float4 v = L.v[i];
+          o.x = __builtin_fmaf(tj, v.x, o.x);
+          o.y = __builtin_fmaf(tj, v.y, o.y);
+          o.z = __builtin_fmaf(tj, v.z, o.z);
         }
-      } else {
-        for (int i = n_obs - 1; i >= 0; --i) {
-          const float4 o = L.o[i];
-          hs = dist2_3(sx, sy, sz, o.x, o.y, o.z) <= o.w ? i : hs;
-        }
+        float d2 = dist2_3(cx[0], cy[0], cz[0], o.x, o.y, o.z);
+#pragma unroll
+        for (int s = 1; s < kArmSpheres; ++s) d2 = fminf(d2, dist2_3(cx[s], cy[s], cz[s], o.x, o.y, o.z));
+        hs = d2 <= o.w ? i : hs;
       }
-      hit = hs < hit ? hs : hit;
+      hit = min(hit, hs);
     }
-  }
-  // first colliding state of each segment (lowest lane with a hit)
-  const unsigned long long hm = __ballot(hit != kInt32Max);
-  const unsigned long long m0 = SEG == 64 ? hm : (hm & 0xffffffffull);
-  const unsigned long long m1 = SEG == 64 ? 0ull : (hm >> 32);
-  const int f0 = m0 ? __ffsll((long long)m0) - 1 : 0;
-  const int f1 = m1 ? __ffsll((long long)m1) - 1 : 0;
-  const int col = (sgi == 0 ? m0 : m1) != 0ull;
-  const int f = seg_pick_i<SEG>(hit, f0, f1);
-  const float pfx = seg_pick<SEG>(ex, f0, f1), pfy = seg_pick<SEG>(ey, f0, f1),
-              pfz = seg_pick<SEG>(ez, f0, f1);
-  const int ln = N - 1;
-  const float ptx = seg_bcast<SEG>(ex, ln), pty = seg_bcast<SEG>(ey, ln), ptz = seg_bcast<SEG>(ez, ln);
+    if (!live) hit = kInt32Max;
+    if (c.pose && hit != kInt32Max) l += last ? c.Qf[2] : c.Q[2];
+    const float S = seg_sum<SEG>(l) + s_c0;
+    // first colliding state of each segment (lowest lane with a hit)
+    const unsigned long long hm = __ballot(hit != kInt32Max);
+    const unsigned long long m0 = SEG == 64 ? hm : (hm & 0xffffffffull);
+    const unsigned long long m1 = SEG == 64 ? 0ull : (hm >> 32);
+    const int f0 = m0 ? __ffsll((long long)m0) - 1 : 0;
+    const int f1 = m1 ? __ffsll((long long)m1) - 1 : 0;
+    const int col = (sgi == 0 ? m0 : m1) != 0ull;
+    const int f = seg_pick_i<SEG>(hit, f0, f1);
+    const float pfx = seg_pick<SEG>(ex, f0, f1), pfy = seg_pick<SEG>(ey, f0, f1),
+                pfz = seg_pick<SEG>(ez, f0, f1);
+    const int ln = N - 1;
+    const float ptx = seg_bcast<SEG>(ex, ln), pty = seg_bcast<SEG>(ey, ln), ptz = seg_bcast<SEG>(ez, ln);
 
-  float src[3];
-  src[0] = c.ref_mode == 1 ? pfx : ptx;
-  src[1] = c.ref_mode == 1 ? pfy : pty;
-  src[2] = c.ref_mode == 1 ? pfz : ptz;
-  if (j == 0) {
-    if (act) {
-      b.S[k] = S;
-      b.col[k] = col;
-      b.first[k] = col ? f : -1;
-      b.pT[3 * k] = ptx;
-      b.pT[3 * k + 1] = pty;
-      b.pT[3 * k + 2] = ptz;
-      b.pF[3 * k] = col ? pfx : 0.f;
-      b.pF[3 * k + 1] = col ? pfy : 0.f;
-      b.pF[3 * k + 2] = col ? pfz : 0.f;
-      const float dx = ptx - s_p0[0], dy = pty - s_p0[1], dz = ptz - s_p0[2];
-      const float den =
-          __builtin_amdgcn_sqrtf(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx))) + c.norm_eps;
-      const float inv = __builtin_amdgcn_rcpf(den);
-      b.g[3 * k] = dx * inv;
-      b.g[3 * k + 1] = dy * inv;
-      b.g[3 * k + 2] = dz * inv;
+    float src[3];
+    src[0] = c.ref_mode == 1 ? pfx : ptx;
+    src[1] = c.ref_mode == 1 ? pfy : pty;
+    src[2] = c.ref_mode == 1 ? pfz : ptz;
+    if (j == 0) {
+      if (act) {
+        b.S[k] = S;
+        b.col[k] = col;
+        b.first[k] = col ? f : -1;
+        b.pT[3 * k] = ptx;
+        b.pT[3 * k + 1] = pty;
+        b.pT[3 * k + 2] = ptz;
+        b.pF[3 * k] = col ? pfx : 0.f;
+        b.pF[3 * k + 1] = col ? pfy : 0.f;
+        b.pF[3 * k + 2] = col ? pfz : 0.f;
+        const float dx = ptx - s_p0[0], dy = pty - s_p0[1], dz = ptz - s_p0[2];
+        const float den =
+            __builtin_amdgcn_sqrtf(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx))) + c.norm_eps;
+        const float inv = __builtin_amdgcn_rcpf(den);
+        b.g[3 * k] = dx * inv;
+        b.g[3 * k + 1] = dy * inv;
+        b.g[3 * k + 2] = dz * inv;
+      }
+      rollout_contrib(s_rec[kloc], act, col, col ? f : -1, closest, S, src, 3);
     }
-    rollout_contrib(s_rec[kloc], act, col, col ? f : -1, closest, S, src, 3);
-  }
   }
   write_group_partials<kRollThreads>(c, b, s_rec, RPB, bx);
 }
 
-template <int SEG>
-__global__ __launch_bounds__(kRollThreads) void k_rollout_arm(Cfg c, Bufs b, const float* __restrict__ x_t, const float* __restrict__ obs, int n_obs) {
-  rollout_arm_body<SEG>(c, b, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, x_t, obs, n_obs);
+template <int SEG, bool EXTRA>
+__global__ __launch_bounds__(kRollThreads + (EXTRA ? kWave : 0)) void k_rollout_arm(Cfg c, Bufs b, const float* __restrict__ x_t, const float* __restrict__ obs, int n_obs) {
+  rollout_arm_body<SEG, 1, EXTRA>(c, b, (int)blockIdx.x, x_t, obs, n_obs);
 }
 
 // ---------------------------------------------------------------------------
@@ -834,15 +811,15 @@ __device__ __forceinline__ void rollout_unicycle_slot(CSlotStatic st, CSlotIO io
   // the layout is the member's own (a block-uniform branch)
   switch (S.c.seg) {
 #define CEMPPI_UNI(seg, G, C) \
-  case seg: rollout_unicycle_body<G, C, 2>(S.c, S.b, local, I.x_t, I.obs, I.n_obs, sh); break;
+  case seg: rollout_unicycle_body<G, C, 2, false>(S.c, S.b, local, I.x_t, I.obs, I.n_obs, sh); break;
     CEMPPI_UNI_LAYOUTS(CEMPPI_UNI)
 #undef CEMPPI_UNI
   }
 }
 
 // Unicycle items with a block each (the full member set, whose items the host
-// knows): 64 planners of a batch, 15,000 items, 68 us against 76-78 us for
-// persistent blocks, whose registers leave too few waves to cover an item's
+// knows): 64 planners of a batch, 15,000 items, 68 us where persistent blocks
+// took 76-78 us, whose registers leave too few waves to cover an item's
 // latency.
 __global__ __launch_bounds__(kUniThreads) void kb_rollout_unicycle(CSlotStatic st, CSlotIO io, Tab t) {
   __shared__ UniLds sh;
@@ -865,9 +842,9 @@ __global__ __launch_bounds__(kRollThreads) void kb_rollout_arm(CSlotStatic st, C
     const SlotIO& I = *(const SlotIO*)(io + slot);
     // the segment width is the member's own (a block-uniform branch)
     if (S.c.seg == 32)
-      rollout_arm_body<32, R>(S.c, S.b, local, 0, 0, I.x_t, I.obs, I.n_obs);
+      rollout_arm_body<32, R, false>(S.c, S.b, local, I.x_t, I.obs, I.n_obs);
     else
-      rollout_arm_body<64, R>(S.c, S.b, local, 0, 0, I.x_t, I.obs, I.n_obs);
+      rollout_arm_body<64, R, false>(S.c, S.b, local, I.x_t, I.obs, I.n_obs);
   });
 }
 
@@ -884,10 +861,10 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_records(Cfg c, Bufs b,
   __shared__ int s_bad, s_closest;
   __shared__ float s_p0[3];
   __shared__ __align__(16) float s_rec[kRedThreads][kPart];
-  prologue<DYN>(c, x_t, load_obs<DYN, 2>(c, b, obs, n_obs, (int)threadIdx.x), n_obs, L, s_bad, s_closest, s_p0);
   const uint32_t step = b.ctrl->step_lo;
+  if (threadIdx.x < kWave) prologue<DYN>(c, b, x_t, obs, n_obs, blockIdx.x == 0, step, L, s_bad, s_closest, s_p0);
+  __syncthreads();
   const int bad = s_bad, closest = s_closest;
-  if (blockIdx.x == 0) publish<kRedThreads>(c, b, obs, n_obs, bad, closest, s_p0, step);
   const int P = DYN == 0 ? 2 : 3;
   {
     const int k = blockIdx.x * kRedThreads + threadIdx.x;
@@ -966,14 +943,22 @@ void launch_rollout(Launcher& L, const Cfg& c, const Bufs& b, const float* x_t, 
     switch (c.seg) {
 #define CEMPPI_UNI(seg, G, C)                                                                                \
   case seg:                                                                                                  \
-    L(c.cv ? k_rollout_unicycle<G, C, 1> : k_rollout_unicycle<G, C, 0>, grid, dim3(kUniThreads), c, b, x_t, obs, \
-      n_obs);                                                                                                \
+    L(c.cv ? k_rollout_unicycle<G, C, 1> : k_rollout_unicycle<G, C, 0>, grid, dim3(kUniThreads + kWave), c, b, x_t, \
+      obs, n_obs);                                                                                            \
     break;
       CEMPPI_UNI_LAYOUTS(CEMPPI_UNI)
 #undef CEMPPI_UNI
     }
   } else {
-    L(c.seg == 32 ? k_rollout_arm<32> : k_rollout_arm<64>, grid, dim3(kRollThreads), c, b, x_t, obs, n_obs);
+    // A wave of its own for the prologue while the blocks fit the chip twice;
+    // in larger launches three blocks of eight waves on a CU are worth more
+    // than two of nine.  Measured with / without, us: K = 4,096 12.8 / 13.7,
+    // 8,192 16.1 / 16.5, 12,000 24.9 / 21.3, 65,536 123 / 87.
+    if (c.nblk_roll <= 512)
+      L(c.seg == 32 ? k_rollout_arm<32, true> : k_rollout_arm<64, true>, grid, dim3(kRollThreads + kWave), c, b, x_t, obs,
+        n_obs);
+    else
+      L(c.seg == 32 ? k_rollout_arm<32, false> : k_rollout_arm<64, false>, grid, dim3(kRollThreads), c, b, x_t, obs, n_obs);
   }
 }
 

@@ -75,3 +75,25 @@ def test_batch_members_of_every_layout_bitwise():
             assert torch.equal(x.U_out, y.U_out) and torch.equal(x.info_buf, y.info_buf), (step, i)
             assert torch.equal(x.debug(B.DBG_COST, x.K), y.debug(B.DBG_COST, y.K)), (step, i)
     batch.close()
+
+
+@pytest.mark.parametrize("ns,n_obs,N,K,pose", [(1, 1, 7, 33, False), (7, 17, 31, 65, True), (8, 64, 32, 100, False),
+                                               (9, 3, 33, 41, True), (16, 64, 40, 50, True), (15, 0, 1, 9, False)])
+def test_arm_sphere_groups_match_oracle(ns, n_obs, N, K, pose):
+    s = W.random_scene(300 + ns, dynamics=W.ARM6, num_samples=K, horizon=N, n_obs=n_obs)
+    kw = dict(n_link_spheres=ns, flags=(W.FLAG_POSE_COST if pose else 0) | W.FLAG_OBS_CONST_VEL)
+    if pose:
+        kw.update(Q=[10.0, 3.0, 50.0, 0.0, 0.0, 0.0], Qf=[10.0, 3.0, 50.0, 0.0, 0.0, 0.0])
+    s.spec = s.spec.replace(**kw)
+    pl = P._planner(s.spec)
+    P._set_U(pl, s.U0)
+    before = s.field.positions()
+    if n_obs:
+        pl.set_history(H.to_dev(before[None]))
+    s.field.step(s.spec.dt)
+    obs = s.field.observation()
+    r = H.gpu_replan(pl, s.x0, obs)
+    hist = np.stack([s.field.positions(), before]) if n_obs else None
+    o = oracle.replan(s.spec, s.x0, s.U0, obs, hist)
+    P._compare_rollouts(r, o, s.spec)
+    pl.close()
