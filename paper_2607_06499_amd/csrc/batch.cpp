@@ -174,7 +174,7 @@ void fill_tables(const ce_mppi_batch* B, const int* members, int count, int* h) 
   for (int kd = 0; kd < kPlanKinds; ++kd) {
     h[L.cnt_p[kd]] = (int)lp[kd].size();
     copy(lp[kd], L.p_slot[kd]);
-    prefix(lp[kd], L.compact[kd], [](const ce_mppi_planner* P) { return (P->c.K + 255) / 256; });
+    prefix(lp[kd], L.compact[kd], [](const ce_mppi_planner* P) { return (P->c.K + kChunk - 1) / kChunk; });
     prefix(lp[kd], L.one[kd], [](const ce_mppi_planner*) { return 1; });
     // the DBSCAN tables are written on the device by kb_plan
   }
@@ -208,10 +208,10 @@ void area_tabs(const ce_mppi_batch* B, Area& a) {
     T.plan.pref_adj[kd] = d + L.dyn_adj[kd];
     T.plan.pref_lab[kd] = d + L.dyn_lab[kd];
     T.has[kd] = B->n_p[kd] > 0;
-    T.grid_compact[kd] = std::max(1, std::min(B->compact_total[kd], 4 * cus));
+    T.grid_compact[kd] = std::max(1, std::min(B->compact_total[kd], 2 * cus));
     T.grid_one[kd] = std::max(1, std::min(B->n_p[kd], cus));
-    // one labelling block per CU fits the LDS of the angular windows
-    T.grid_lab[kd] = std::max(1, std::min(B->lab_total[kd], cus));
+    // the blocks of the angular windows take one item each, the others loop
+    T.grid_lab[kd] = std::max(1, kd == 2 ? B->lab_total[kd] : std::min(B->lab_total[kd], cus));
   }
   T.update = Tab{d + L.all_slot, d + L.update, d + L.cnt_all};
   T.finish = Tab{d + L.all_slot, d + L.finish, d + L.cnt_all};
@@ -317,7 +317,7 @@ ce_status ce_mppi_batch_create(ce_mppi_planner* const* planners, int32_t n, ce_m
     for (int ri = 0; ri < 4; ++ri) {
       B->roll_total[B->roll_kind[i]][ri] += roll_items(P, 1 << ri);
     }
-    B->compact_total[B->p_kind[i]] += (P->c.K + 255) / 256;
+    B->compact_total[B->p_kind[i]] += (P->c.K + kChunk - 1) / kChunk;
     B->update_total += P->c.nblk_upd;
   }
   B->lay.make(n);

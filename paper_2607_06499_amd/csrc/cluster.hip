@@ -94,25 +94,27 @@ __device__ __forceinline__ bool tiles_apart(const Cfg& c, const Bufs& b, int I, 
 __device__ __forceinline__ bool is_min_field(int f) { return f == P_SMIN_ALL || f == P_SMIN_FEAS; }
 
 // ---------------------------------------------------------------------------
-// Reduction of the rollout-group partial records (256-thread blocks):
-// thread t owns records t, t+256, ... (coalesced), each wave combines its
-// lanes by an xor butterfly (every lane ends with the same value), and the
-// four wave results are added in wave order.  Also returns the number of
-// feasible rollouts in records [0, upto).  A thread requests kRecBatch of its
-// records before adding any of them (in the same order).
-__device__ void reduce_partials(const Cfg& c, const Bufs& b, int upto, float* s_tot, int* s_before) {
-  __shared__ float s_w[4][kPart + 1];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+// Reduction of the rollout-group partial records by a block of kFinThreads:
+// thread t owns records t, t + kFinThreads, ... (coalesced), each wave combines
+// its lanes by a scan on DPP lane moves, and the wave results are added in wave
+// order.  Also returns the number of feasible rollouts in records [0, upto).  A
+// thread requests kRecBatch of its records before adding any of them (in the
+// same order).  (Blocks of 256 threads read four times as many records each:
+// 100 MB from the L2s at K = 65,536.)
+__device__ __forceinline__ void reduce_partials(const Cfg& c, const Bufs& b, int upto, float* s_tot, int* s_before) {
+  constexpr int NT = kFinThreads, NW = NT / kWave;
+  __shared__ float s_w[NW][kPart + 1];
+  const int tid = item_thread(), lane = tid & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
   float acc[kPart + 1];
 #pragma unroll
   for (int f = 0; f < kPart; ++f) acc[f] = is_min_field(f) ? INFINITY : 0.f;
   acc[kPart] = 0.f;
   const float4* rows = reinterpret_cast<const float4*>(b.part);
-  for (int i0 = tid; i0 < c.npart; i0 += 256 * kRecBatch) {
+  for (int i0 = tid; i0 < c.npart; i0 += NT * kRecBatch) {
     float4 x[kRecBatch], y[kRecBatch], z[kRecBatch];
 #pragma unroll
     for (int r = 0; r < kRecBatch; ++r) {
-      const int i = i0 + r * 256;
+      const int i = i0 + r * NT;
       if (i < c.npart) {
         x[r] = rows[3 * i];
         y[r] = rows[3 * i + 1];
@@ -121,7 +123,7 @@ __device__ void reduce_partials(const Cfg& c, const Bufs& b, int upto, float* s_
     }
 #pragma unroll
     for (int r = 0; r < kRecBatch; ++r) {
-      const int i = i0 + r * 256;
+      const int i = i0 + r * NT;
       if (i >= c.npart) break;
       const float v[kPart] = {x[r].x, x[r].y, x[r].z, x[r].w, y[r].x, y[r].y,
                               y[r].z, y[r].w, z[r].x, z[r].y, z[r].z, z[r].w};
@@ -130,29 +132,25 @@ __device__ void reduce_partials(const Cfg& c, const Bufs& b, int upto, float* s_
       if (i < upto) acc[kPart] += v[P_NFEAS];
     }
   }
+  if (wv * kWave < c.npart) {  // (a wave without records keeps the neutral values)
 #pragma unroll
-  for (int f = 0; f <= kPart; ++f) {
-    float v = acc[f];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const float o = __shfl_xor(v, off, kWave);
-      v = (f < kPart && is_min_field(f)) ? fminf(v, o) : v + o;
-    }
-    acc[f] = v;
+    for (int f = 0; f <= kPart; ++f)
+      acc[f] = f < kPart && is_min_field(f) ? wave_min(acc[f]) : seg_sum<kWave>(acc[f]);
   }
   if (lane == 0) {
 #pragma unroll
     for (int f = 0; f <= kPart; ++f) s_w[wv][f] = acc[f];
   }
-  __syncthreads();
+  lds_sync();
   if (tid <= kPart) {
     const bool mn = tid < kPart && is_min_field(tid);
-    const float a = s_w[0][tid], b1 = s_w[1][tid], b2 = s_w[2][tid], b3 = s_w[3][tid];
-    const float t = mn ? fminf(fminf(fminf(a, b1), b2), b3) : ((a + b1) + b2) + b3;
+    float t = s_w[0][tid];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) t = mn ? fminf(t, s_w[w][tid]) : t + s_w[w][tid];
     if (tid < kPart) s_tot[tid] = t;
     else *s_before = (int)t;
   }
-  __syncthreads();
+  lds_sync();
 }
 
 // Branch of Alg. 1 and the reference point of Eq. (11) from the totals.
@@ -212,15 +210,67 @@ __device__ __forceinline__ int win_bin(const Cfg& c, float2 zz) {
   return win_ring(c, zz) ? win_bucket(win_u(c, zz)) : kWinBins;
 }
 
+// What a replan's later kernels need of the totals (one thread).
+__device__ __forceinline__ void publish_totals(const Cfg& c, const Bufs& b, const Totals& T, const float* tot) {
+  Ctrl* ct = b.ctrl;
+  ct->n_col = T.ncol;
+  ct->n_feas = T.nfeas;
+  ct->n_ref = T.nref;
+  ct->branch = T.branch;
+  ct->status = T.status;
+  ct->smin_all = tot[P_SMIN_ALL];
+  ct->smin_feas = tot[P_SMIN_FEAS];
+  ct->M = 0;
+  ct->n_trees = 0;
+  ct->tree_overflow = 0;
+  ct->stat_direct = 0;
+  ct->sel = -1;
+  for (int i = 0; i < 3; ++i) ct->ref[i] = T.ref[i];
+  // Eq. (17) for o*, once per replan on the clustering branch (the
+  // selection reads it): the mean of H'-1 finite differences telescopes
+  // to (o_t - o_{t-H'+1}) / ((H'-1) dt)
+  float v[3] = {0.f, 0.f, 0.f};
+  int Hp = 0;
+  if (c.scene_mode == 1 && T.branch == 0) {
+    const int hc = ct->hist_count;
+    Hp = hc < c.H ? hc : c.H;
+    const int o = ct->closest;
+    if (Hp >= 2 && o >= 0) {
+      const int h0 = ct->hist_head;
+      const int h1 = (h0 - (Hp - 1) + 2 * c.H) % c.H;
+      const float* pa = b.hist + ((size_t)h0 * c.max_obs + o) * c.p;
+      const float* pz = b.hist + ((size_t)h1 * c.max_obs + o) * c.p;
+      const float den = (float)(Hp - 1) * c.dt;
+      v[0] = (pa[0] - pz[0]) / den;
+      v[1] = (pa[1] - pz[1]) / den;
+      if (c.p == 3) v[2] = (pa[2] - pz[2]) / den;
+    }
+  }
+  const float nv = sqrtf(__builtin_fmaf(v[2], v[2], __builtin_fmaf(v[1], v[1], v[0] * v[0])));
+  for (int i = 0; i < 3; ++i) {
+    ct->v_obs[i] = v[i];
+    ct->v_hat[i] = v[i] / (nv + c.norm_eps);
+  }
+  ct->dyn_h = Hp;
+  ct->dyn_ok = (c.scene_mode == 1 && Hp >= 2 && !(nv < c.v_obs_min)) ? 1 : 0;
+}
+
+// Feature of Eq. (13) of a terminal point.
+__device__ __forceinline__ float2 feature2(const Cfg& c, float2 p, float rx, float ry) {
+  const float dx = p.x - rx, dy = p.y - ry;
+  const float den = sqrtf(__builtin_fmaf(dy, dy, dx * dx)) + c.norm_eps;
+  return make_float2(dx / den, dy / den);
+}
+
 template <int P, bool BIN = false>
-__device__ __forceinline__ void compact_body(const Cfg& c, const Bufs& b, int bx, int by, int nbx) {
+__device__ __forceinline__ void compact_body(const Cfg& c, const Bufs& b, int bx) {
   using ZT = typename ZVec<P>::T;
   __shared__ float s_tot[kPart + 1];
   __shared__ int s_before;
   // the rollout's own record and the input flag are requested before the
   // partials (they are only needed on the clustering branch)
   // (unconditional loads at a clamped index keep them out of branches)
-  const int k = bx * 256 + threadIdx.x;
+  const int k = bx * kFinThreads + threadIdx.x;
   const bool ink = k < c.K;
   const int kc = ink ? k : c.K - 1;
   const int bad = b.ctrl->nonfinite;
@@ -232,72 +282,26 @@ __device__ __forceinline__ void compact_body(const Cfg& c, const Bufs& b, int bx
     pk[i] = b.pT[(size_t)kc * P + i];
     gk[i] = b.g[(size_t)kc * P + i];
   }
-  const int blk0 = (bx * 256) / kGroup;
-  reduce_partials(c, b, blk0, s_tot, &s_before);
+  reduce_partials(c, b, bx * (kFinThreads / kGroup), s_tot, &s_before);
   const Totals T = decide(c, s_tot, bad);
-  if (bx == 0 && threadIdx.x == 0) {
-    Ctrl* ct = b.ctrl;
-    ct->n_col = T.ncol;
-    ct->n_feas = T.nfeas;
-    ct->n_ref = T.nref;
-    ct->branch = T.branch;
-    ct->status = T.status;
-    ct->smin_all = s_tot[P_SMIN_ALL];
-    ct->smin_feas = s_tot[P_SMIN_FEAS];
-    ct->M = 0;
-    ct->n_trees = 0;
-    ct->tree_overflow = 0;
-    ct->stat_direct = 0;
-    ct->sel = -1;
-    for (int i = 0; i < 3; ++i) ct->ref[i] = T.ref[i];
-    // Eq. (17) for o*, once per replan on the clustering branch (the
-    // selection reads it): the mean of H'-1 finite differences telescopes
-    // to (o_t - o_{t-H'+1}) / ((H'-1) dt)
-    float v[3] = {0.f, 0.f, 0.f};
-    int Hp = 0;
-    if (c.scene_mode == 1 && T.branch == 0) {
-      const int hc = ct->hist_count;
-      Hp = hc < c.H ? hc : c.H;
-      const int o = ct->closest;
-      if (Hp >= 2 && o >= 0) {
-        const int h0 = ct->hist_head;
-        const int h1 = (h0 - (Hp - 1) + 2 * c.H) % c.H;
-        const float* pa = b.hist + ((size_t)h0 * c.max_obs + o) * c.p;
-        const float* pz = b.hist + ((size_t)h1 * c.max_obs + o) * c.p;
-        const float den = (float)(Hp - 1) * c.dt;
-        v[0] = (pa[0] - pz[0]) / den;
-        v[1] = (pa[1] - pz[1]) / den;
-        if (c.p == 3) v[2] = (pa[2] - pz[2]) / den;
-      }
-    }
-    const float nv = sqrtf(__builtin_fmaf(v[2], v[2], __builtin_fmaf(v[1], v[1], v[0] * v[0])));
-    for (int i = 0; i < 3; ++i) {
-      ct->v_obs[i] = v[i];
-      ct->v_hat[i] = v[i] / (nv + c.norm_eps);
-    }
-    ct->dyn_h = Hp;
-    ct->dyn_ok = (c.scene_mode == 1 && Hp >= 2 && !(nv < c.v_obs_min)) ? 1 : 0;
-  }
+  if (bx == 0 && threadIdx.x == 0) publish_totals(c, b, T, s_tot);
   if (T.branch != 0) return;
   const int feas = ink ? !colk : 0;
   int tot;
-  const int local = block_excl_scan<256>(feas, &tot);
+  const int local = block_excl_scan<kFinThreads>(feas, &tot);
   if (!feas) return;
   const int rank = s_before + local;
-  float d[3] = {0.f, 0.f, 0.f}, g[3] = {0.f, 0.f, 0.f};
-  for (int i = 0; i < P; ++i) {
-    d[i] = pk[i] - T.ref[i];
-    g[i] = gk[i];
-  }
-  const float nd = sqrtf(__builtin_fmaf(d[2], d[2], __builtin_fmaf(d[1], d[1], d[0] * d[0])));
-  const float den = nd + c.norm_eps;
   ZT zz, gg;
   if constexpr (P == 2) {
-    zz = make_float2(d[0] / den, d[1] / den);
-    gg = make_float2(g[0], g[1]);
+    zz = feature2(c, make_float2(pk[0], pk[1]), T.ref[0], T.ref[1]);
+    gg = make_float2(gk[0], gk[1]);
   } else {
+    float d[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) d[i] = pk[i] - T.ref[i];
+    const float den = sqrtf(__builtin_fmaf(d[2], d[2], __builtin_fmaf(d[1], d[1], d[0] * d[0]))) + c.norm_eps;
     zz = make_float4(d[0] / den, d[1] / den, d[2] / den, 0.f);
-    gg = make_float4(g[0], g[1], g[2], 0.f);
+    gg = make_float4(gk[0], gk[1], gk[2], 0.f);
   }
   reinterpret_cast<ZT*>(b.z)[rank] = zz;
   reinterpret_cast<ZT*>(b.gv)[rank] = gg;
@@ -317,8 +321,8 @@ __device__ __forceinline__ void compact_body(const Cfg& c, const Bufs& b, int bx
 }
 
 template <int P, bool BIN>
-__global__ __launch_bounds__(256) void k_compact(Cfg c, Bufs b) {
-  compact_body<P, BIN>(c, b, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x);
+__global__ __launch_bounds__(kFinThreads) void k_compact(Cfg c, Bufs b) {
+  compact_body<P, BIN>(c, b, (int)blockIdx.x);
 }
 
 // per-point DBSCAN state for a stage call on caller features
@@ -1129,29 +1133,26 @@ __device__ void uf_fallback(const Cfg& c, const Bufs& b, const float* zin, int V
 // Cluster statistics of Alg. 1 [Cluster stats]: count, cost sum, direction
 // sums (for Eq. (16)) and minimum cost.  The points are taken in chunks of
 // kChunk, one per thread of a labelling block: chunk_reduce sums clusters
-// c0 .. c0 + ncl - 1 over a chunk, each wave by an xor butterfly, the wave
+// c0 .. c0 + ncl - 1 over a chunk, each wave by a DPP scan, the wave
 // results in wave order; the chunks are added in ascending order.  Every path
 // takes this order, so the totals do not depend on the path or on how the
 // chunks were spread over blocks.  use(j, f, v) receives field f of cluster
-// c0 + j on one thread each.
-template <int P, typename F>
+// c0 + j on one thread each.  LAST: the block's last use of s_red.
+template <int P, bool LAST = false, typename F>
 __device__ __forceinline__ void chunk_reduce(int c0, int ncl, int lab, float S, typename ZVec<P>::T g,
                                              float (*s_red)[kStatClusters][6], F&& use) {
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int t = item_thread(), lane = t & (kWave - 1), w = t / kWave;
   for (int j = 0; j < ncl; ++j) {
     const bool in = lab == c0 + j;
     const int n = __popcll(__ballot(in));
     float sS = in ? S : 0.f, g0 = in ? g.x : 0.f, g1 = in ? g.y : 0.f, g2 = 0.f, mn = in ? S : INFINITY;
     if constexpr (P == 3) g2 = in ? g.z : 0.f;
     if (n) {  // wave-uniform
-#pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        sS += __shfl_xor(sS, off, kWave);
-        g0 += __shfl_xor(g0, off, kWave);
-        g1 += __shfl_xor(g1, off, kWave);
-        if constexpr (P == 3) g2 += __shfl_xor(g2, off, kWave);
-        mn = fminf(mn, __shfl_xor(mn, off, kWave));
-      }
+      sS = seg_sum<kWave>(sS);
+      g0 = seg_sum<kWave>(g0);
+      g1 = seg_sum<kWave>(g1);
+      if constexpr (P == 3) g2 = seg_sum<kWave>(g2);
+      mn = wave_min(mn);
     }
     if (lane == 0) {
       float* r = s_red[w][j];
@@ -1163,25 +1164,25 @@ __device__ __forceinline__ void chunk_reduce(int c0, int ncl, int lab, float S, 
       r[5] = (float)n;
     }
   }
-  __syncthreads();
-  const int j = threadIdx.x / kStatFields, f = threadIdx.x % kStatFields;
+  LAST ? lds_sync() : __syncthreads();
+  const int j = t / kStatFields, f = t % kStatFields;
   if (j < ncl && f < 6) {
     float v = s_red[0][j][f];
 #pragma unroll
     for (int q = 1; q < kFinThreads / kWave; ++q) v = f == 4 ? fminf(v, s_red[q][j][f]) : v + s_red[q][j][f];
     use(j, f, v);
   }
-  __syncthreads();
+  if (!LAST) __syncthreads();
 }
 static_assert(kStatClusters * kStatFields <= kFinThreads, "one thread per cluster and field");
 
 // at most kStatClusters clusters: the sums of chunk q go to the statistics
 // array, and the selection adds the chunks
-template <int P>
+template <int P, bool LAST = false>
 __device__ __forceinline__ void chunk_stats(const Bufs& b, int q, int M, int lab, float S, typename ZVec<P>::T g,
                                             float (*s_red)[kStatClusters][6]) {
   float* out = b.stat + (size_t)q * (kStatClusters * kStatFields);
-  chunk_reduce<P>(0, M, lab, S, g, s_red, [&](int j, int f, float v) { out[j * kStatFields + f] = v; });
+  chunk_reduce<P, LAST>(0, M, lab, S, g, s_red, [&](int j, int f, float v) { out[j * kStatFields + f] = v; });
 }
 
 // more clusters: one block takes every chunk (first: the chunk starts the
@@ -2307,6 +2308,7 @@ struct WinFast {
   // off-ring points
   int parent[kWave + kOffMax], cmin[kWave + kOffMax];
   float red[kFinThreads / kWave][kStatClusters][6];
+  short own[kChunk];  // place of the block's own points among the open or the off-ring points
   int nopen, nu, nz, no, nmaybe, M;
 };
 struct WinGeneral {
@@ -2316,6 +2318,10 @@ struct WinGeneral {
 };
 struct WinLds {
   int start[kWinBins + 2];  // first position of each bucket; [kWinBins]: ring points
+  // in the compacting form: feasible rollouts of every 64 and their number before each
+  unsigned long long fmask[kPostMaxK / kWave];
+  int frank[kPostMaxK / kWave];
+  int vidx[kChunk];  // and the rollout and bucket of each of the block's own points
   union {
     WinFast f;
     WinGeneral g;
@@ -2338,9 +2344,11 @@ __device__ __forceinline__ int win_npts(const int* start, int lo, int hi) {
   return x <= kWinBins ? start[x] - start[m] : start[kWinBins] - start[m] + start[x - kWinBins];
 }
 // ring points that are neighbours of every point of bucket j for certain: the
-// part of the inner window that the points of the bucket share
-__device__ __forceinline__ int win_sure(const Cfg& c, const int* start, int j) {
-  return win_npts(start, (int)ceilf((float)(j + 1) - c.w_in), (int)floorf((float)j + c.w_in) - 1);
+// buckets j + 1 - floor(w_in) .. j - 1 + floor(w_in), which every point of the
+// bucket has in its inner window (at least five buckets, at most a quarter turn)
+__device__ __forceinline__ int win_sure(const Cfg& c, const int* start, int nring, int j) {
+  const int f = (int)c.w_in, m = wmod(j + 1 - f), x = m + 2 * f - 1;
+  return start[x & (kWinBins - 1)] + (x >= kWinBins ? nring : 0) - start[m];
 }
 
 // The general form: every block counts its own points exactly (ring points of
@@ -2409,28 +2417,71 @@ __device__ __forceinline__ void win_general(const Cfg& c, const Bufs& b, int V, 
   wcc_body<true>(c, b, nullptr, V, nullptr, nullptr, nullptr, L.cc, L.start, lst);
 }
 
-// Block bx of the labelling: the solution over the buckets, then its own
-// chunk; false (for the whole block) where the set needs the general form.  Bound by latency: a chain of about ten barriers and three load
-// rounds, the same at every size up to the passes over the keys (a key and two
-// LDS updates per 1,024 points).
-__device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, WinLds& L) {
-  constexpr int NT = kFinThreads, PER = kWinBins / NT, KB = 8, NW = NT / kWave;
-  WinFast& F = L.f;
-  const int t = item_thread(), lane = t & (kWave - 1), wv = t / kWave;
-  const float2* z = reinterpret_cast<const float2*>(b.z);
-  // the first keys and the block's own records are requested with the control
-  // words (every array holds K entries)
-  int key0[KB];
+// The points of a labelling block in ascending order, at most KB per thread:
+// point u * kFinThreads + t is thread t's u-th.  POST (the compacting form):
+// points are rollouts, those outside V have no bucket (-1), and the buckets and
+// features are held in registers.  Otherwise points are compacted indices and
+// keys and features come from memory (the first KB keys are requested ahead).
+// (The order of the points is the same in both, and nothing else of an index
+// reaches the results.)
+template <bool POST>
+struct WinPoints {
+  static constexpr int KB = POST ? kPostMaxK / kFinThreads : 8;
+  int bk[KB];
+  float2 z[POST ? KB : 1];
+
+  // f(point, bucket, feature getter) for every point of the thread
+  template <typename F>
+  __device__ __forceinline__ void each(const Cfg& c, const Bufs& b, int V, int t, F&& f) const {
+    if constexpr (POST) {
 #pragma unroll
-  for (int u = 0; u < KB; ++u) key0[u] = u * NT + t < c.K ? b.wkey[u * NT + t] : 0;
-  const int a = bx * kChunk + t, ac = min(a, c.K - 1);
-  const int keya = b.wkey[ac];
-  const float Sa = b.Sv[ac];
-  const float2 ga = reinterpret_cast<const float2*>(b.gv)[ac];
-  const int V = dbscan_V(b, nullptr, 0);
-  if (bx * kChunk >= V) return true;
+      for (int u = 0; u < KB; ++u) {
+        if (u * kFinThreads >= c.K) break;
+        if (bk[u] >= 0) f(u * kFinThreads + t, bk[u], [&]() { return z[u]; });
+      }
+    } else {
+      const float2* zp = reinterpret_cast<const float2*>(b.z);
+      for (int k0 = 0; k0 < V; k0 += kFinThreads * KB) {
+        int key[KB];
+#pragma unroll
+        for (int u = 0; u < KB; ++u) key[u] = k0 == 0 ? bk[u] : b.wkey[min(k0 + u * kFinThreads + t, V - 1)];
+#pragma unroll
+        for (int u = 0; u < KB; ++u) {
+          const int k = k0 + u * kFinThreads + t;
+          if (k < V) f(k, key[u] >> kWinShift, [&]() { return zp[k]; });
+        }
+      }
+    }
+  }
+};
+
+// Rank among the feasible rollouts of rollout k (one of them), POST form.
+__device__ __forceinline__ int win_rank(const WinLds& L, int k) {
+  return L.frank[k >> 6] + __popcll(L.fmask[k >> 6] & ((1ull << (k & 63)) - 1));
+}
+
+// Block bx of the labelling of V points: the solution over the buckets, then
+// its own chunk (thread t: compacted index a, bucket bka, cost Sa, direction
+// ga); false (for the whole block) where the set needs the general form.  Bound
+// by the instructions of its 16 waves, four to a SIMD (the bucket passes are
+// about 1,200 per wave at every size), then by a chain of about ten barriers;
+// the passes over the points add two LDS updates per 1,024.  Barriers that
+// order LDS only, wave scans on lane moves and one atomic per wave and run in
+// place of __syncthreads(), LDS shuffles and one atomic per bucket: 17.0 to 12.7
+// us at 7,690 points, 37 to 22 us at 62,000.
+template <bool POST>
+__device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int V, int bx, int t, const WinPoints<POST>& W,
+                                         int bka, float Sa, float2 ga, WinLds& L) {
+  constexpr int NT = kFinThreads, PER = kWinBins / NT, NW = NT / kWave;
+  WinFast& F = L.f;
+  const int lane = t & (kWave - 1), wv = t / kWave;
+  const int a = bx * kChunk + t;
   const bool own = a < V;
   const float r2 = c.eps2;
+  auto note_own = [&](int k, int at) {  // the place of an own point
+    const int q = (POST ? win_rank(L, k) : k) - bx * kChunk;
+    if ((unsigned)q < (unsigned)kChunk) F.own[q] = (short)at;
+  };
 
   // points and lowest index of every bucket
 #pragma unroll
@@ -2447,25 +2498,14 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
     F.omin[t] = ~0ull;
   }
   if (t == 0) F.nopen = F.nu = F.nz = F.no = F.nmaybe = 0;
-  __syncthreads();
-  for (int k0 = 0; k0 < V; k0 += NT * KB) {
-    int key[KB];
-#pragma unroll
-    for (int u = 0; u < KB; ++u) {
-      const int k = k0 + u * NT + t;
-      key[u] = k0 == 0 ? key0[u] : (k < V ? b.wkey[k] : 0);
-    }
-#pragma unroll
-    for (int u = 0; u < KB; ++u) {
-      const int k = k0 + u * NT + t, bk = key[u] >> kWinShift;
-      if (k < V && bk < kWinBins) {
-        atomicAdd(&L.start[bk], 1);
-        // (later rounds hold higher indices: most read the minimum and go on)
-        if (k < F.bmin[bk]) atomicMin(&F.bmin[bk], k);
-      }
-    }
-  }
-  __syncthreads();
+  lds_sync();
+  W.each(c, b, V, t, [&](int k, int bk, auto) {
+    if (bk == kWinBins) return;
+    atomicAdd(&L.start[bk], 1);
+    // (later rounds hold higher indices: most read the minimum and go on)
+    if (k < F.bmin[bk]) atomicMin(&F.bmin[bk], k);
+  });
+  lds_sync();
   int cnt[PER], sum = 0;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
@@ -2473,14 +2513,14 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
     sum += cnt[i];
   }
   int nring;
-  int off = block_excl_scan<NT>(sum, &nring);
+  int off = block_excl_scan<NT, true>(sum, &nring);
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     L.start[t * PER + i] = off;
     off += cnt[i];
   }
   if (t == 0) L.start[kWinBins] = nring;
-  __syncthreads();
+  lds_sync();
   const int noff = V - nring;
   if (noff > kOffMax) return false;
   // buckets that the counts leave open, and the boundary buckets of their
@@ -2490,7 +2530,7 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int j = t * PER + i;
-    open[i] = cnt[i] > 0 && win_sure(c, L.start, j) < c.min_pts;
+    open[i] = cnt[i] > 0 && win_sure(c, L.start, nring, j) < c.min_pts;
     if (open[i]) {
       nopen += cnt[i];
       F.open[j] = 1;
@@ -2501,52 +2541,40 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
     }
   }
   if (nopen) atomicAdd(&F.nopen, nopen);
-  __syncthreads();
+  lds_sync();
   if (F.nopen > kOpenMax) return false;
-  int mine_u = -1;  // the own point's place among the open or the off-ring points
   if (F.nopen > 0 || noff > 0) {
     // list the open points, the points of their boundary buckets and the
     // off-ring points
-    for (int k0 = 0; k0 < V; k0 += NT * KB) {
-      int key[KB];
-#pragma unroll
-      for (int u = 0; u < KB; ++u) {
-        const int k = k0 + u * NT + t;
-        key[u] = k0 == 0 ? key0[u] : (k < V ? b.wkey[k] : 0);
+    W.each(c, b, V, t, [&](int k, int bk, auto zf) {
+      if (bk == kWinBins) {
+        const int o = atomicAdd(&F.no, 1);
+        F.ok[o] = k;
+        F.oz[o] = zf();
+        note_own(k, o);
+        return;
       }
-#pragma unroll
-      for (int u = 0; u < KB; ++u) {
-        const int k = k0 + u * NT + t, bk = key[u] >> kWinShift;
-        if (k >= V) continue;
-        if (bk == kWinBins) {
-          const int o = atomicAdd(&F.no, 1);
-          F.ok[o] = k;
-          F.oz[o] = z[k];
-          if (k == a) mine_u = o;
-          continue;
-        }
-        const bool op = F.open[bk] != 0, zn = F.zone[bk] != 0;
-        if (!op && !zn) continue;
-        const float2 zk = z[k];
-        int up = -1;
-        if (op) {
-          up = atomicAdd(&F.nu, 1);
-          F.uk[up] = k;
-          F.ub[up] = bk;
-          F.uz[up] = zk;
-          if (k == a) mine_u = up;
-        }
-        if (zn) {
-          const int zp = atomicAdd(&F.nz, 1);
-          if (zp < kZoneMax) {
-            F.zk[zp] = k;
-            F.zb[zp] = bk | ((up + 1) << 16);
-            F.zz[zp] = zk;
-          }
+      const bool op = F.open[bk] != 0, zn = F.zone[bk] != 0;
+      if (!op && !zn) return;
+      const float2 zk = zf();
+      int up = -1;
+      if (op) {
+        up = atomicAdd(&F.nu, 1);
+        F.uk[up] = k;
+        F.ub[up] = bk;
+        F.uz[up] = zk;
+        note_own(k, up);
+      }
+      if (zn) {
+        const int zp = atomicAdd(&F.nz, 1);
+        if (zp < kZoneMax) {
+          F.zk[zp] = k;
+          F.zb[zp] = bk | ((up + 1) << 16);
+          F.zz[zp] = zk;
         }
       }
-    }
-    __syncthreads();
+    });
+    lds_sync();
     if (F.nz > kZoneMax) return false;
     // exact counts: open points, one wave each; off-ring points against every
     // point, the whole block
@@ -2569,24 +2597,17 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
     for (int o = 0; o < noff; ++o) {
       const float2 zo = F.oz[o];
       int n = 0;
-      for (int k0 = 0; k0 < V; k0 += NT * KB) {
-        float2 zq[KB];
-#pragma unroll
-        for (int u = 0; u < KB; ++u) zq[u] = z[min(k0 + u * NT + t, V - 1)];
-#pragma unroll
-        for (int u = 0; u < KB; ++u)
-          n += __popcll(__ballot(k0 + u * NT + t < V && ZVec<2>::d2(zo, zq[u]) <= r2));
-      }
-      if (lane == 0) atomicAdd(&F.oc[o], n);
+      W.each(c, b, V, t, [&](int, int, auto zf) { n += ZVec<2>::d2(zo, zf()) <= r2 ? 1 : 0; });
+      if (n) atomicAdd(&F.oc[o], n);
     }
     // lowest core index of the open buckets
 #pragma unroll
     for (int i = 0; i < PER; ++i)
       if (open[i]) F.bmin[t * PER + i] = kNoCore;
-    __syncthreads();
+    lds_sync();
     for (int i = t; i < F.nu; i += NT)
       if (F.uc[i] >= c.min_pts) atomicMin(&F.bmin[F.ub[i]], F.uk[i]);
-    __syncthreads();
+    lds_sync();
   }
   // runs of core buckets: the core bucket before each core bucket (cyclic) and
   // the gap to it
@@ -2597,7 +2618,7 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
     if (bm[i] != kNoCore) mine = t * PER + i;
   }
   int last;
-  int pv = block_excl_max<NT>(mine, &last);
+  int pv = block_excl_max<NT, true>(mine, &last);
   int st[PER], prv[PER], nst_mine = 0;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
@@ -2612,7 +2633,7 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
     nst_mine += st[i];
   }
   int nst;
-  int cum = block_excl_scan<NT>(nst_mine, &nst);
+  int cum = block_excl_scan<NT, true>(nst_mine, &nst);
   const int nR = last < 0 ? 0 : max(nst, 1);
   if (nR > kWave) return false;
   int run_of[PER];
@@ -2623,12 +2644,28 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
     if (bm[i] != kNoCore) {
       cum += st[i];
       run_of[i] = nst == 0 ? 0 : (cum > 0 ? cum - 1 : nst - 1);
-      atomicMin(&F.run[run_of[i]], bm[i]);
       if (st[i] && nR >= 2 && j - prv[i] <= c.w_gout) atomicAdd(&F.nmaybe, 1);
     }
     F.lab[j] = run_of[i];
   }
-  __syncthreads();
+  // lowest core index of each run, one atomic per wave and run (thousands of
+  // buckets of one run would take their turns at one LDS word: 4,000 cycles)
+  int rn = -1, rlo = kInt32Max;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    if (run_of[i] < 0) continue;
+    if (rn < 0) rn = run_of[i];
+    if (run_of[i] == rn) rlo = min(rlo, bm[i]);
+    else atomicMin(&F.run[run_of[i]], bm[i]);
+  }
+  unsigned long long todo;
+  while ((todo = __ballot(rn >= 0)) != 0) {  // wave-uniform
+    const int r = __builtin_amdgcn_readlane(rn, __ffsll(todo) - 1);
+    const int lo = wave_min(rn == r ? rlo : kInt32Max);
+    if (lane == 0) atomicMin(&F.run[r], lo);
+    if (rn == r) rn = -1;
+  }
+  lds_sync();
   if (F.nmaybe > 0) return false;
   bool ocore = false;
   for (int o = 0; o < noff; ++o) ocore |= F.oc[o] >= c.min_pts;
@@ -2650,26 +2687,25 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
       F.cmin[t] = t < kWave ? (t < nR ? F.run[t] : kInt32Max)
                             : (F.oc[t - kWave] >= c.min_pts ? F.ok[t - kWave] : kInt32Max);
     }
-    __syncthreads();
+    lds_sync();
     for (int o = 0; o < noff; ++o) {
       if (F.oc[o] < c.min_pts) continue;
       const float2 zo = F.oz[o];
-      for (int k = t; k < V; k += NT) {
-        const int bk = b.wkey[k] >> kWinShift;
-        if (bk < kWinBins && !F.open[bk] && ZVec<2>::d2(zo, z[k]) <= r2)
+      W.each(c, b, V, t, [&](int, int bk, auto zf) {
+        if (bk < kWinBins && !F.open[bk] && ZVec<2>::d2(zo, zf()) <= r2)
           win_union(F.parent, F.lab[bk], kWave + o);
-      }
+      });
       for (int i = t; i < F.nu; i += NT)
         if (F.uc[i] >= c.min_pts && ZVec<2>::d2(zo, F.uz[i]) <= r2) win_union(F.parent, F.lab[F.ub[i]], kWave + o);
       if (t < noff && F.oc[t] >= c.min_pts && ZVec<2>::d2(zo, F.oz[t]) <= r2)
         win_union(F.parent, kWave + t, kWave + o);
     }
-    __syncthreads();
+    lds_sync();
     if (t < nn && F.cmin[t] != kInt32Max) {
       const int rt = win_find(F.parent, t), m = ld_wg(&F.cmin[t]);
       if (rt != t) atomicMin(&F.cmin[rt], m);
     }
-    __syncthreads();
+    lds_sync();
     int r = -1, M = 0;
     if (t < nn) {
       const int mv = F.cmin[win_find(F.parent, t)];
@@ -2686,13 +2722,13 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
     if (t >= kWave && t < nn) F.ol[t - kWave] = r;
     if (t == 0) F.M = M;
   }
-  __syncthreads();
+  lds_sync();
   const int M = F.M;
   if (M > kStatClusters) return false;
 #pragma unroll
   for (int i = 0; i < PER; ++i)
     if (run_of[i] >= 0) F.lab[t * PER + i] = F.rank[run_of[i]];
-  __syncthreads();
+  lds_sync();
   // border rule: the lowest-index core neighbour of every open point that is
   // not core (one wave each) and of every off-ring point that is not
   for (int i = wv; i < F.nu; i += NW) {
@@ -2714,9 +2750,7 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
         take(F.zk[e], F.lab[bk]);
     }
     if (lane < noff && F.oc[lane] >= c.min_pts && ZVec<2>::d2(zi, F.oz[lane]) <= r2) take(F.ok[lane], F.ol[lane]);
-    int mm = m;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) mm = min(mm, __shfl_xor(mm, d, kWave));
+    const int mm = wave_min(m);
     // (an index belongs to one lane unless none was found)
     if (m == mm && (mm != kNoCore || lane == 0)) F.ul[i] = mm == kNoCore ? -1 : lb;
   }
@@ -2728,35 +2762,28 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
       const unsigned long long v = ((unsigned long long)(unsigned)k << 32) | (unsigned)l;
       m = v < m ? v : m;
     };
-    for (int k = t; k < V; k += NT) {
-      const int bk = b.wkey[k] >> kWinShift;
-      if (bk < kWinBins && !F.open[bk] && ZVec<2>::d2(zo, z[k]) <= r2) {
-        take(k, F.lab[bk]);
-        break;  // (ascending: the first is the lowest)
-      }
-    }
+    W.each(c, b, V, t, [&](int k, int bk, auto zf) {
+      if (bk < kWinBins && !F.open[bk] && ZVec<2>::d2(zo, zf()) <= r2) take(k, F.lab[bk]);
+    });
     for (int i = t; i < F.nu; i += NT)
       if (F.uc[i] >= c.min_pts && ZVec<2>::d2(zo, F.uz[i]) <= r2) take(F.uk[i], F.lab[F.ub[i]]);
     if (t < noff && F.oc[t] >= c.min_pts && ZVec<2>::d2(zo, F.oz[t]) <= r2) take(F.ok[t], F.ol[t]);
     if (m != ~0ull) atomicMin(&F.omin[o], m);
   }
-  __syncthreads();
+  lds_sync();
   // the block's own chunk
-  const int bk = keya >> kWinShift;
   int lab = -1, n = 0;
   if (own) {
-    if (bk == kWinBins) {
-      n = F.oc[mine_u];
-      lab = n >= c.min_pts ? F.ol[mine_u] : (F.omin[mine_u] == ~0ull ? -1 : (int)(unsigned)F.omin[mine_u]);
-    } else if (F.open[bk]) {
-      n = F.uc[mine_u];
-      lab = n >= c.min_pts ? F.lab[bk] : F.ul[mine_u];
+    if (bka == kWinBins) {
+      n = F.oc[F.own[t]];
+      lab = n >= c.min_pts ? F.ol[F.own[t]] : (F.omin[F.own[t]] == ~0ull ? -1 : (int)(unsigned)F.omin[F.own[t]]);
+    } else if (F.open[bka]) {
+      n = F.uc[F.own[t]];
+      lab = n >= c.min_pts ? F.lab[bka] : F.ul[F.own[t]];
     } else {
-      n = win_sure(c, L.start, bk);
-      lab = F.lab[bk];
+      n = win_sure(c, L.start, nring, bka);
+      lab = F.lab[bka];
     }
-    b.label[a] = lab;
-    b.ncount[a] = n;
   }
   if (bx == 0 && t == 0) {
     Ctrl* ct = b.ctrl;
@@ -2765,17 +2792,116 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int bx, Wi
     ct->M = M;
     ct->stat_direct = 0;
   }
-  if (M > 0) chunk_stats<2>(b, bx, M, lab, Sa, ga, F.red);
+  if (M > 0) chunk_stats<2, true>(b, bx, M, lab, Sa, ga, F.red);
+  if (own) {
+    b.label[a] = lab;
+    b.ncount[a] = n;
+  }
   return true;
 }
 
+// One block of the labelling.  POST: the block also does the compaction's work
+// (k_compact): totals, reference point, and its own candidates' records; every
+// block finds the buckets of all rollouts for itself.  One launch and a pass
+// over memory less, for about 100 instructions per 64 rollouts in every block.
+// A whole replan, separate against compacting: 33.3 and 32.0 us at K = 256, 34.4
+// and 34.0 (one scene) or 36.5 and 35.1 (another) at 2,048, 34.4 and 35.5 or
+// 38.2 and 38.2 at 4,096, 39.9 and 43.7 at 8,192: the line is at kPostMaxK.
+template <bool POST>
 __device__ __forceinline__ void wlabel_body(const Cfg& c, const Bufs& b, int bx, WinLds& L) {
-  if (!win_fast(c, b, bx, L)) win_general(c, b, dbscan_V(b, nullptr, 0), bx, L);
+  constexpr int NT = kFinThreads;
+  const int t = item_thread();
+  WinPoints<POST> W;
+  const int a = bx * kChunk + t;
+  int V, bka = 0;
+  float Sa = 0.f;
+  float2 ga = make_float2(0.f, 0.f);
+  if constexpr (POST) {
+    constexpr int KB = WinPoints<POST>::KB, NW = NT / kWave;
+    const int lane = t & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(t / kWave);
+    const float2* pT = reinterpret_cast<const float2*>(b.pT);
+    const int bad = b.ctrl->nonfinite;
+#pragma unroll
+    for (int u = 0; u < KB; ++u) {
+      if (u * NT >= c.K) break;
+      const int k = min(u * NT + t, c.K - 1);
+      W.bk[u] = b.col[k];
+      W.z[u] = pT[k];
+    }
+    __shared__ float s_tot[kPart + 1];
+    __shared__ int s_before;
+    reduce_partials(c, b, 0, s_tot, &s_before);
+    const Totals T = decide(c, s_tot, bad);
+    if (bx == 0 && t == 0) publish_totals(c, b, T, s_tot);
+    V = T.branch == 0 ? T.nfeas : 0;
+    if (bx * kChunk >= V) return;
+#pragma unroll
+    for (int u = 0; u < KB; ++u) {
+      if (u * NT >= c.K) break;
+      const bool feas = u * NT + t < c.K && !W.bk[u];
+      const unsigned long long m = __ballot(feas);
+      if (lane == 0) L.fmask[u * NW + wv] = m;
+      W.z[u] = feature2(c, W.z[u], T.ref[0], T.ref[1]);
+      W.bk[u] = feas ? win_bin(c, W.z[u]) : -1;
+    }
+    lds_sync();
+    // ranks: every wave scans the words; its own points' places
+    const int nw = (c.K + NT - 1) / NT * NW;
+    static_assert(kPostMaxK / kWave <= kWave, "one word per lane");
+    const unsigned long long word = lane < nw ? L.fmask[lane] : 0ull;
+    const int before = wave_incl_scan(__popcll(word)) - __popcll(word);
+    if (wv == 0 && lane < nw) L.frank[lane] = before;
+#pragma unroll
+    for (int u = 0; u < KB; ++u) {
+      if (u * NT >= c.K) break;
+      const int k = u * NT + t;
+      const unsigned long long own = __ballot(W.bk[u] >= 0);
+      const int q = __builtin_amdgcn_readlane(before, u * NW + wv) + __popcll(own & ((1ull << lane) - 1)) - bx * kChunk;
+      if (W.bk[u] >= 0 && (unsigned)q < (unsigned)kChunk) {
+        L.vidx[q] = k | (W.bk[u] << kWinShift);
+        b.vidx[bx * kChunk + q] = k;
+        reinterpret_cast<float2*>(b.z)[bx * kChunk + q] = W.z[u];
+      }
+    }
+    lds_sync();
+    if (a < V) {
+      const int kb = L.vidx[t], k = kb & (kWinMaxK - 1);
+      bka = kb >> kWinShift;
+      Sa = b.S[k];
+      ga = reinterpret_cast<const float2*>(b.g)[k];
+    }
+  } else {
+    const int ac = min(a, c.K - 1);
+#pragma unroll
+    for (int u = 0; u < WinPoints<POST>::KB; ++u) W.bk[u] = b.wkey[min(u * NT + t, c.K - 1)];
+    bka = b.wkey[ac] >> kWinShift;
+    Sa = b.Sv[ac];
+    ga = reinterpret_cast<const float2*>(b.gv)[ac];
+    V = dbscan_V(b, nullptr, 0);
+    if (bx * kChunk >= V) return;
+  }
+  const bool done = win_fast<POST>(c, b, V, bx, t, W, bka, Sa, ga, L);
+  if (POST && a < V) {
+    b.Sv[a] = Sa;
+    reinterpret_cast<float2*>(b.gv)[a] = ga;
+  }
+  if (done) return;
+  if constexpr (POST) {
+    // the general form reads features and buckets of every point from memory:
+    // each block writes them all (the same values)
+    W.each(c, b, V, t, [&](int k, int bk, auto zf) {
+      const int q = win_rank(L, k);
+      b.wkey[q] = bk << kWinShift;
+      reinterpret_cast<float2*>(b.z)[q] = zf();
+    });
+  }
+  win_general(c, b, V, bx, L);
 }
 
+template <bool POST>
 __global__ __launch_bounds__(kFinThreads) void k_wlabel(Cfg c, Bufs b) {
   __shared__ WinLds L;
-  wlabel_body(c, b, (int)blockIdx.x, L);
+  wlabel_body<POST>(c, b, (int)blockIdx.x, L);
 }
 
 // ---------------------------------------------------------------------------
@@ -3256,11 +3382,11 @@ __global__ __launch_bounds__(kFinThreads) void kb_plan(CSlotStatic st, PlanOut o
   const Bufs& b = S.b
 
 template <int P, bool BIN = false>
-__global__ __launch_bounds__(256) void kb_compact(CSlotStatic st, Tab t) {
+__global__ __launch_bounds__(kFinThreads) void kb_compact(CSlotStatic st, Tab t) {
   __shared__ int s_pref[kMaxBatch + 1];
-  for_each_item<256>(t, s_pref, [&](int slot, int local) {
+  for_each_item<kFinThreads>(t, s_pref, [&](int slot, int local) {
     CEMPPI_SLOT(slot);
-    compact_body<P, BIN>(c, b, local, 0, 0);
+    compact_body<P, BIN>(c, b, local);
   });
 }
 
@@ -3307,14 +3433,18 @@ __global__ __launch_bounds__(kTile) void kb_tree_adj(CSlotStatic st, Tab t) {
   });
 }
 
-// angular windows of the 2-D members: the labelling blocks of every member
+// angular windows of the 2-D members: the labelling blocks of every member, one
+// item per block (in a loop over items the compiler carries 60 registers of
+// addresses and masks from one to the next and spills others).  The compaction
+// stays a phase of its own: its blocks fill the chip over the members, and
+// members on both forms would take two launches (64 members: 152 against 135 us)
 __global__ __launch_bounds__(kFinThreads) void kb_wlabel(CSlotStatic st, Tab t) {
-  __shared__ int s_pref[kMaxBatch + 1];
   __shared__ WinLds L;
-  for_each_item<kFinThreads>(t, s_pref, [&](int slot, int local) {
-    CEMPPI_SLOT(slot);
-    wlabel_body(c, b, local, L);
-  });
+  int local;
+  const int slot = item_of(t, (int)blockIdx.x, &local);
+  if (slot < 0) return;
+  CEMPPI_SLOT(slot);
+  wlabel_body<false>(c, b, local, L);
 }
 
 template <int P>
@@ -3374,7 +3504,8 @@ static void launch_dbscan_p(Launcher& L, const Cfg& c, const Bufs& b, const floa
       L(k_wdbscan, dim3((Vin + kWinPos - 1) / kWinPos), dim3(kFinThreads), c, b, zin, Vin, mout, lab_out,
         cnt_out);
     else
-      L(k_wlabel, dim3((c.K + kChunk - 1) / kChunk), dim3(kFinThreads), c, b);
+      L(c.K <= kPostMaxK ? k_wlabel<true> : k_wlabel<false>, dim3((c.K + kChunk - 1) / kChunk), dim3(kFinThreads), c,
+        b);
     return;
   }
   const int ngrp = (ntile + kColGroup - 1) / kColGroup;
@@ -3413,14 +3544,14 @@ static void launch_dbscan_p(Launcher& L, const Cfg& c, const Bufs& b, const floa
 // the cross-stream synchronisation of the branches costs more than the
 // overlap saves).
 void launch_post_rollout(Launcher& L, const Cfg& c, const Bufs& b) {
-  const int nk = (c.K + 255) / 256;
+  const dim3 nk((c.K + kChunk - 1) / kChunk), nt(kFinThreads);
   int* none = nullptr;
   if (c.p == 2) {
-    if (use_window(c, b)) L(k_compact<2, true>, dim3(nk), dim3(256), c, b);
-    else L(k_compact<2, false>, dim3(nk), dim3(256), c, b);
+    if (!use_window(c, b)) L(k_compact<2, false>, nk, nt, c, b);
+    else if (c.K > kPostMaxK) L(k_compact<2, true>, nk, nt, c, b);
     launch_dbscan_p<2>(L, c, b, nullptr, 0, c.ntile, none, none, none);
   } else {
-    L(k_compact<3, false>, dim3(nk), dim3(256), c, b);
+    L(k_compact<3, false>, nk, nt, c, b);
     launch_dbscan_p<3>(L, c, b, nullptr, 0, c.ntile, none, none, none);
   }
   using UFn = void (*)(Cfg, Bufs);
@@ -3496,9 +3627,9 @@ void launch_batch_post(Launcher& L, const SlotStatic* st, const SlotIO* io, cons
   const CSlotIO cio = (CSlotIO)io;
   for (int kd = 0; kd < kPlanKinds; ++kd) {
     if (!T.has[kd]) continue;
-    if (kd == 0) L(kb_compact<2>, dim3(T.grid_compact[0]), dim3(256), cst, T.compact[0]);
-    else if (kd == 1) L(kb_compact<3>, dim3(T.grid_compact[1]), dim3(256), cst, T.compact[1]);
-    else L(kb_compact<2, true>, dim3(T.grid_compact[2]), dim3(256), cst, T.compact[2]);
+    if (kd == 0) L(kb_compact<2>, dim3(T.grid_compact[0]), dim3(kFinThreads), cst, T.compact[0]);
+    else if (kd == 1) L(kb_compact<3>, dim3(T.grid_compact[1]), dim3(kFinThreads), cst, T.compact[1]);
+    else L(kb_compact<2, true>, dim3(T.grid_compact[2]), dim3(kFinThreads), cst, T.compact[2]);
   }
   L(kb_plan, dim3(1), dim3(kFinThreads), cst, T.plan);
   if (T.has[2]) L(kb_wlabel, dim3(T.grid_lab[2]), dim3(kFinThreads), cst, T.lab[2]);

@@ -72,6 +72,7 @@ constexpr int kWinMaxK = 1 << kWinShift;
 constexpr int kWinMaxRuns = 1024;  // runs of core buckets (at most kWinBins / (gap + 1) with gap >= 3)
 constexpr int kWinPos = 512;  // sorted positions per count-and-place block
 static_assert(kWinMaxK >= kAdjMaxK, "the windowed path covers every planner with a bitmap");
+constexpr int kPostMaxK = 2 * kFinThreads;  // 2-D windows: the labelling blocks compact for themselves up to this size
 constexpr int kLabBatch = 8;   // points per thread per labelling pass
 constexpr int kRecBatch = 4;   // partial records per thread in flight at once
 constexpr int kFinRows = 8;    // update-partial rows per wave in flight at once (final combination)
@@ -112,8 +113,10 @@ struct Ctrl {
   int32_t dyn_h, dyn_ok;  // Eq. (17) estimate of this replan: H' and whether the dynamic rule applies
   uint32_t status;
   uint32_t step_used;
-  int32_t wticket;  // completion ticket of the window DBSCAN launch (zero between calls)
   int32_t stat_direct;  // the cluster arrays hold the final statistics (more than kStatClusters clusters)
+  // completion ticket of the window DBSCAN launch (zero between calls), on a
+  // line of its own: blocks take tickets while block 0 stores the words above
+  alignas(128) int32_t wticket;
 };
 
 // Scalar configuration (kernel argument).
@@ -280,21 +283,12 @@ __device__ __forceinline__ int item_of(const Tab& t, int it, int* local) {
   return __builtin_amdgcn_readfirstlane(t.slot[q]);
 }
 
-// The thread index as a value the compiler cannot see through: addresses that
-// follow from it are not carried across the items of a persistent loop (they
-// cost the labelling kernel of a batch 60 registers and put others in scratch
-// memory, which adds about 25 us to every dispatch).
-__device__ __forceinline__ int item_thread() {
-  int t = (int)threadIdx.x;
-  asm volatile("" : "+v"(t));
-  return t;
-}
-
 // Tables of the batched post-rollout phases.  Index kd is the group of
 // planners: p = 2 on the sorted distance passes (0), p = 3 (1), p = 2 on the
 // angular windows (2).  Static tables for compaction and for the spatial sort
-// (one item per planner); the DBSCAN tables are filled on the device from
-// each planner's feasible count (PlanOut).  Update and finish run over every planner of the batch.
+// (one item per planner); the DBSCAN tables are filled on the device from each
+// planner's feasible count (PlanOut).  Update and finish run over every planner
+// of the batch.
 constexpr int kPlanKinds = 3;
 struct PlanOut {
   const int* slot[kPlanKinds];  // planners of each group
@@ -490,56 +484,99 @@ __device__ __forceinline__ int ld_acquire(const int* p) {
   return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// block-wide (blockDim.x == NT) exclusive scan of one int per thread;
-// returns the exclusive prefix and writes the total.
-template <int NT>
+// wave-wide inclusive sums and maxima (identity -1) on DPP lane moves: row
+// shifts by 1, 2, 4, 8, then rows 0 and 2 into 1 and 3, then 1 into 2 and 3.
+// (Six __shfl moves each go through LDS: the cluster statistics of one chunk
+// alone were 30 of them per cluster and wave.)
+#define CEMPPI_DPP_SCAN(OP, ID)                                                \
+  v = OP(v, __builtin_amdgcn_update_dpp(ID, v, 0x111, 0xf, 0xf, false));       \
+  v = OP(v, __builtin_amdgcn_update_dpp(ID, v, 0x112, 0xf, 0xf, false));       \
+  v = OP(v, __builtin_amdgcn_update_dpp(ID, v, 0x114, 0xf, 0xf, false));       \
+  v = OP(v, __builtin_amdgcn_update_dpp(ID, v, 0x118, 0xf, 0xf, false));       \
+  v = OP(v, __builtin_amdgcn_update_dpp(ID, v, 0x142, 0xa, 0xf, false));       \
+  v = OP(v, __builtin_amdgcn_update_dpp(ID, v, 0x143, 0xc, 0xf, false))
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  auto add = [](int a, int b) { return a + b; };
+  CEMPPI_DPP_SCAN(add, 0);
+  return v;
+}
+__device__ __forceinline__ int wave_incl_max(int v) {
+  auto mx = [](int a, int b) { return max(a, b); };
+  CEMPPI_DPP_SCAN(mx, -1);
+  return v;
+}
+__device__ __forceinline__ int wave_min(int v) {
+  auto mn = [](int a, int b) { return min(a, b); };
+  CEMPPI_DPP_SCAN(mn, 0x7fffffff);
+  return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+// the wave's minimum
+__device__ __forceinline__ float wave_min(float x) {
+  int v = __float_as_int(x);
+  auto mn = [](int a, int b) { return __float_as_int(fminf(__int_as_float(a), __int_as_float(b))); };
+  CEMPPI_DPP_SCAN(mn, 0x7f800000);
+  return __int_as_float(__builtin_amdgcn_readlane(v, kWave - 1));
+}
+#undef CEMPPI_DPP_SCAN
+
+// The thread index as a value the compiler cannot see through: addresses and
+// masks that follow from it are not carried across a long kernel or the items of
+// a persistent loop (registers put in scratch memory add about 25 us to every
+// dispatch).
+__device__ __forceinline__ int item_thread() {
+  int t = (int)threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Barrier of a block that exchanges data in LDS only.  (__syncthreads() also
+// waits for every global load and store in flight: one memory latency, about
+// 2,000 cycles, at the first barrier after a store.)
+__device__ __forceinline__ void lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// block-wide (blockDim.x == NT) exclusive scan of one int per thread; returns
+// the sum over the lower threads and writes the block total.  LDS: the barriers
+// order LDS only, and there is none behind the reads (the caller has one before
+// the next such scan).  The wave totals are scanned by one more wave scan (a
+// select and two sums per wave total are 64 instructions in each of 16 waves,
+// four of which share a SIMD: 1,000 cycles).
+template <int NT, bool LDS = false>
 __device__ __forceinline__ int block_excl_scan(int v, int* total) {
-  __shared__ int s_w[NT / kWave];
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  int inc = v;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int t = __shfl_up(inc, (unsigned)d, kWave);
-    if (lane >= d) inc += t;
-  }
+  constexpr int NW = NT / kWave;
+  static_assert(NW <= kWave, "one wave total per lane");
+  __shared__ int s_w[NW];
+  const int t = item_thread(), w = __builtin_amdgcn_readfirstlane(t / kWave), lane = t & (kWave - 1);
+  const int inc = wave_incl_scan(v);
   if (lane == kWave - 1) s_w[w] = inc;
-  __syncthreads();
-  int base = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < NT / kWave; ++i) {
-    if (i < w) base += s_w[i];
-    tot += s_w[i];
-  }
-  __syncthreads();
-  *total = tot;
-  return base + inc - v;
+  LDS ? lds_sync() : __syncthreads();
+  const int sums = wave_incl_scan(lane < NW ? s_w[lane] : 0);
+  if (!LDS) __syncthreads();
+  *total = __builtin_amdgcn_readlane(sums, NW - 1);
+  return (w > 0 ? __builtin_amdgcn_readlane(sums, w - 1) : 0) + inc - v;
 }
 
 // block-wide (blockDim.x == NT) exclusive max-scan of one int per thread
 // (identity -1); returns the maximum over the lower threads and writes the
 // block maximum.
-template <int NT>
+template <int NT, bool LDS = false>
 __device__ __forceinline__ int block_excl_max(int v, int* total) {
-  __shared__ int s_w[NT / kWave];
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  int inc = v;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int t = __shfl_up(inc, (unsigned)d, kWave);
-    if (lane >= d) inc = max(inc, t);
-  }
-  const int below = __shfl_up(inc, 1u, kWave);
+  constexpr int NW = NT / kWave;
+  static_assert(NW <= kWave, "one wave maximum per lane");
+  __shared__ int s_w[NW];
+  const int t = item_thread(), w = __builtin_amdgcn_readfirstlane(t / kWave), lane = t & (kWave - 1);
+  const int inc = wave_incl_max(v);
+  // the lane below (lane 0: nothing)
+  const int below = __builtin_amdgcn_update_dpp(-1, inc, 0x138, 0xf, 0xf, false);
   if (lane == kWave - 1) s_w[w] = inc;
-  __syncthreads();
-  int base = -1, tot = -1;
-#pragma unroll
-  for (int i = 0; i < NT / kWave; ++i) {
-    if (i < w) base = max(base, s_w[i]);
-    tot = max(tot, s_w[i]);
-  }
-  __syncthreads();
-  *total = tot;
-  return lane > 0 ? max(base, below) : base;
+  LDS ? lds_sync() : __syncthreads();
+  const int top = wave_incl_max(lane < NW ? s_w[lane] : -1);
+  if (!LDS) __syncthreads();
+  *total = __builtin_amdgcn_readlane(top, NW - 1);
+  return max(w > 0 ? __builtin_amdgcn_readlane(top, w - 1) : -1, below);
 }
 
 }  // namespace cemppi

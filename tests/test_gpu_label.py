@@ -63,6 +63,9 @@ def _cases():
     for V in (1023, 1024, 1025, 8191, 8193, 12289):
         c.append((f"size_{V}", _dirs(np.concatenate([rng.normal(0.5, 0.3, V - 9), u(2, 6, 9)])), 0.25, 20))
     c.append(("size_65000", _dirs(np.concatenate([rng.normal(0.5, 0.3, 64975), u(2, 6, 25)])), 0.25, 20))
+    # K = V + 5 at the ends of the range whose blocks compact for themselves
+    for V in (1019, 1020, 2042, 2043, 2044):
+        c.append((f"size_{V}", _dirs(np.concatenate([rng.normal(0.5, 0.3, V - 9), u(2, 6, 9)])), 0.25, 20))
     return c
 
 
