@@ -341,14 +341,16 @@ ce_status ce_mppi_dbscan_noalloc(int32_t device, const float* z, int32_t V, int3
 
 /* ---- launch mode and timing ---- */
 enum { CE_LAUNCH_GRAPH = 0, CE_LAUNCH_DIRECT = 1 };
-/* CE_LAUNCH_GRAPH (default): the first replan records the planner's kernel
+/* CE_LAUNCH_GRAPH: the first replan records the planner's kernel
  * chain into a hipGraph and every replan replays it (the first and last
  * kernels are re-pointed when the caller's buffers change).
  * CE_LAUNCH_DIRECT: every kernel of the replan is launched on the caller's
  * stream.  Both run the same kernels with the same arguments and give the
  * same bits.  Which is faster depends on the host: a replay costs the device
  * a few microseconds more than the same direct launches, while direct launches
- * cost the host a few microseconds each (see ce_mppi_tune_launch). */
+ * cost the host a few microseconds each (see ce_mppi_tune_launch).  A planner
+ * whose mode was not set launches the short chain of 2-D features on the
+ * angular windows directly and replays the others. */
 ce_status ce_mppi_set_launch_mode(ce_mppi_planner* planner, int32_t mode);
 /* For callers that replan back to back: run `reps` replans on (x_t,
  * obstacles) in each launch mode, timing host wall clock from the first call

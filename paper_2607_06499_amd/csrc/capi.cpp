@@ -572,6 +572,27 @@ void mark_stream(ce_mppi_planner* P, hipStream_t s) {
 }
 }  // namespace cemppi
 
+namespace {
+// Launch mode of a replan whose caller has not set one.  A chain of at most five
+// kernels (2-D features on the angular windows) goes out kernel by kernel: the
+// host submits it in 17-23 us against 28-32 us for a graph launch, and the device
+// runs it without the graph's own start (us a replan back to back, direct against
+// graph: 25.2 and 29.3 at K = 300, 23.6 and 30.2 on the fallback branch at 8,192,
+// 33.7 and 36.1 with clusters, 78 and 83.5 at 65,536).  The eight kernels of the
+// other chains cost the host as much either way (36-41 us, 37 and 36 us a replan
+// at K = 50) and are replayed.  So is every chain on a stream that is being
+// captured.
+bool replay_by_default(const ce_mppi_planner* P, hipStream_t s) {
+  if (!(P->c.p == 2 && P->c.dbpath == 0 && P->b.wcnt)) return true;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return cap != hipStreamCaptureStatusNone;
+}
+}  // namespace
+
 namespace cemppi {
 ce_status replan_unchecked(ce_mppi_planner* P, const float* x_t, const float* obstacles,
                                    int32_t n_obs, float* u_out, float* U_out, ce_mppi_info* info,
@@ -595,7 +616,7 @@ ce_status replan_unchecked(ce_mppi_planner* P, const float* x_t, const float* ob
     launch_finish(L, P->c, P->b, u_out, U_out, info);
     if (e == hipSuccess && L.err == hipSuccess) e = hipEventRecord(t.ev[3 * i + 2], s);
     if (e == hipSuccess) e = L.err;
-  } else if (P->launch_mode == CE_LAUNCH_GRAPH) {
+  } else if (P->launch_mode == kLaunchAuto ? replay_by_default(P, s) : P->launch_mode == CE_LAUNCH_GRAPH) {
     e = replan_graph(P, x_t, obstacles, n_obs, u_out, U_out, info, s);
   } else {
     Launcher L(s);

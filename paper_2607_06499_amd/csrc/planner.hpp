@@ -37,6 +37,8 @@ struct Timing {
 
 }  // namespace cemppi
 
+constexpr int kLaunchAuto = -1;  // launch mode of a planner whose caller has not set one
+
 struct ce_mppi_planner {
   ce_mppi_config cfg;
   cemppi::Cfg c;
@@ -44,7 +46,7 @@ struct ce_mppi_planner {
   void* arena = nullptr;
   size_t arena_bytes = 0;
   size_t cap_K = 0;
-  int launch_mode = CE_LAUNCH_GRAPH;
+  int launch_mode = kLaunchAuto;  // or the caller's CE_LAUNCH_GRAPH or CE_LAUNCH_DIRECT
   cemppi::ReplanGraph g;
   cemppi::Timing t;
   // stream of the last replan (or batch replan) of this planner
