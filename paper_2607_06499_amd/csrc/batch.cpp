@@ -41,7 +41,7 @@ struct Layout {
   size_t roll_slot[kRollKinds], roll_pref[kRollKinds][4];
   size_t p_slot[kPlanKinds], compact[kPlanKinds], one[kPlanKinds], dyn_cnt[kPlanKinds], dyn_adj[kPlanKinds],
       dyn_lab[kPlanKinds];
-  size_t all_slot, update, finish;
+  size_t all_slot, update;
   size_t ints = 0;
   void make(int n) {
     size_t o = 0;
@@ -67,7 +67,6 @@ struct Layout {
     }
     all_slot = take(n);
     update = take(n + 1);
-    finish = take(n + 1);
     ints = o;
   }
 };
@@ -182,7 +181,6 @@ void fill_tables(const ce_mppi_batch* B, const int* members, int count, int* h) 
   std::copy(members, members + count, h + L.all_slot);
   std::vector<int> all(members, members + count);
   prefix(all, L.update, [](const ce_mppi_planner* P) { return P->c.nblk_upd; });
-  prefix(all, L.finish, [](const ce_mppi_planner*) { return 1; });
 }
 
 // Tables of an area as kernel arguments, with the grids of the tuning.
@@ -214,10 +212,8 @@ void area_tabs(const ce_mppi_batch* B, Area& a) {
     T.grid_lab[kd] = std::max(1, kd == 2 ? B->lab_total[kd] : std::min(B->lab_total[kd], cus));
   }
   T.update = Tab{d + L.all_slot, d + L.update, d + L.cnt_all};
-  T.finish = Tab{d + L.all_slot, d + L.finish, d + L.cnt_all};
   T.grid_tile = B->tune.tile_blocks_per_cu * cus;
-  T.grid_update = std::max(1, std::min(B->update_total, 4 * cus));
-  T.grid_finish = std::max(1, std::min(B->n, cus));
+  T.grid_update = std::max(1, B->update_total);
   T.colg = B->tune.colg;
   T.plan.colg = B->tune.colg;
 }

@@ -23,8 +23,7 @@ void launch_rollout(Launcher& L, const Cfg& c, const Bufs& b, const float* x_t, 
 void launch_reduce_records(Launcher& L, const Cfg& c, const Bufs& b, const float* x_t,
                            const float* obs, int n_obs);
 void launch_stage_noise(Launcher& L, const Cfg& c, uint32_t step, uint32_t* words, float* gauss);
-void launch_post_rollout(Launcher& L, const Cfg& c, const Bufs& b);
-void launch_finish(Launcher& L, const Cfg& c, const Bufs& b, float* u_out, float* U_out, void* info);
+void launch_post_rollout(Launcher& L, const Cfg& c, const Bufs& b, float* u_out, float* U_out, void* info);
 void launch_window_counts(Launcher& L, const Cfg& c, const Bufs& b);
 void launch_stage_dbscan(Launcher& L, const Cfg& c, const Bufs& b, const float* z, int V,
                          int* ncount, int* label, int* mout);
@@ -390,11 +389,8 @@ ce_status ce_mppi_create(const ce_mppi_config* cfg, ce_mppi_planner** out) {
   const size_t o_stat = cv.take<float>((K + kChunk - 1) / kChunk * kStatClusters * kStatFields);
   const size_t o_ccost = cv.take<float>((size_t)c.mcap), o_cdir = cv.take<float>((size_t)c.mcap * 4);
   const size_t o_csize = cv.take<int>((size_t)c.mcap), o_csmin = cv.take<float>((size_t)c.mcap);
-  // update partials, then rows that stay zero so the final combination can
-  // request whole batches of rows (kFinRows per wave) without bounds tests,
-  // and the chunks of the last row that reach past its end
-  const size_t o_upart = cv.take<float>((size_t)(c.nblk_upd + (kFinThreads / kWave) * kFinRows) * (NM + 1) +
-                                        (size_t)kFinChunks * kWave);
+  // update rows and the chunks of the last one that reach past its end
+  const size_t o_upart = cv.take<float>((size_t)c.nblk_upd * (NM + 1) + (size_t)kFinChunks * kWave);
   P->arena_bytes = cv.off;
   e = hipMalloc(&P->arena, P->arena_bytes);
   if (e != hipSuccess) {
@@ -484,8 +480,7 @@ hipError_t build_graph(ce_mppi_planner* P, const float* x_t, const float* obs, i
   if (e != hipSuccess) return e;
   Launcher L(nullptr, g.graph);
   launch_rollout(L, P->c, P->b, x_t, obs, n_obs);
-  launch_post_rollout(L, P->c, P->b);
-  launch_finish(L, P->c, P->b, u_out, U_out, info);
+  launch_post_rollout(L, P->c, P->b, u_out, U_out, info);
   if (L.err != hipSuccess) return L.err;
   g.first = L.nodes.front();
   g.last = L.nodes.back();
@@ -573,12 +568,12 @@ void mark_stream(ce_mppi_planner* P, hipStream_t s) {
 }  // namespace cemppi
 
 namespace {
-// Launch mode of a replan whose caller has not set one.  A chain of at most five
+// Launch mode of a replan whose caller has not set one.  A chain of at most four
 // kernels (2-D features on the angular windows) goes out kernel by kernel: the
 // host submits it in 17-23 us against 28-32 us for a graph launch, and the device
 // runs it without the graph's own start (us a replan back to back, direct against
-// graph: 25.2 and 29.3 at K = 300, 23.6 and 30.2 on the fallback branch at 8,192,
-// 33.7 and 36.1 with clusters, 78 and 83.5 at 65,536).  The eight kernels of the
+// graph, when it was five: 25.2 and 29.3 at K = 300, 23.6 and 30.2 on the fallback
+// branch at 8,192, 33.7 and 36.1 with clusters, 78 and 83.5 at 65,536).  The seven kernels of the
 // other chains cost the host as much either way (36-41 us, 37 and 36 us a replan
 // at K = 50) and are replayed.  So is every chain on a stream that is being
 // captured.
@@ -612,8 +607,7 @@ ce_status replan_unchecked(ce_mppi_planner* P, const float* x_t, const float* ob
     e = hipEventRecord(t.ev[3 * i], s);
     launch_rollout(L, P->c, P->b, x_t, obstacles, n_obs);
     if (e == hipSuccess && L.err == hipSuccess) e = hipEventRecord(t.ev[3 * i + 1], s);
-    launch_post_rollout(L, P->c, P->b);
-    launch_finish(L, P->c, P->b, u_out, U_out, info);
+    launch_post_rollout(L, P->c, P->b, u_out, U_out, info);
     if (e == hipSuccess && L.err == hipSuccess) e = hipEventRecord(t.ev[3 * i + 2], s);
     if (e == hipSuccess) e = L.err;
   } else if (P->launch_mode == kLaunchAuto ? replay_by_default(P, s) : P->launch_mode == CE_LAUNCH_GRAPH) {
@@ -621,8 +615,7 @@ ce_status replan_unchecked(ce_mppi_planner* P, const float* x_t, const float* ob
   } else {
     Launcher L(s);
     launch_rollout(L, P->c, P->b, x_t, obstacles, n_obs);
-    launch_post_rollout(L, P->c, P->b);
-    launch_finish(L, P->c, P->b, u_out, U_out, info);
+    launch_post_rollout(L, P->c, P->b, u_out, U_out, info);
     e = L.err;
   }
   if (e != hipSuccess) return hip_fail(e, "replan launch");
@@ -851,8 +844,7 @@ ce_status ce_mppi_replan_from_rollouts(ce_mppi_planner* P, const float* x_t, con
   if (e != hipSuccess) return hip_fail(e, "replan_from_rollouts copy");
   Launcher L(s);
   launch_reduce_records(L, c, b, x_t, obstacles, n_obs);
-  launch_post_rollout(L, c, b);
-  launch_finish(L, c, b, u_out, U_out, info);
+  launch_post_rollout(L, c, b, u_out, U_out, info);
   if (L.err != hipSuccess) return hip_fail(L.err, "replan_from_rollouts");
   return CE_OK;
 }

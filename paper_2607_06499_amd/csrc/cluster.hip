@@ -211,7 +211,7 @@ __device__ __forceinline__ int win_bin(const Cfg& c, float2 zz) {
 }
 
 // What a replan's later kernels need of the totals (one thread).
-__device__ __forceinline__ void publish_totals(const Cfg& c, const Bufs& b, const Totals& T, const float* tot) {
+__device__ __forceinline__ void publish_totals(const Bufs& b, const Totals& T, const float* tot) {
   Ctrl* ct = b.ctrl;
   ct->n_col = T.ncol;
   ct->n_feas = T.nfeas;
@@ -226,33 +226,53 @@ __device__ __forceinline__ void publish_totals(const Cfg& c, const Bufs& b, cons
   ct->stat_direct = 0;
   ct->sel = -1;
   for (int i = 0; i < 3; ++i) ct->ref[i] = T.ref[i];
-  // Eq. (17) for o*, once per replan on the clustering branch (the
-  // selection reads it): the mean of H'-1 finite differences telescopes
-  // to (o_t - o_{t-H'+1}) / ((H'-1) dt)
-  float v[3] = {0.f, 0.f, 0.f};
-  int Hp = 0;
-  if (c.scene_mode == 1 && T.branch == 0) {
-    const int hc = ct->hist_count;
-    Hp = hc < c.H ? hc : c.H;
-    const int o = ct->closest;
-    if (Hp >= 2 && o >= 0) {
-      const int h0 = ct->hist_head;
-      const int h1 = (h0 - (Hp - 1) + 2 * c.H) % c.H;
-      const float* pa = b.hist + ((size_t)h0 * c.max_obs + o) * c.p;
-      const float* pz = b.hist + ((size_t)h1 * c.max_obs + o) * c.p;
-      const float den = (float)(Hp - 1) * c.dt;
-      v[0] = (pa[0] - pz[0]) / den;
-      v[1] = (pa[1] - pz[1]) / den;
-      if (c.p == 3) v[2] = (pa[2] - pz[2]) / den;
+}
+
+// Eq. (17) for o*, once per replan on the clustering branch (the selection
+// reads it): the mean of H'-1 finite differences telescopes to
+// (o_t - o_{t-H'+1}) / ((H'-1) dt).  In three parts, so that one thread's chain
+// of loads (ring state, positions) runs behind the block's work and not after it:
+// 3 memory latencies at the end of the compaction otherwise.
+struct DynIn {
+  int hc, h0, o, Hp;
+  float pa[3], pz[3];
+};
+__device__ __forceinline__ void dyn_ring(const Cfg& c, const Bufs& b, DynIn& d) {
+  d.hc = b.ctrl->hist_count;
+  d.h0 = b.ctrl->hist_head;
+  d.o = b.ctrl->closest;
+}
+__device__ __forceinline__ void dyn_load(const Cfg& c, const Bufs& b, int branch, DynIn& d) {
+  d.Hp = c.scene_mode == 1 && branch == 0 ? min(d.hc, c.H) : 0;
+  if (d.Hp >= 2 && d.o >= 0) {
+    const int h1 = (d.h0 - (d.Hp - 1) + 2 * c.H) % c.H;
+    const float* pa = b.hist + ((size_t)d.h0 * c.max_obs + d.o) * c.p;
+    const float* pz = b.hist + ((size_t)h1 * c.max_obs + d.o) * c.p;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      d.pa[i] = pa[i < c.p ? i : 0];
+      d.pz[i] = pz[i < c.p ? i : 0];
     }
   }
-  const float nv = sqrtf(__builtin_fmaf(v[2], v[2], __builtin_fmaf(v[1], v[1], v[0] * v[0])));
+}
+__device__ __forceinline__ void dyn_publish(const Cfg& c, const Bufs& b, const DynIn& d) {
+  Ctrl* ct = b.ctrl;
+  float v[3] = {0.f, 0.f, 0.f}, vh[3], nv = 0.f;
+  vh[0] = vh[1] = vh[2] = 0.f / c.norm_eps;
+  if (d.Hp >= 2 && d.o >= 0) {
+    const float den = (float)(d.Hp - 1) * c.dt;
+    v[0] = (d.pa[0] - d.pz[0]) / den;
+    v[1] = (d.pa[1] - d.pz[1]) / den;
+    if (c.p == 3) v[2] = (d.pa[2] - d.pz[2]) / den;
+    nv = sqrtf(__builtin_fmaf(v[2], v[2], __builtin_fmaf(v[1], v[1], v[0] * v[0])));
+    for (int i = 0; i < 3; ++i) vh[i] = v[i] / (nv + c.norm_eps);
+  }
   for (int i = 0; i < 3; ++i) {
     ct->v_obs[i] = v[i];
-    ct->v_hat[i] = v[i] / (nv + c.norm_eps);
+    ct->v_hat[i] = vh[i];
   }
-  ct->dyn_h = Hp;
-  ct->dyn_ok = (c.scene_mode == 1 && Hp >= 2 && !(nv < c.v_obs_min)) ? 1 : 0;
+  ct->dyn_h = d.Hp;
+  ct->dyn_ok = (c.scene_mode == 1 && d.Hp >= 2 && !(nv < c.v_obs_min)) ? 1 : 0;
 }
 
 // Feature of Eq. (13) of a terminal point.
@@ -282,13 +302,21 @@ __device__ __forceinline__ void compact_body(const Cfg& c, const Bufs& b, int bx
     pk[i] = b.pT[(size_t)kc * P + i];
     gk[i] = b.g[(size_t)kc * P + i];
   }
+  const bool pub = bx == 0 && threadIdx.x == kFinThreads - 1;
+  DynIn dyn;
+  if (pub) dyn_ring(c, b, dyn);
   reduce_partials(c, b, bx * (kFinThreads / kGroup), s_tot, &s_before);
   const Totals T = decide(c, s_tot, bad);
-  if (bx == 0 && threadIdx.x == 0) publish_totals(c, b, T, s_tot);
+  if (pub) {
+    dyn_load(c, b, T.branch, dyn);
+    publish_totals(b, T, s_tot);
+    if (T.branch != 0) dyn_publish(c, b, dyn);
+  }
   if (T.branch != 0) return;
   const int feas = ink ? !colk : 0;
   int tot;
-  const int local = block_excl_scan<kFinThreads>(feas, &tot);
+  const int local = block_excl_scan<kFinThreads, true>(feas, &tot);
+  if (pub) dyn_publish(c, b, dyn);
   if (!feas) return;
   const int rank = s_before + local;
   ZT zz, gg;
@@ -2816,6 +2844,8 @@ __device__ __forceinline__ void wlabel_body(const Cfg& c, const Bufs& b, int bx,
   int V, bka = 0;
   float Sa = 0.f;
   float2 ga = make_float2(0.f, 0.f);
+  bool pub = false;
+  DynIn dyn;
   if constexpr (POST) {
     constexpr int KB = WinPoints<POST>::KB, NW = NT / kWave;
     const int lane = t & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(t / kWave);
@@ -2830,9 +2860,15 @@ __device__ __forceinline__ void wlabel_body(const Cfg& c, const Bufs& b, int bx,
     }
     __shared__ float s_tot[kPart + 1];
     __shared__ int s_before;
+    pub = bx == 0 && t == NT - 1;
+    if (pub) dyn_ring(c, b, dyn);
     reduce_partials(c, b, 0, s_tot, &s_before);
     const Totals T = decide(c, s_tot, bad);
-    if (bx == 0 && t == 0) publish_totals(c, b, T, s_tot);
+    if (pub) {
+      dyn_load(c, b, T.branch, dyn);
+      publish_totals(b, T, s_tot);
+      if (T.branch != 0) dyn_publish(c, b, dyn);
+    }
     V = T.branch == 0 ? T.nfeas : 0;
     if (bx * kChunk >= V) return;
 #pragma unroll
@@ -2885,6 +2921,7 @@ __device__ __forceinline__ void wlabel_body(const Cfg& c, const Bufs& b, int bx,
     b.Sv[a] = Sa;
     reinterpret_cast<float2*>(b.gv)[a] = ga;
   }
+  if (pub) dyn_publish(c, b, dyn);
   if (done) return;
   if constexpr (POST) {
     // the general form reads features and buckets of every point from memory:
@@ -2919,11 +2956,11 @@ __device__ __forceinline__ float (*stat_lds())[kStatFields] {
   return s_tot;
 }
 __device__ __forceinline__ ClusterStat cluster_stats(const Cfg& c, const Bufs& b, int M, int V,
-                                                     const float (&pre)[kStatBatch], bool publish) {
+                                                     const float (&pre)[kStatBatch], float* stage, bool publish) {
   ClusterStat r;
   r.cost = r.smin = INFINITY;
   r.dir = make_float4(0.f, 0.f, 0.f, 0.f);
-  const int t = threadIdx.x;
+  const int t = item_thread();
   if (M > kStatClusters) {  // b.ctrl->stat_direct
     r.cost = b.c_cost[t < M ? t : 0];
     r.smin = b.c_smin[t < M ? t : 0];
@@ -2931,24 +2968,42 @@ __device__ __forceinline__ ClusterStat cluster_stats(const Cfg& c, const Bufs& b
     return r;
   }
   float (*s_tot)[kStatFields] = stat_lds();
-  const int nch = (V + kChunk - 1) / kChunk, f = t % kStatFields;
-  for (int i = t; i < M * kStatFields; i += kUpdThreads) {
-    float v = 0.f;
-    for (int q0 = 0; q0 < nch; q0 += kStatBatch) {
-      float x[kStatBatch];
+  const int nch = (V + kChunk - 1) / kChunk, f = t % kStatFields, nf = M * kStatFields;
+  float v = 0.f;
+  if (nch <= kStatBatch) {
 #pragma unroll
-      for (int q = 0; q < kStatBatch; ++q)
-        x[q] = (q0 == 0 && i == t) ? pre[q]
-                                   : b.stat[(size_t)min(q0 + q, nch - 1) * (kStatClusters * kStatFields) + i];
+    for (int q = 0; q < kStatBatch; ++q) {
+      if (q >= nch) break;
+      v = q == 0 ? pre[q] : (f == 4 ? fminf(v, pre[q]) : v + pre[q]);
+    }
+  } else {
+    // more chunks: the block stages as many as fit (32 of up to eight clusters),
+    // so that their first touch costs one memory latency; eight at a time by the
+    // adding threads were 12 us at 61 chunks
+    constexpr int E = 4;
+    static_assert(E * kUpdThreads <= kUpdThreads / kWave * kFinChunks * kWave, "the staged chunks fit");
+    const int sh = nf <= 8 ? 3 : 32 - __clz(nf - 1), per = kUpdThreads >> sh;
+    for (int q0 = 0; q0 < nch; q0 += E * per) {
+      const int i = t & ((1 << sh) - 1), q = q0 + (t >> sh);
+      float x[E];
 #pragma unroll
-      for (int q = 0; q < kStatBatch; ++q) {
-        if (q0 + q >= nch) break;
-        v = q0 + q == 0 ? x[q] : (f == 4 ? fminf(v, x[q]) : v + x[q]);
+      for (int e = 0; e < E; ++e)
+        x[e] = q + e * per < nch && i < nf ? b.stat[(size_t)(q + e * per) * (kStatClusters * kStatFields) + i] : 0.f;
+      lds_sync();
+#pragma unroll
+      for (int e = 0; e < E; ++e) stage[t + e * kUpdThreads] = x[e];
+      lds_sync();
+      if (t < nf) {
+        const int n = min(E * per, nch - q0);
+        for (int k = 0; k < n; ++k) {
+          const float y = stage[(k << sh) + t];
+          v = q0 + k == 0 ? y : (f == 4 ? fminf(v, y) : v + y);
+        }
       }
     }
-    s_tot[i / kStatFields][f] = v;
   }
-  __syncthreads();
+  if (t < nf) s_tot[t / kStatFields][f] = v;  // (at most one field per thread)
+  lds_sync();
   if (t < M) {
     const float* v = s_tot[t];
     const ClusterMean m = c.p == 2 ? cluster_mean<2>(c, v[0], v[1], v[2], v[3], v[5])
@@ -2981,13 +3036,18 @@ struct Sel {
   float margin, smin, v[3], vh[3];
 };
 
-// The statistics of cluster threadIdx.x come loaded; further clusters are
-// loaded here.
+// The statistics of cluster threadIdx.x come loaded, and the words of Eq. (17);
+// further clusters are loaded here.
+struct DynWords {
+  int h, ok;
+  float v[3], vh[3];
+};
 __device__ __forceinline__ Sel select_cluster(const Cfg& c, const Bufs& b, int M, float pre_cost, float pre_mn,
-                                              float4 pre_dir) {
-  __shared__ float s_k1[kUpdThreads / kWave], s_k2[kUpdThreads / kWave], s_m1[kUpdThreads / kWave];
-  __shared__ int s_i1[kUpdThreads / kWave];
-  const Ctrl* ct = b.ctrl;
+                                              float4 pre_dir, const DynWords& dw) {
+  constexpr int NW = kUpdThreads / kWave;
+  __shared__ float s_k1[NW], s_k2[NW], s_m1[NW];
+  __shared__ int s_i1[NW];
+  const int t = item_thread(), wv = __builtin_amdgcn_readfirstlane(t / kWave);
   Sel s;
   s.sel = -1;
   s.rule = 0;
@@ -3001,25 +3061,23 @@ __device__ __forceinline__ Sel select_cluster(const Cfg& c, const Bufs& b, int M
     return s;
   }
   if (c.scene_mode == 1) {
-    // the estimate of Eq. (17), computed once by the compaction kernel
-    s.h_used = ct->dyn_h;
-    s.v[0] = ct->v_obs[0];
-    s.v[1] = ct->v_obs[1];
-    s.v[2] = ct->v_obs[2];
-    s.vh[0] = ct->v_hat[0];
-    s.vh[1] = ct->v_hat[1];
-    s.vh[2] = ct->v_hat[2];
-    if (ct->dyn_ok) s.rule = 1;
+    // the estimate of Eq. (17), computed once by the compaction
+    s.h_used = dw.h;
+    for (int i = 0; i < 3; ++i) {
+      s.v[i] = dw.v[i];
+      s.vh[i] = dw.vh[i];
+    }
+    if (dw.ok) s.rule = 1;
     else s.status_add = 8u;
   }
   // best key (ties to the lowest cluster), its minimum cost, and the second
-  // best key: per thread over a strided subset of the clusters, then wave
-  // butterflies and the four waves in order (min and the tie rule are exact,
-  // so the result does not depend on the combining order)
+  // best key: per thread over a strided subset of the clusters, then a scan over
+  // the lanes and the waves with clusters in order (min and the tie rule are
+  // exact, so the result does not depend on the combining order)
   float k1 = INFINITY, k2 = INFINITY, m1 = INFINITY;
   int i1 = kInt32Max;
-  for (int cl = threadIdx.x; cl < M; cl += kUpdThreads) {
-    const bool first = cl == (int)threadIdx.x;
+  for (int cl = t; cl < M; cl += kUpdThreads) {
+    const bool first = cl == t;
     const float cost = first ? pre_cost : b.c_cost[cl], mn = first ? pre_mn : b.c_smin[cl];
     const float4 dir = first ? pre_dir : reinterpret_cast<const float4*>(b.c_dir)[cl];
     const float key = s.rule == 0 ? cost : dir.x * s.vh[0] + dir.y * s.vh[1] + dir.z * s.vh[2];
@@ -3040,27 +3098,43 @@ __device__ __forceinline__ Sel select_cluster(const Cfg& c, const Bufs& b, int M
     am = takeb ? bm : am;
     a2 = n2;
   };
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const float b1 = __shfl_xor(k1, off, kWave), b2 = __shfl_xor(k2, off, kWave);
-    const int bi = __shfl_xor(i1, off, kWave);
-    const float bm = __shfl_xor(m1, off, kWave);
-    combine(k1, k2, i1, m1, b1, b2, bi, bm);
+  const int nw = min((M + kWave - 1) / kWave, NW);  // waves with clusters
+  if (M == 1) {  // the one cluster is thread 0's
+    if (t == 0) {
+      s_k1[0] = k1;
+      s_k2[0] = k2;
+      s_i1[0] = i1;
+      s_m1[0] = m1;
+    }
+  } else if (wv < nw) {
+    // (lanes without a source keep their own values against the neutral ones)
+    const int inf = 0x7f800000;
+#define CEMPPI_SEL_STEP(ctrl, rows)                                                                              \
+  combine(k1, k2, i1, m1,                                                                                        \
+          __int_as_float(__builtin_amdgcn_update_dpp(inf, __float_as_int(k1), ctrl, rows, 0xf, false)),          \
+          __int_as_float(__builtin_amdgcn_update_dpp(inf, __float_as_int(k2), ctrl, rows, 0xf, false)),          \
+          __builtin_amdgcn_update_dpp(kInt32Max, i1, ctrl, rows, 0xf, false),                                    \
+          __int_as_float(__builtin_amdgcn_update_dpp(inf, __float_as_int(m1), ctrl, rows, 0xf, false)))
+    CEMPPI_SEL_STEP(0x111, 0xf);
+    CEMPPI_SEL_STEP(0x112, 0xf);
+    CEMPPI_SEL_STEP(0x114, 0xf);
+    CEMPPI_SEL_STEP(0x118, 0xf);
+    CEMPPI_SEL_STEP(0x142, 0xa);
+    CEMPPI_SEL_STEP(0x143, 0xc);
+#undef CEMPPI_SEL_STEP
+    if ((t & (kWave - 1)) == kWave - 1) {
+      s_k1[wv] = k1;
+      s_k2[wv] = k2;
+      s_i1[wv] = i1;
+      s_m1[wv] = m1;
+    }
   }
-  const int wv = threadIdx.x / kWave;
-  if ((threadIdx.x & (kWave - 1)) == 0) {
-    s_k1[wv] = k1;
-    s_k2[wv] = k2;
-    s_i1[wv] = i1;
-    s_m1[wv] = m1;
-  }
-  __syncthreads();
+  lds_sync();
   k1 = s_k1[0];
   k2 = s_k2[0];
   i1 = s_i1[0];
   m1 = s_m1[0];
-#pragma unroll
-  for (int w = 1; w < kUpdThreads / kWave; ++w) combine(k1, k2, i1, m1, s_k1[w], s_k2[w], s_i1[w], s_m1[w]);
+  for (int w = 1; w < nw; ++w) combine(k1, k2, i1, m1, s_k1[w], s_k2[w], s_i1[w], s_m1[w]);
   if (i1 >= M) {  // no key compared below +inf (infinite or NaN keys): the lowest cluster
     i1 = 0;
     m1 = M > kStatClusters ? b.c_smin[0] : stat_lds()[0][4];
@@ -3068,7 +3142,6 @@ __device__ __forceinline__ Sel select_cluster(const Cfg& c, const Bufs& b, int M
   s.sel = i1;
   s.smin = m1;
   s.margin = M > 1 ? k2 - k1 : INFINITY;
-  __syncthreads();
   return s;
 }
 
@@ -3077,16 +3150,28 @@ __device__ __forceinline__ Sel select_cluster(const Cfg& c, const Bufs& b, int M
 // w * PER + PER - 1 (in order), lane l the elements l, l + 64, ... (NCH
 // chunks, two chunks of every row requested at once; a chunk past the row's
 // end reads the next row, or the slack after the last, and is not used);
-// element N m is the weight sum.  The four waves are added in order.
+// element N m is the weight sum.  The waves are added in order; thread e
+// returns element e.
 struct UpdLds {
   float w[kUpdChunk];
   int k[kUpdChunk];
   float acc[kUpdThreads / kWave][kFinChunks * kWave];
+  float tot[kMaxNM + 1];
+  float un[kMaxNM];
+  int last;
 };
 
+// Sum of the waves' elements, in wave order.
+__device__ __forceinline__ float upd_waves(const UpdLds& L, int e) {
+  float v = L.acc[0][e];
+#pragma unroll
+  for (int w = 1; w < kUpdThreads / kWave; ++w) v += L.acc[w][e];
+  return v;
+}
+
 template <int NCH>
-__device__ __forceinline__ void update_sums(const Bufs& b, int NM, float* part, UpdLds& L) {
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+__device__ __forceinline__ float update_sums(const Bufs& b, int NM, int t, UpdLds& L) {
+  const int lane = t & (kWave - 1), wv = t / kWave;
   constexpr int PER = kUpdChunk / (kUpdThreads / kWave);
 #pragma unroll
   for (int c0 = 0; c0 < NCH; c0 += 2) {
@@ -3113,25 +3198,45 @@ __device__ __forceinline__ void update_sums(const Bufs& b, int NM, float* part, 
       L.acc[wv][e] = acc;
     }
   }
-  __syncthreads();
-  float (*s_acc)[kFinChunks * kWave] = L.acc;
-  for (int e = threadIdx.x; e <= NM; e += kUpdThreads)
-    part[e] = ((s_acc[0][e] + s_acc[1][e]) + s_acc[2][e]) + s_acc[3][e];
+  lds_sync();
+  return t <= NM ? upd_waves(L, t) : 0.f;
 }
 
-// Update partials, Eq. (19)-(20) (Eq. (6)-(7) on the fallback branches):
-// block b takes kUpdChunk candidates (16 per wave); lane = element of the
-// [N][m] sequence; the four waves' sums are combined in a fixed order.
+// Update, Eq. (19)-(20) (Eq. (6)-(7) on the fallback branches), and the
+// outputs.  Block bx takes kUpdChunk candidates, 16 per wave; lane = element of
+// the [N][m] sequence.  Blocks past the last candidate end at once; the others
+// store their sums as a row, and the block that finishes last adds the rows in a
+// fixed order, U_new = U + sum / sum(w), and writes outputs, shifted nominal
+// (last control repeated), step counter and info record.
+//
+// Bound by its chain of memory latencies (control words and candidate records,
+// perturbation rows, ticket, partial rows).  The rows are stored and loaded at
+// agent scope, past the L2s: a ticket taken after the stores have completed is
+// all the order they need, where a device-scope release would write back the
+// whole L2 of each XCD.  Measured, with the final combination as a kernel of its
+// own (blocks of 64 candidates) and so: 5.5 + 3.4 and 6.5 us at K = 300, 5.4 +
+// 3.8 and 7.8 at 8,192, 20.4 + 7.7 and 20.0 at 65,536, a batch of 64 26 + 7 and
+// 23.7.  Blocks of 256 candidates and 1,024 threads: 7.1, 8.8, 16.3 and 27.1.
 template <int NCH>
-__device__ __forceinline__ void update_body(const Cfg& c, const Bufs& b, UpdLds& L, int bx) {
-  float* s_w = L.w;
-  int* s_k = L.k;
+__device__ __forceinline__ void update_body(const Cfg& c, const Bufs& b, UpdLds& L, int bx, float* __restrict__ u_out,
+                                            float* __restrict__ U_out, void* info_out) {
   const Ctrl* ct = b.ctrl;
+  const int t = item_thread(), lane = t & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int branch = ct->branch, n_feas = ct->n_feas, M_cl = ct->M;
+  const bool bad = ct->nonfinite != 0;
+  const float smin_all = ct->smin_all, smin_feas = ct->smin_feas;
+  DynWords dw;
+  dw.h = ct->dyn_h;
+  dw.ok = ct->dyn_ok;
+  for (int i = 0; i < 3; ++i) {
+    dw.v[i] = ct->v_obs[i];
+    dw.vh[i] = ct->v_hat[i];
+  }
   // the candidate records of both branches are requested with the control
   // words, before the branch is known (every array holds K entries)
   const int a0 = bx * kUpdChunk;
-  const int a = a0 + (int)threadIdx.x;
-  const bool ina = threadIdx.x < kUpdChunk && a < c.K;
+  const int a = a0 + t;
+  const bool ina = t < kUpdChunk && a < c.K;
   const int ac = ina ? a : 0;  // unconditional loads at a clamped index
   const float S_all = b.S[ac];
   const int lab_v = b.label[ac], k_v = b.vidx[ac];
@@ -3141,13 +3246,14 @@ __device__ __forceinline__ void update_body(const Cfg& c, const Bufs& b, UpdLds&
   float pre[kStatBatch];
 #pragma unroll
   for (int q = 0; q < kStatBatch; ++q)
-    pre[q] = b.stat[(size_t)min(q, nchunk_k - 1) * (kStatClusters * kStatFields) + threadIdx.x];
-  const int branch = ct->branch;
-  const bool bad = ct->nonfinite != 0;
-  const int NM = c.NM;
+    pre[q] = b.stat[(size_t)min(q, nchunk_k - 1) * (kStatClusters * kStatFields) +
+                    min(t, kStatClusters * kStatFields - 1)];
+  const int NM = c.NM, W = NM + 1;
   const bool over_all = branch != 0;
-  const int M = branch == 0 ? ct->M : 0;
-  const int ncand = over_all ? c.K : ct->n_feas;
+  const int M = branch == 0 ? M_cl : 0;
+  const int ncand = over_all ? c.K : n_feas;
+  const int nrows = (ncand + kUpdChunk - 1) / kUpdChunk;
+  if (bx >= nrows) return;
   const bool mine = ina && !bad && a < ncand;
   int lab = -1, kk = 0;
   float Sa = 0.f;
@@ -3163,9 +3269,9 @@ __device__ __forceinline__ void update_body(const Cfg& c, const Bufs& b, UpdLds&
   }
   Sel s;
   int sel_n = 0;
-  if (branch == 0 && (a0 < ncand || bx == 0)) {
-    const ClusterStat cs = cluster_stats(c, b, M, ncand, pre, bx == 0);
-    s = select_cluster(c, b, M, cs.cost, cs.smin, cs.dir);
+  if (branch == 0) {
+    const ClusterStat cs = cluster_stats(c, b, M, ncand, pre, &L.acc[0][0], bx == 0);
+    s = select_cluster(c, b, M, cs.cost, cs.smin, cs.dir, dw);
     sel_n = s.sel >= 0 ? cluster_size(b, M, s.sel) : 0;
   } else {
     s.sel = -1;
@@ -3176,119 +3282,102 @@ __device__ __forceinline__ void update_body(const Cfg& c, const Bufs& b, UpdLds&
     s.smin = INFINITY;
     for (int i = 0; i < 3; ++i) s.v[i] = s.vh[i] = 0.f;
   }
-  if (bx == 0 && threadIdx.x == 0 && branch == 0) {
-    Ctrl* cw = b.ctrl;
-    cw->sel = s.sel;
-    cw->rule = s.rule;
-    cw->h_used = s.h_used;
-    cw->margin = s.margin;
-    cw->status = ct->status | s.status_add;
-    for (int i = 0; i < 3; ++i) {
-      cw->v_obs[i] = s.v[i];
-      cw->v_hat[i] = s.vh[i];
-    }
-    cw->sel_size = sel_n;
-    cw->smin_sel = s.smin;
-  }
   const int sel = s.sel;
-  const float smin = over_all ? ct->smin_all : (sel >= 0 ? s.smin : ct->smin_feas);
+  const float smin = over_all ? smin_all : (sel >= 0 ? s.smin : smin_feas);
   const float inv_l = 1.0f / c.lambda;
-  if (threadIdx.x < kUpdChunk) {
+  if (t < kUpdChunk) {
     float w = 0.f;
     if (mine && (over_all || sel < 0 || lab == sel)) w = expf(-(Sa - smin) * inv_l);
-    s_w[threadIdx.x] = w;
-    s_k[threadIdx.x] = kk;  // a valid row whenever the weight is nonzero
+    L.w[t] = w;
+    L.k[t] = kk;  // a valid row whenever the weight is nonzero
   }
-  __syncthreads();
-  float* part = b.upart + (size_t)bx * (NM + 1);
-  update_sums<NCH>(b, NM, part, L);
-}
-
-template <int NCH>
-__global__ __launch_bounds__(kUpdThreads) void k_update(Cfg c, Bufs b) {
-  __shared__ UpdLds L;
-  update_body<NCH>(c, b, L, (int)blockIdx.x);
-}
-
-// Final combination (one block): sum of the update partials in a fixed order,
-// U_new = U + sum / sum(w), outputs, shift (last control repeated), step
-// counter and the info record.  NCH = ceil((N m + 1) / 64) element chunks.
-struct FinLds {
-  float part[kFinThreads / kWave][kMaxNM + 1];
-  float tot[kMaxNM + 1];
-  float un[kMaxNM];
-};
-
-template <int NCH>
-__device__ __forceinline__ void finish_body(const Cfg& c, const Bufs& b, FinLds& sh, float* __restrict__ u_out, float* __restrict__ U_out, void* info_out) {
-  float (*s_part)[kMaxNM + 1] = sh.part;
-  float* s_tot = sh.tot;
-  float* s_un = sh.un;
-  // the control words and the nominal are requested with the partials
+  lds_sync();
+  float tot = update_sums<NCH>(b, NM, t, L);
+  if (nrows > 1) {
+    if (t < W)
+      __hip_atomic_store(b.upart + (size_t)bx * W + t, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // every wave's part of the row has reached memory before the ticket
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (t == 0) {
+      const int l =
+          __hip_atomic_fetch_add(&b.ctrl->uticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nrows - 1;
+      if (l) __hip_atomic_store(&b.ctrl->uticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next replan
+      L.last = l;
+    }
+    __syncthreads();
+    if (!L.last) return;
+  }
+  // the nominal and the record's words are requested with the rows
+  const float u_own = b.U[t < NM ? t : 0];
   const Ctrl cv = *b.ctrl;
-  const bool bad = cv.nonfinite != 0;
-  const int NM = c.NM, W = NM + 1;
-  const int e_own = threadIdx.x;  // NM <= kMaxNM <= kFinThreads: one element per thread
-  const int nb = c.nblk_upd;
-  // wave w sums the rows w, w + 16, ... in increasing order, lane l the
-  // elements l, l + 64, ... of each (whole rows: coalesced).  A batch of
-  // kFinRows rows per wave is requested at once; rows past the last update
-  // block are zero padding and the chunks past a row's end read the next
-  // row (those sums are never used), so the loads need no tests.
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  constexpr int NW = kFinThreads / kWave;
-  float acc[NCH];
+  if (nrows > 1) {
+    // wave w sums the rows w, w + 16, ... in increasing order, lane l the
+    // elements l, l + 64, ...; kFinRows rows per wave are requested at once (the
+    // chunks past a row's end read the next row; those sums are never used)
+    constexpr int NW = kUpdThreads / kWave;
+    float acc[NCH];
 #pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) acc[ch] = 0.f;
-  float u_own = 0.f;
-  for (int r0 = wv; r0 < nb; r0 += NW * kFinRows) {
-    float v[kFinRows][NCH];
+    for (int ch = 0; ch < NCH; ++ch) acc[ch] = 0.f;
+    for (int r0 = wv; r0 < nrows; r0 += NW * kFinRows) {
+      float v[kFinRows][NCH];
 #pragma unroll
-    for (int rb = 0; rb < kFinRows; ++rb)
+      for (int rb = 0; rb < kFinRows; ++rb) {
+        if (r0 + rb * NW >= nrows) break;
 #pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) v[rb][ch] = b.upart[(r0 + rb * NW) * W + ch * kWave + lane];  // < 2^31
-    if (r0 == wv) u_own = b.U[e_own < NM ? e_own : 0];
+        for (int ch = 0; ch < NCH; ++ch)
+          v[rb][ch] = __hip_atomic_load(b.upart + (r0 + rb * NW) * W + ch * kWave + lane, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+      }
 #pragma unroll
-    for (int rb = 0; rb < kFinRows; ++rb)
+      for (int rb = 0; rb < kFinRows; ++rb) {
+        if (r0 + rb * NW >= nrows) break;
 #pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) acc[ch] += v[rb][ch];
+        for (int ch = 0; ch < NCH; ++ch) acc[ch] += v[rb][ch];
+      }
+    }
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) L.acc[wv][ch * kWave + lane] = acc[ch];
+    lds_sync();
+    if (t < W) tot = upd_waves(L, t);
   }
-  if (nb <= wv) u_own = b.U[e_own < NM ? e_own : 0];
-#pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) {
-    const int e = ch * kWave + lane;
-    if (e < W) s_part[wv][e] = acc[ch];
+  if (t < W) L.tot[t] = tot;
+  lds_sync();
+  const float wsum = L.tot[NM];
+  if (t < NM) {
+    const float un = bad ? u_own : u_own + tot / wsum;
+    if (U_out) U_out[t] = un;
+    b.Unew[t] = un;
+    L.un[t] = un;
   }
-  __syncthreads();
-  if (e_own < W) {
-    float t = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) t += s_part[w][e_own];
-    s_tot[e_own] = t;
-  }
-  __syncthreads();
-  const float wsum = s_tot[NM];
-  if (e_own < NM) {
-    const float un = bad ? u_own : u_own + s_tot[e_own] / wsum;
-    if (U_out) U_out[e_own] = un;
-    b.Unew[e_own] = un;
-    s_un[e_own] = un;
-  }
-  __syncthreads();
-  if (e_own < NM) {
-    const int j = e_own / c.m, i = e_own % c.m;
-    if (j == 0 && u_out) u_out[i] = s_un[e_own];
+  lds_sync();
+  if (t < NM) {
+    const int j = t / c.m, i = t % c.m;
+    if (j == 0 && u_out) u_out[i] = L.un[t];
     if (!bad) {
       const int src = j + 1 < c.N ? j + 1 : c.N - 1;
-      b.U[e_own] = s_un[src * c.m + i];
+      b.U[t] = L.un[src * c.m + i];
     }
   }
-  if (threadIdx.x == 0) {
+  if (t == 0) {
     Ctrl* cw = b.ctrl;
-    const int branch = cv.branch;
     const bool cl = branch == 0;
-    const bool hasM = cl && cv.M > 0;
-    const float smin = !cl ? cv.smin_all : (hasM ? cv.smin_sel : cv.smin_feas);
+    const bool hasM = cl && M > 0;
+    const uint32_t status = cv.status | s.status_add;
+    const float s_min = !cl ? smin_all : (hasM ? s.smin : smin_feas);
+    if (cl) {
+      cw->sel = s.sel;
+      cw->rule = s.rule;
+      cw->h_used = s.h_used;
+      cw->margin = s.margin;
+      cw->status = status;
+      cw->sel_size = sel_n;
+      cw->smin_sel = s.smin;
+      for (int i = 0; i < 3; ++i) {
+        cw->v_obs[i] = s.v[i];
+        cw->v_hat[i] = s.vh[i];
+      }
+    }
     cw->wsum = wsum;
     // ring state for the next replan's rollout blocks
     cw->hs_head = cv.hist_head;
@@ -3311,20 +3400,20 @@ __device__ __forceinline__ void finish_body(const Cfg& c, const Bufs& b, FinLds&
       inf->n_collide = bad ? 0 : cv.n_col;
       inf->n_feasible = bad ? 0 : cv.n_feas;
       inf->n_ref = cl ? cv.n_ref : 0;
-      inf->n_clusters = cl ? cv.M : 0;
-      inf->selected = hasM ? cv.sel : -1;
-      inf->selected_size = hasM ? cv.sel_size : 0;
+      inf->n_clusters = cl ? M : 0;
+      inf->selected = hasM ? s.sel : -1;
+      inf->selected_size = hasM ? sel_n : 0;
       inf->closest = cv.closest;
-      inf->rule = hasM ? cv.rule : 0;
-      inf->history_used = hasM ? cv.h_used : 0;
-      inf->status = cv.status;
+      inf->rule = hasM ? s.rule : 0;
+      inf->history_used = hasM ? s.h_used : 0;
+      inf->status = status;
       inf->step = cv.step_used;
-      inf->margin = hasM ? cv.margin : INFINITY;
-      inf->s_min = smin;
+      inf->margin = hasM ? s.margin : INFINITY;
+      inf->s_min = s_min;
       for (int i = 0; i < 3; ++i) {
         inf->ref_point[i] = cl ? cv.ref[i] : 0.f;
-        inf->v_obs[i] = hasM ? cv.v_obs[i] : 0.f;
-        inf->v_obs_hat[i] = hasM ? cv.v_hat[i] : 0.f;
+        inf->v_obs[i] = hasM ? s.v[i] : 0.f;
+        inf->v_obs_hat[i] = hasM ? s.vh[i] : 0.f;
       }
       inf->weight_sum = wsum;
     }
@@ -3332,9 +3421,10 @@ __device__ __forceinline__ void finish_body(const Cfg& c, const Bufs& b, FinLds&
 }
 
 template <int NCH>
-__global__ __launch_bounds__(kFinThreads) void k_finish(Cfg c, Bufs b, float* __restrict__ u_out, float* __restrict__ U_out, void* info_out) {
-  __shared__ FinLds sh;
-  finish_body<NCH>(c, b, sh, u_out, U_out, info_out);
+__global__ __launch_bounds__(kUpdThreads) void k_update(Cfg c, Bufs b, float* __restrict__ u_out,
+                                                        float* __restrict__ U_out, void* info_out) {
+  __shared__ UpdLds L;
+  update_body<NCH>(c, b, L, (int)blockIdx.x, u_out, U_out, info_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -3456,37 +3546,22 @@ __global__ __launch_bounds__(kFinThreads) void kb_tree_cc(CSlotStatic st, Tab t)
   });
 }
 
-__global__ __launch_bounds__(kUpdThreads) void kb_update(CSlotStatic st, Tab t) {
-  __shared__ int s_pref[kMaxBatch + 1];
+// (one item per block: see kb_wlabel)
+__global__ __launch_bounds__(kUpdThreads) void kb_update(CSlotStatic st, CSlotIO io, Tab t) {
   __shared__ UpdLds L;
-  for_each_item<kUpdThreads>(t, s_pref, [&](int slot, int local) {
-    CEMPPI_SLOT(slot);
-    switch ((c.NM + 1 + kWave - 1) / kWave) {
-      case 1: update_body<1>(c, b, L, local); break;
-      case 2: update_body<2>(c, b, L, local); break;
-      case 3: update_body<3>(c, b, L, local); break;
-      case 4: update_body<4>(c, b, L, local); break;
-      case 5: update_body<5>(c, b, L, local); break;
-      default: update_body<6>(c, b, L, local); break;
-    }
-  });
-}
-
-__global__ __launch_bounds__(kFinThreads) void kb_finish(CSlotStatic st, CSlotIO io, Tab t) {
-  __shared__ int s_pref[kMaxBatch + 1];
-  __shared__ FinLds sh;
-  for_each_item<kFinThreads>(t, s_pref, [&](int slot, int) {
-    CEMPPI_SLOT(slot);
-    const SlotIO& I = *(const SlotIO*)(io + slot);
-    switch ((c.NM + 1 + kWave - 1) / kWave) {
-      case 1: finish_body<1>(c, b, sh, I.u_out, I.U_out, I.info); break;
-      case 2: finish_body<2>(c, b, sh, I.u_out, I.U_out, I.info); break;
-      case 3: finish_body<3>(c, b, sh, I.u_out, I.U_out, I.info); break;
-      case 4: finish_body<4>(c, b, sh, I.u_out, I.U_out, I.info); break;
-      case 5: finish_body<5>(c, b, sh, I.u_out, I.U_out, I.info); break;
-      default: finish_body<6>(c, b, sh, I.u_out, I.U_out, I.info); break;
-    }
-  });
+  int local;
+  const int slot = item_of(t, (int)blockIdx.x, &local);
+  if (slot < 0) return;
+  CEMPPI_SLOT(slot);
+  const SlotIO& I = *(const SlotIO*)(io + slot);
+  switch ((c.NM + 1 + kWave - 1) / kWave) {
+    case 1: update_body<1>(c, b, L, local, I.u_out, I.U_out, I.info); break;
+    case 2: update_body<2>(c, b, L, local, I.u_out, I.U_out, I.info); break;
+    case 3: update_body<3>(c, b, L, local, I.u_out, I.U_out, I.info); break;
+    case 4: update_body<4>(c, b, L, local, I.u_out, I.U_out, I.info); break;
+    case 5: update_body<5>(c, b, L, local, I.u_out, I.U_out, I.info); break;
+    default: update_body<6>(c, b, L, local, I.u_out, I.U_out, I.info); break;
+  }
 }
 #undef CEMPPI_SLOT
 
@@ -3543,7 +3618,7 @@ static void launch_dbscan_p(Launcher& L, const Cfg& c, const Bufs& b, const floa
 // (a graph fork into a clustering and a fallback branch was measured slower:
 // the cross-stream synchronisation of the branches costs more than the
 // overlap saves).
-void launch_post_rollout(Launcher& L, const Cfg& c, const Bufs& b) {
+void launch_post_rollout(Launcher& L, const Cfg& c, const Bufs& b, float* u_out, float* U_out, void* info) {
   const dim3 nk((c.K + kChunk - 1) / kChunk), nt(kFinThreads);
   int* none = nullptr;
   if (c.p == 2) {
@@ -3554,16 +3629,10 @@ void launch_post_rollout(Launcher& L, const Cfg& c, const Bufs& b) {
     L(k_compact<3, false>, nk, nt, c, b);
     launch_dbscan_p<3>(L, c, b, nullptr, 0, c.ntile, none, none, none);
   }
-  using UFn = void (*)(Cfg, Bufs);
+  static_assert(kFinChunks <= 6, "update kernels exist for up to 6 element chunks");
+  using UFn = void (*)(Cfg, Bufs, float*, float*, void*);
   static const UFn upds[6] = {k_update<1>, k_update<2>, k_update<3>, k_update<4>, k_update<5>, k_update<6>};
-  L(upds[(c.NM + 1 + kWave - 1) / kWave - 1], dim3(c.nblk_upd), dim3(kUpdThreads), c, b);
-}
-
-void launch_finish(Launcher& L, const Cfg& c, const Bufs& b, float* u_out, float* U_out, void* info) {
-  static_assert(kFinChunks <= 6, "finish kernels exist for up to 6 element chunks");
-  using FFn = void (*)(Cfg, Bufs, float*, float*, void*);
-  static const FFn fins[6] = {k_finish<1>, k_finish<2>, k_finish<3>, k_finish<4>, k_finish<5>, k_finish<6>};
-  L(fins[(c.NM + 1 + kWave - 1) / kWave - 1], dim3(1), dim3(kFinThreads), c, b, u_out, U_out, info);
+  L(upds[(c.NM + 1 + kWave - 1) / kWave - 1], dim3(c.nblk_upd), dim3(kUpdThreads), c, b, u_out, U_out, info);
 }
 
 void launch_stage_dbscan(Launcher& L, const Cfg& c, const Bufs& b, const float* z, int V,
@@ -3653,8 +3722,7 @@ void launch_batch_post(Launcher& L, const SlotStatic* st, const SlotIO* io, cons
     if (kd == 0) L(kb_tree_cc<2>, dim3(T.grid_lab[0]), dim3(kFinThreads), cst, T.lab[0]);
     else L(kb_tree_cc<3>, dim3(T.grid_lab[1]), dim3(kFinThreads), cst, T.lab[1]);
   }
-  L(kb_update, dim3(T.grid_update), dim3(kUpdThreads), cst, T.update);
-  L(kb_finish, dim3(T.grid_finish), dim3(kFinThreads), cst, cio, T.finish);
+  L(kb_update, dim3(T.grid_update), dim3(kUpdThreads), cst, cio, T.update);
 }
 
 }  // namespace cemppi

@@ -40,12 +40,12 @@ enum PartField {
 
 // DBSCAN tiles: kTile rows (one per thread) x kTile columns (staged in LDS)
 constexpr int kTile = 128;
-// update kernel: candidates per block (16 per wave) and threads; the
-// single-block finisher
-constexpr int kUpdChunk = 64;
-constexpr int kUpdThreads = 256;
+// update kernel: candidates per block (16 per wave) and threads; blocks of the
+// compaction, the labelling and the other single-block passes
+constexpr int kUpdChunk = 128;
+constexpr int kUpdThreads = 512;
 constexpr int kFinThreads = 1024;
-static_assert(kMaxNM <= kFinThreads, "the final combination holds one element per thread");
+static_assert(kMaxNM < kUpdThreads, "the update holds one element and the weight sum per thread");
 // tree graph handled by the fast path
 constexpr int kMaxTrees = 64;
 constexpr int kColGroup = 2;   // column tiles per tree-adjacency block
@@ -117,6 +117,8 @@ struct Ctrl {
   // completion ticket of the window DBSCAN launch (zero between calls), on a
   // line of its own: blocks take tickets while block 0 stores the words above
   alignas(128) int32_t wticket;
+  // and of the update's blocks
+  alignas(128) int32_t uticket;
 };
 
 // Scalar configuration (kernel argument).
@@ -287,8 +289,8 @@ __device__ __forceinline__ int item_of(const Tab& t, int it, int* local) {
 // planners: p = 2 on the sorted distance passes (0), p = 3 (1), p = 2 on the
 // angular windows (2).  Static tables for compaction and for the spatial sort
 // (one item per planner); the DBSCAN tables are filled on the device from each
-// planner's feasible count (PlanOut).  Update and finish run over every planner
-// of the batch.
+// planner's feasible count (PlanOut).  The update runs over every planner of the
+// batch.
 constexpr int kPlanKinds = 3;
 struct PlanOut {
   const int* slot[kPlanKinds];  // planners of each group
@@ -301,9 +303,9 @@ struct PlanOut {
 
 struct BatchTabs {
   Tab compact[kPlanKinds], cnt[kPlanKinds], adj[kPlanKinds], one[kPlanKinds], lab[kPlanKinds];
-  Tab update, finish;
+  Tab update;
   PlanOut plan;
-  int grid_compact[kPlanKinds], grid_one[kPlanKinds], grid_lab[kPlanKinds], grid_update, grid_finish;
+  int grid_compact[kPlanKinds], grid_one[kPlanKinds], grid_lab[kPlanKinds], grid_update;
   int grid_tile;
   int colg;
   int has[kPlanKinds];  // the batch has planners of the group (its phases are launched)
