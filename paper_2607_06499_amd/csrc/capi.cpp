@@ -125,7 +125,7 @@ ce_status validate(const ce_mppi_config* c) {
   return CE_OK;
 }
 
-// Angular windows of the 2-D DBSCAN (cluster.hip, k_wdbscan), in
+// Angular windows of the 2-D DBSCAN (cluster.hip, k_wlabel), in
 // double precision.  Ring points have |z| in [s_lo, s_hi]: the features of
 // Eq. (13) are unit directions scaled by |d| / (|d| + eps_n), so this holds
 // for every feasible rollout whose terminal point is more than about 1 mm
@@ -573,10 +573,10 @@ namespace {
 // host submits it in 17-23 us against 28-32 us for a graph launch, and the device
 // runs it without the graph's own start (us a replan back to back, direct against
 // graph, when it was five: 25.2 and 29.3 at K = 300, 23.6 and 30.2 on the fallback
-// branch at 8,192, 33.7 and 36.1 with clusters, 78 and 83.5 at 65,536).  The seven kernels of the
-// other chains cost the host as much either way (36-41 us, 37 and 36 us a replan
-// at K = 50) and are replayed.  So is every chain on a stream that is being
-// captured.
+// branch at 8,192, 33.7 and 36.1 with clusters, 78 and 83.5 at 65,536).  The seven
+// kernels of the other chains cost the host as much either way (36-41 us, 37 and
+// 36 us a replan at K = 50) and are replayed.  So is every chain on a stream that
+// is being captured.
 bool replay_by_default(const ce_mppi_planner* P, hipStream_t s) {
   if (!(P->c.p == 2 && P->c.dbpath == 0 && P->b.wcnt)) return true;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

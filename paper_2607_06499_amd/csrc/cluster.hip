@@ -9,7 +9,8 @@
 // (neighbour counts, minima, bit ORs); every floating-point reduction that
 // several blocks need is recomputed by each of them from the previous
 // kernel's outputs in a fixed order (so results are deterministic), and the
-// work that needs a single view runs in a one-block kernel.
+// work that needs a single view is done by the block that finishes last (a
+// ticket) or in a one-block kernel.
 //
 // DBSCAN plan (exact, deterministic; V = number of feasible rollouts):
 //  1. count   tiled all-pairs eps-neighbour count -> core flags
@@ -193,7 +194,7 @@ __device__ __forceinline__ Totals decide(const Cfg& c, const float* tot, int bad
 // in ascending rollout order, features z (Eq. (13)) and the DBSCAN arrays.
 // Block 0 publishes the totals.
 // ---------------------------------------------------------------------------
-// Angular buckets of the windowed DBSCAN (k_wdbscan below).  The
+// Angular buckets of the windowed DBSCAN (k_wlabel below).  The
 // bucket coordinate of a feature is its angle mapped to [0, kWinBins]; a
 // ring point has a squared norm within [w_r2lo, w_r2hi]; every other point
 // goes to the extra bucket kWinBins ("off the ring").
@@ -2502,12 +2503,13 @@ __device__ __forceinline__ int win_rank(const WinLds& L, int k) {
 // Block bx of the labelling of V points: the solution over the buckets, then
 // its own chunk (thread t: compacted index a, bucket bka, cost Sa, direction
 // ga); false (for the whole block) where the set needs the general form.  Bound
-// by the instructions of its 16 waves, four to a SIMD (the bucket passes are
-// about 1,200 per wave at every size), then by a chain of about ten barriers;
-// the passes over the points add two LDS updates per 1,024.  Barriers that
-// order LDS only, wave scans on lane moves and one atomic per wave and run in
-// place of __syncthreads(), LDS shuffles and one atomic per bucket: 17.0 to 12.7
-// us at 7,690 points, 37 to 22 us at 62,000.
+// by what one block per CU can overlap: a chain of about ten barriers between
+// dependent steps of some 565 vector, 315 scalar and 75 LDS instructions per wave,
+// 16 waves on four SIMDs (the vector units of its CU issue a third of the time);
+// the passes over the points add two LDS updates per 1,024.  Barriers that order
+// LDS only, wave scans on lane moves and one atomic per wave and run in place of
+// __syncthreads(), LDS shuffles and one atomic per bucket: 17.0 to 12.4 us at
+// 7,690 points, 37 to 20 us at 61,000.
 template <bool POST>
 __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int V, int bx, int t, const WinPoints<POST>& W,
                                          int bka, float Sa, float2 ga, WinLds& L) {
@@ -3624,7 +3626,7 @@ static void launch_dbscan_p(Launcher& L, const Cfg& c, const Bufs& b, const floa
     cnt_out);
 }
 
-// Everything between the rollouts and the final combination, as one chain
+// Everything after the rollouts, as one chain
 // (a graph fork into a clustering and a fallback branch was measured slower:
 // the cross-stream synchronisation of the branches costs more than the
 // overlap saves).

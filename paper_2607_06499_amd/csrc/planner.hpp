@@ -14,7 +14,7 @@
 namespace cemppi {
 
 // Replan as a hipGraph: the whole kernel chain recorded once, the first
-// (rollout) and last (finish) nodes re-pointed when the caller's buffers
+// (rollout) and last (update) nodes re-pointed when the caller's buffers
 // change.
 struct ReplanGraph {
   hipGraph_t graph = nullptr;
