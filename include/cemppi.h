@@ -349,8 +349,8 @@ enum { CE_LAUNCH_GRAPH = 0, CE_LAUNCH_DIRECT = 1 };
  * same bits.  Which is faster depends on the host: a replay costs the device
  * a few microseconds more than the same direct launches, while direct launches
  * cost the host a few microseconds each (see ce_mppi_tune_launch).  A planner
- * whose mode was not set launches the short chain of 2-D features on the
- * angular windows directly and replays the others. */
+ * whose mode was not set launches a short chain (2-D features on the angular
+ * windows; 3-D features up to 256 rollouts) directly and replays the others. */
 ce_status ce_mppi_set_launch_mode(ce_mppi_planner* planner, int32_t mode);
 /* For callers that replan back to back: run `reps` replans on (x_t,
  * obstacles) in each launch mode, timing host wall clock from the first call

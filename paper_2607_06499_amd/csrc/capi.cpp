@@ -25,6 +25,7 @@ void launch_reduce_records(Launcher& L, const Cfg& c, const Bufs& b, const float
 void launch_stage_noise(Launcher& L, const Cfg& c, uint32_t step, uint32_t* words, float* gauss);
 void launch_post_rollout(Launcher& L, const Cfg& c, const Bufs& b, float* u_out, float* U_out, void* info);
 void launch_window_counts(Launcher& L, const Cfg& c, const Bufs& b);
+bool short_chain(const Cfg& c, const Bufs& b);
 void launch_stage_dbscan(Launcher& L, const Cfg& c, const Bufs& b, const float* z, int V,
                          int* ncount, int* label, int* mout);
 }  // namespace cemppi
@@ -569,7 +570,8 @@ void mark_stream(ce_mppi_planner* P, hipStream_t s) {
 
 namespace {
 // Launch mode of a replan whose caller has not set one.  A chain of at most four
-// kernels (2-D features on the angular windows) goes out kernel by kernel: the
+// kernels (2-D features on the angular windows, and small planners of 3-D features,
+// whose compaction and DBSCAN are one kernel) goes out kernel by kernel: the
 // host submits it in 17-23 us against 28-32 us for a graph launch, and the device
 // runs it without the graph's own start (us a replan back to back, direct against
 // graph, when it was five: 25.2 and 29.3 at K = 300, 23.6 and 30.2 on the fallback
@@ -578,7 +580,7 @@ namespace {
 // 36 us a replan at K = 50) and are replayed.  So is every chain on a stream that
 // is being captured.
 bool replay_by_default(const ce_mppi_planner* P, hipStream_t s) {
-  if (!(P->c.p == 2 && P->c.dbpath == 0 && P->b.wcnt)) return true;
+  if (!short_chain(P->c, P->b)) return true;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
     (void)hipGetLastError();

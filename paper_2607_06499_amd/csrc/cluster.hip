@@ -2826,7 +2826,7 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int V, int
       lab = F.lab[bka];
     }
   }
-  if (bx == 0 && t == 0) {
+  if (bx == 0 && t == NT - 1) {  // (the thread that has cleared these words)
     Ctrl* ct = b.ctrl;
     ct->n_trees = nR;
     ct->tree_overflow = 0;
@@ -2952,6 +2952,211 @@ template <bool POST>
 __global__ __launch_bounds__(kFinThreads) void k_wlabel(Cfg c, Bufs b) {
   __shared__ WinLds L;
   wlabel_body<POST>(c, b, (int)blockIdx.x, L);
+}
+
+// ---------------------------------------------------------------------------
+// Compaction and DBSCAN of a small planner in one block (3-D features, at most
+// kSmallK rollouts, the bitmap path): the adjacency bitmap stays in LDS, one
+// 64-bit word per thread (four threads per row), and the steps are those of the
+// bitmap passes: counts, lowest core neighbour, hook trees, their components,
+// labels, statistics.  Trees are linked by a row per core point and tree (mask
+// tests against the tree's members) and a union-find over the roots.
+//
+// Bound by the latency of its steps.  It takes the place of five kernels (17 us in
+// all at K = 50, this one 8.2).  A replan, five kernels against one, us: 35.0 and
+// 24.1 at K = 50, 33.6 and 23.1 at 128 (126 feasible), 40.3 and 29.1 at 256.
+// kSmallK is where a thread has one word of the bitmap; the pair tests grow with
+// V^2 on this one block (16 times as many at 1,024, about 60 us).
+template <int P>
+struct SmallLds {
+  using ZT = typename ZVec<P>::T;
+  ZT z[kSmallK], g[kSmallK];
+  float S[kSmallK];
+  unsigned long long adj[kSmallK / kWave][kSmallK];  // [word][row]
+  unsigned long long tm[kSmallK / kWave][kSmallK];   // members of each tree
+  unsigned long long fmask[kSmallK / kWave], core[kSmallK / kWave], root[kSmallK / kWave], head[kSmallK / kWave];
+  int hook[kSmallK], parent[kSmallK], num[kSmallK];
+  float red[kFinThreads / kWave][kStatClusters][6];
+};
+
+// bits of the words below bit x
+template <int NWD>
+__device__ __forceinline__ int words_rank(const unsigned long long (&w)[NWD], int x) {
+  int r = 0;
+#pragma unroll
+  for (int q = 0; q < NWD; ++q) {
+    const int n = x - q * kWave;
+    r += __popcll(n >= kWave ? w[q] : (n > 0 ? w[q] & ((1ull << n) - 1) : 0ull));
+  }
+  return r;
+}
+
+template <int P>
+__device__ __forceinline__ void small_body(const Cfg& c, const Bufs& b, SmallLds<P>& L) {
+  using ZT = typename ZVec<P>::T;
+  constexpr int NT = kFinThreads, NWD = kSmallK / kWave;
+  static_assert(NT == kSmallK * NWD, "a thread per row and word");
+  __shared__ float s_tot[kPart + 1];
+  __shared__ int s_before;
+  const int t = item_thread(), lane = t & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(t / kWave);
+  const bool in = t < c.K;  // (K <= kSmallK)
+  const int kc = in ? t : c.K - 1;
+  const int bad = b.ctrl->nonfinite;
+  const bool feas = in && !b.col[kc];
+  const float Sk = b.S[kc];
+  float pk[P], gk[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    pk[i] = b.pT[kc * P + i];
+    gk[i] = b.g[kc * P + i];
+  }
+  const bool pub = t == NT - 1;
+  DynIn dyn;
+  if (pub) dyn_ring(c, b, dyn);
+  reduce_partials(c, b, 0, s_tot, &s_before);
+  const Totals T = decide(c, s_tot, bad);
+  if (pub) {
+    dyn_load(c, b, T.branch, dyn);
+    publish_totals(b, T, s_tot);
+    if (T.branch != 0) dyn_publish(c, b, dyn);
+  }
+  if (T.branch != 0) return;
+  const int V = T.nfeas;
+  const unsigned long long fm = __ballot(feas);
+  if (wv < NWD && lane == 0) L.fmask[wv] = fm;
+  if (t < kSmallK) {
+    L.z[t] = ZVec<P>::far();
+    L.num[t] = -1;
+#pragma unroll
+    for (int q = 0; q < NWD; ++q) L.tm[q][t] = 0ull;
+  }
+  lds_sync();
+  if (feas) {
+    const int rank = words_rank<NWD>(L.fmask, t);
+    float d[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) d[i] = pk[i] - T.ref[i];
+    const float den = sqrtf(__builtin_fmaf(d[2], d[2], __builtin_fmaf(d[1], d[1], d[0] * d[0]))) + c.norm_eps;
+    const ZT zz = make_float4(d[0] / den, d[1] / den, d[2] / den, 0.f);
+    const ZT gg = make_float4(gk[0], gk[1], gk[2], 0.f);
+    L.z[rank] = zz;
+    L.g[rank] = gg;
+    L.S[rank] = Sk;
+    reinterpret_cast<ZT*>(b.z)[rank] = zz;
+    reinterpret_cast<ZT*>(b.gv)[rank] = gg;
+    b.vidx[rank] = t;
+    b.Sv[rank] = Sk;
+  }
+  lds_sync();
+  // word q of row r (a wave's threads share q: the columns are broadcast)
+  {
+    const int r = t % kSmallK, q = wv / NWD;
+    unsigned long long m = 0ull;
+    if (q * kWave < V && (r & ~(kWave - 1)) < V) {
+      const ZT zr = L.z[r];
+      const float r2 = c.eps2;
+#pragma unroll 16
+      for (int i = 0; i < kWave; ++i)
+        m |= (unsigned long long)(ZVec<P>::d2(zr, L.z[q * kWave + i]) <= r2 ? 1 : 0) << i;
+      // columns past V are parked far away from the points, not from each other
+      if (r >= V) m = 0ull;
+    }
+    L.adj[q][r] = m;
+  }
+  lds_sync();
+  const bool row = t < V;
+  unsigned long long w[NWD];
+  int n = 0;
+#pragma unroll
+  for (int q = 0; q < NWD; ++q) {
+    w[q] = row ? L.adj[q][t] : 0ull;
+    n += __popcll(w[q]);
+  }
+  const bool core = row && n >= c.min_pts;
+  const unsigned long long cm = __ballot(core);
+  if (wv < NWD && lane == 0) L.core[wv] = cm;
+  lds_sync();
+  int mcn = -1;  // lowest core neighbour
+#pragma unroll
+  for (int q = NWD - 1; q >= 0; --q) {
+    w[q] &= L.core[q];
+    if (w[q]) mcn = q * kWave + __ffsll(w[q]) - 1;
+  }
+  const bool root = core && mcn == t;
+  const unsigned long long rm = __ballot(root);
+  if (wv < NWD && lane == 0) L.root[wv] = rm;
+  if (row) {
+    L.hook[t] = core ? mcn : -1;
+    L.parent[t] = t;
+  }
+  lds_sync();
+  int rt = -1;  // root of the point's tree (core), indices decrease along the hooks
+  if (core) {
+    rt = t;
+    while (true) {
+      const int x = L.hook[rt];
+      if (x == rt) break;
+      rt = x;
+    }
+    atomicOr(&L.tm[t / kWave][rt], 1ull << (t % kWave));
+  }
+  lds_sync();
+  int R = 0;
+#pragma unroll
+  for (int q = 0; q < NWD; ++q) R += __popcll(L.root[q]);
+  if (R > 1) {
+#pragma unroll
+    for (int q = 0; q < NWD; ++q) {
+      unsigned long long rest = L.root[q];
+      while (rest) {  // the same in every thread
+        const int j = q * kWave + __ffsll(rest) - 1;
+        rest &= rest - 1;
+        unsigned long long hit = 0ull;
+#pragma unroll
+        for (int p = 0; p < NWD; ++p) hit |= w[p] & L.tm[p][j];
+        if (core && j != rt && hit) win_union(L.parent, rt, j);
+      }
+    }
+    lds_sync();
+  }
+  // clusters: components by their lowest root
+  const bool head = root && win_find(L.parent, t) == t;
+  const unsigned long long hm = __ballot(head);
+  if (wv < NWD && lane == 0) L.head[wv] = hm;
+  lds_sync();
+  int M = 0;
+#pragma unroll
+  for (int q = 0; q < NWD; ++q) M += __popcll(L.head[q]);
+  if (core) L.num[t] = words_rank<NWD>(L.head, win_find(L.parent, rt));
+  lds_sync();
+  const int lab = mcn >= 0 ? L.num[core ? t : mcn] : -1;
+  const float Sa = row ? L.S[t] : 0.f;
+  const ZT ga = row ? L.g[t] : make_float4(0.f, 0.f, 0.f, 0.f);
+  const bool direct = M > kStatClusters;
+  if (pub) {  // (the thread that has cleared these words)
+    Ctrl* ct = b.ctrl;
+    ct->n_trees = R;
+    ct->tree_overflow = R > kMaxTrees ? 1 : 0;
+    ct->M = M;
+    ct->stat_direct = direct ? 1 : 0;
+    dyn_publish(c, b, dyn);
+  }
+  if (row) {
+    b.label[t] = lab;
+    b.ncount[t] = n;
+  }
+  if (M == 0) return;
+  if (direct) {
+    chunk_stats_many<P>(b, true, M, lab, Sa, ga, L.red);
+    direct_means<P>(c, b, M);
+  } else {
+    chunk_stats<P, true>(b, 0, M, lab, Sa, ga, L.red);
+  }
+}
+
+__global__ __launch_bounds__(kFinThreads) void k_small3(Cfg c, Bufs b) {
+  __shared__ SmallLds<3> L;
+  small_body<3>(c, b, L);
 }
 
 // ---------------------------------------------------------------------------
@@ -3583,6 +3788,12 @@ __global__ __launch_bounds__(kUpdThreads) void kb_update(CSlotStatic st, CSlotIO
 // windows are valid; the no-allocation entry point has no window buffers)
 static bool use_window(const Cfg& c, const Bufs& b) { return c.p == 2 && c.dbpath == 0 && b.wcnt; }
 
+// one block compacts and labels (the bitmap path's planners of 3-D features)
+static bool use_small(const Cfg& c, const Bufs& b) {
+  return c.p == 3 && c.dbpath == 1 && b.adj && c.K <= kSmallK;
+}
+bool short_chain(const Cfg& c, const Bufs& b) { return use_window(c, b) || use_small(c, b); }
+
 template <int P>
 static void launch_dbscan_p(Launcher& L, const Cfg& c, const Bufs& b, const float* zin, int Vin,
                             int ntile, int* lab_out, int* cnt_out, int* mout) {
@@ -3637,6 +3848,8 @@ void launch_post_rollout(Launcher& L, const Cfg& c, const Bufs& b, float* u_out,
     if (!use_window(c, b)) L(k_compact<2, false>, nk, nt, c, b);
     else if (c.K > kPostMaxK) L(k_compact<2, true>, nk, nt, c, b);
     launch_dbscan_p<2>(L, c, b, nullptr, 0, c.ntile, none, none, none);
+  } else if (use_small(c, b)) {
+    L(k_small3, dim3(1), nt, c, b);
   } else {
     L(k_compact<3, false>, nk, nt, c, b);
     launch_dbscan_p<3>(L, c, b, nullptr, 0, c.ntile, none, none, none);

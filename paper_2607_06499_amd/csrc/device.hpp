@@ -73,6 +73,7 @@ constexpr int kWinMaxRuns = 1024;  // runs of core buckets (at most kWinBins / (
 constexpr int kWinPos = 512;  // sorted positions per count-and-place block
 static_assert(kWinMaxK >= kAdjMaxK, "the windowed path covers every planner with a bitmap");
 constexpr int kPostMaxK = 2 * kFinThreads;  // 2-D windows: the labelling blocks compact for themselves up to this size
+constexpr int kSmallK = 256;    // 3-D bitmap planners of at most this size: one block compacts and labels
 constexpr int kLabBatch = 8;   // points per thread per labelling pass
 constexpr int kRecBatch = 4;   // partial records per thread in flight at once
 constexpr int kFinRows = 8;    // update-partial rows per wave in flight at once (final combination)
