@@ -36,6 +36,10 @@
 
 namespace cemppi {
 
+// none(): the row or column of a tile that holds no point (past V, or left out of
+// a pass).  Every comparison of a distance to it is false, whatever the other
+// operand and the radius: a finite parking place is a neighbour of a feature at
+// that place, and of every point once the squared radius overflows.
 template <int P>
 struct ZVec;
 // Morton cell of a feature (points of the unit disc / ball; values outside
@@ -58,8 +62,7 @@ __device__ __forceinline__ unsigned spread3(unsigned v) {  // 4 bits -> every 3r
 template <>
 struct ZVec<2> {
   using T = float2;
-  static __device__ __forceinline__ T far() { return make_float2(1e30f, 1e30f); }
-  static __device__ __forceinline__ T nfar() { return make_float2(-1e30f, -1e30f); }
+  static __device__ __forceinline__ T none() { return make_float2(__builtin_nanf(""), __builtin_nanf("")); }
   static __device__ __forceinline__ float d2(T a, T b) { return dist2_2(a.x, a.y, b.x, b.y); }
   static __device__ __forceinline__ int key(T a) {
     return (int)(spread2((unsigned)morton_q(a.x, 64)) | (spread2((unsigned)morton_q(a.y, 64)) << 1));
@@ -69,8 +72,9 @@ struct ZVec<2> {
 template <>
 struct ZVec<3> {
   using T = float4;
-  static __device__ __forceinline__ T far() { return make_float4(1e30f, 1e30f, 1e30f, 0.f); }
-  static __device__ __forceinline__ T nfar() { return make_float4(-1e30f, -1e30f, -1e30f, 0.f); }
+  static __device__ __forceinline__ T none() {
+    return make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), 0.f);
+  }
   static __device__ __forceinline__ float d2(T a, T b) { return dist2_3(a.x, a.y, a.z, b.x, b.y, b.z); }
   static __device__ __forceinline__ int key(T a) {
     return (int)(spread3((unsigned)morton_q(a.x, 16)) | (spread3((unsigned)morton_q(a.y, 16)) << 1) |
@@ -495,13 +499,13 @@ __device__ __forceinline__ void count_body(const Cfg& c, const Bufs& b, int bx, 
   }
   const ZT* z = reinterpret_cast<const ZT*>(SORTED ? b.zs : (zin ? zin : b.z));
   const int k = I * kTile + r;
-  const ZT zk = k < V ? z[k] : ZVec<P>::far();
+  const ZT zk = k < V ? z[k] : ZVec<P>::none();
   const int ok_k = SORTED ? (k < V ? b.sid[k] : 0) : k;
   ZT zl[COLG];
 #pragma unroll
   for (int u = 0; u < COLG; ++u) {
     const int l = (J0 + u) * kTile + r;
-    zl[u] = (q == 0 && J0 + u < J1 && l < V) ? z[l] : ZVec<P>::far();
+    zl[u] = (q == 0 && J0 + u < J1 && l < V) ? z[l] : ZVec<P>::none();
   }
   const float r2 = c.eps2;
   int cnt = 0;  // this split's count
@@ -523,7 +527,6 @@ __device__ __forceinline__ void count_body(const Cfg& c, const Bufs& b, int bx, 
     if (block_and<NT>(k >= V || tot >= c.min_pts, s_all)) break;
     if (q == 0) s_z[r] = zl[u];
     __syncthreads();
-    // (columns past V are parked far away; the rows there count nothing)
 #pragma unroll 16
     for (int t = q * SPAN; t < (q + 1) * SPAN; ++t) cnt += ZVec<P>::d2(zk, s_z[t]) <= r2 ? 1 : 0;
   }
@@ -577,7 +580,7 @@ __device__ __forceinline__ void mcn_body(const Cfg& c, const Bufs& b, int bx, in
   const int J1 = min(J0 + COLG, nt);
   const ZT* z = reinterpret_cast<const ZT*>(zin ? zin : b.z);
   const int k = I * kTile + r;
-  const ZT zk = k < V ? z[k] : ZVec<P>::far();
+  const ZT zk = k < V ? z[k] : ZVec<P>::none();
   const bool diag = J0 <= I && I < J1;
   // (agent scope: what the blocks of lower columns have found so far)
   const int have = k < V ? __hip_atomic_load(&b.mcn[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
@@ -588,7 +591,7 @@ __device__ __forceinline__ void mcn_body(const Cfg& c, const Bufs& b, int bx, in
   for (int u = 0; u < COLG; ++u) {
     const int l = (J0 + u) * kTile + r;
     const bool ok = q == 0 && J0 + u < J1 && l < V;
-    zl[u] = ok ? z[l] : ZVec<P>::far();
+    zl[u] = ok ? z[l] : ZVec<P>::none();
     ncl[u] = ok ? b.ncount[l] : 0;
   }
   if (diag && q == 0) {
@@ -618,10 +621,10 @@ __device__ __forceinline__ void mcn_body(const Cfg& c, const Bufs& b, int bx, in
     if (J >= J1) break;
     const int mm = row_min();
     if (block_and<NT>(k >= V || mm != kInt32Max, s_all)) break;
-    // non-core columns are parked far away: they can never be a neighbour here
-    if (q == 0) s_z[r] = ncl[u] >= c.min_pts ? zl[u] : ZVec<P>::far();
+    // (non-core columns are nobody's neighbours here)
+    if (q == 0) s_z[r] = ncl[u] >= c.min_pts ? zl[u] : ZVec<P>::none();
     __syncthreads();
-    // 32 columns at a time (past V they are parked too), descending, so that the
+    // 32 columns at a time, descending, so that the
     // last assignment is the lowest hit; a wave stops once its rows have one
     for (int t0 = q * SPAN; t0 < (q + 1) * SPAN; t0 += 32) {
       if (__ballot(k < V && m == kInt32Max) == 0ull) break;
@@ -772,7 +775,7 @@ __device__ __forceinline__ void tree_adj_body(const Cfg& c, const Bufs& b, int b
   // positions first, then the per-point arrays at the original indices)
   const int k = I * kTile + r;
   const int idk = SORTED ? (k < V ? b.sid[k] : 0) : k;
-  const ZT zk0 = k < V ? z[k] : ZVec<P>::far();
+  const ZT zk0 = k < V ? z[k] : ZVec<P>::none();
   int idl[kColGroup], ncl[kColGroup], rl[kColGroup];
   ZT zl[kColGroup];
 #pragma unroll
@@ -780,7 +783,7 @@ __device__ __forceinline__ void tree_adj_body(const Cfg& c, const Bufs& b, int b
     const int l = (J0 + u) * kTile + r;
     const bool ok = q == 0 && J0 + u < J1 && l < V;
     idl[u] = ok ? (SORTED ? b.sid[l] : l) : -1;
-    zl[u] = ok ? z[l] : ZVec<P>::far();
+    zl[u] = ok ? z[l] : ZVec<P>::none();
   }
   const int nck = k < V ? b.ncount[idk] : 0;
   const int hk = k < V ? b.mcn[idk] : -1;
@@ -805,7 +808,7 @@ __device__ __forceinline__ void tree_adj_body(const Cfg& c, const Bufs& b, int b
   if (R < 2 || R > kMaxTrees) return;
   if (threadIdx.x < kMaxTrees) s_adj[threadIdx.x] = 0ull;
   const int tk = nck >= c.min_pts ? tree_id(s_rm, s_woff, rk) : -1;
-  const ZT zk = tk >= 0 ? zk0 : ZVec<P>::far();
+  const ZT zk = tk >= 0 ? zk0 : ZVec<P>::none();
   const float r2 = c.eps2;
   uint32_t mlo = 0u, mhi = 0u;
 #pragma unroll
@@ -816,14 +819,13 @@ __device__ __forceinline__ void tree_adj_body(const Cfg& c, const Bufs& b, int b
     const int tl = ncl[u] >= c.min_pts ? tree_id(s_rm, s_woff, rl[u]) : -1;
     __syncthreads();
     if (q == 0) {
-      s_z[r] = tl >= 0 ? zl[u] : ZVec<P>::far();
+      s_z[r] = tl >= 0 ? zl[u] : ZVec<P>::none();
       s_bit[r] = tl < 0 ? make_uint2(0u, 0u)
                         : (tl < 32 ? make_uint2(1u << tl, 0u) : make_uint2(0u, 1u << (tl - 32)));
     }
     __syncthreads();
     if (tk >= 0) {
-      // branch-free: both LDS words are read for every column (columns past V are
-      // parked far away)
+      // branch-free: both LDS words are read for every column
 #pragma unroll 16
       for (int t = q * SPAN; t < (q + 1) * SPAN; ++t) {
         const uint2 bt = s_bit[t];
@@ -887,14 +889,12 @@ __global__ __launch_bounds__(kTile * CS) void k_adj(Cfg c, Bufs b, const float* 
   const ZT* z = reinterpret_cast<const ZT*>(zin ? zin : b.z);
   const size_t stride = (size_t)c.ntile * kTile;
   const int k = I * kTile + r;
-  // rows past V sit at +1e30, columns past V at -1e30: no pair with either
-  // is a hit (the squared distance overflows to infinity)
-  const ZT zk = k < V ? z[k] : ZVec<P>::far();
+  const ZT zk = k < V ? z[k] : ZVec<P>::none();
   ZT zl[COLG];
 #pragma unroll
   for (int u = 0; u < COLG; ++u) {
     const int l = (J0 + u) * kTile + r;
-    zl[u] = (q == 0 && J0 + u < J1 && l < V) ? z[l] : ZVec<P>::nfar();
+    zl[u] = (q == 0 && J0 + u < J1 && l < V) ? z[l] : ZVec<P>::none();
   }
   const float r2 = c.eps2;
   int cnt = 0;
@@ -2424,7 +2424,7 @@ __device__ __forceinline__ void win_general(const Cfg& c, const Bufs& b, int V, 
         for (int e = e0; e < e1; e += 4) {
           float2 zq[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) zq[u] = e + u < e1 ? z[lst[e + u]] : make_float2(1e30f, 1e30f);
+          for (int u = 0; u < 4; ++u) zq[u] = e + u < e1 ? z[lst[e + u]] : ZVec<2>::none();
 #pragma unroll
           for (int u = 0; u < 4; ++u) n += ZVec<2>::d2(zk, zq[u]) <= r2 ? 1 : 0;
         }
@@ -3025,7 +3025,7 @@ __device__ __forceinline__ void small_body(const Cfg& c, const Bufs& b, SmallLds
   const unsigned long long fm = __ballot(feas);
   if (wv < NWD && lane == 0) L.fmask[wv] = fm;
   if (t < kSmallK) {
-    L.z[t] = ZVec<P>::far();
+    L.z[t] = ZVec<P>::none();
     L.num[t] = -1;
 #pragma unroll
     for (int q = 0; q < NWD; ++q) L.tm[q][t] = 0ull;
@@ -3058,8 +3058,6 @@ __device__ __forceinline__ void small_body(const Cfg& c, const Bufs& b, SmallLds
 #pragma unroll 16
       for (int i = 0; i < kWave; ++i)
         m |= (unsigned long long)(ZVec<P>::d2(zr, L.z[q * kWave + i]) <= r2 ? 1 : 0) << i;
-      // columns past V are parked far away from the points, not from each other
-      if (r >= V) m = 0ull;
     }
     L.adj[q][r] = m;
   }
