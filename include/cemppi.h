@@ -245,7 +245,10 @@ enum {
   CE_DBG_COUNT_ = 15
 };
 /* Copy the named buffer into device memory dst of `bytes` bytes (at most the
- * buffer's full capacity is copied; rows beyond |V| or M are unspecified). */
+ * buffer's full capacity is copied; rows beyond |V| or M are unspecified).
+ * Nothing that a replan or a stage call uses is written.  (CE_DBG_NCOUNT of a
+ * planner that has the angular windows first completes the last call's counts
+ * in an array of its own, by a kernel on `stream`.) */
 ce_status ce_mppi_debug_get(const ce_mppi_planner* planner, int32_t which, void* dst, size_t bytes,
                             void* stream);
 

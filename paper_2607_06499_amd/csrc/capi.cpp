@@ -24,7 +24,7 @@ void launch_reduce_records(Launcher& L, const Cfg& c, const Bufs& b, const float
                            const float* obs, int n_obs);
 void launch_stage_noise(Launcher& L, const Cfg& c, uint32_t step, uint32_t* words, float* gauss);
 void launch_post_rollout(Launcher& L, const Cfg& c, const Bufs& b, float* u_out, float* U_out, void* info);
-void launch_window_counts(Launcher& L, const Cfg& c, const Bufs& b);
+void launch_open_counts(Launcher& L, const Cfg& c, const Bufs& b);
 bool short_chain(const Cfg& c, const Bufs& b);
 void launch_stage_dbscan(Launcher& L, const Cfg& c, const Bufs& b, const float* z, int V,
                          int* ncount, int* label, int* mout);
@@ -387,6 +387,7 @@ ce_status ce_mppi_create(const ce_mppi_config* cfg, ce_mppi_planner** out) {
   const size_t o_wuf = cv.take<int>(with_win ? 3 * (kWinMaxRuns + K) : 0);
   // (one region of K indices per block of the count pass, 512 positions each)
   const size_t o_wzone = cv.take<int>(with_win ? (K + kWinPos - 1) / kWinPos * K : 0);
+  const size_t o_dcnt = cv.take<int>(wk);
   const size_t o_stat = cv.take<float>((K + kChunk - 1) / kChunk * kStatClusters * kStatFields);
   const size_t o_ccost = cv.take<float>((size_t)c.mcap), o_cdir = cv.take<float>((size_t)c.mcap * 4);
   const size_t o_csize = cv.take<int>((size_t)c.mcap), o_csmin = cv.take<float>((size_t)c.mcap);
@@ -435,6 +436,7 @@ ce_status ce_mppi_create(const ce_mppi_config* cfg, ce_mppi_planner** out) {
   b.wnc = with_win ? reinterpret_cast<int*>(base + o_wnc) : nullptr;
   b.wuf = with_win ? reinterpret_cast<int*>(base + o_wuf) : nullptr;
   b.wzone = with_win ? reinterpret_cast<int*>(base + o_wzone) : nullptr;
+  b.dcount = with_win ? reinterpret_cast<int*>(base + o_dcnt) : nullptr;
   b.stat = reinterpret_cast<float*>(base + o_stat);
   b.c_cost = reinterpret_cast<float*>(base + o_ccost);
   b.c_dir = reinterpret_cast<float*>(base + o_cdir);
@@ -1068,11 +1070,14 @@ ce_status ce_mppi_debug_get(const ce_mppi_planner* P, int32_t which, void* dst, 
     case CE_DBG_Z: src = b.z; cap = K * p * 4; if (p == 3) { rows = K; src_pitch = 16; } break;
     case CE_DBG_G: src = b.gv; cap = K * p * 4; if (p == 3) { rows = K; src_pitch = 16; } break;
     case CE_DBG_NCOUNT: {
-      Launcher L(S(stream));
-      launch_window_counts(L, c, b);
-      if (L.err != hipSuccess) return hip_fail(L.err, "debug_get counts");
       src = b.ncount;
       cap = K * 4;
+      if (b.dcount && bytes) {
+        Launcher L(S(stream));
+        launch_open_counts(L, c, b);
+        if (L.err != hipSuccess) return hip_fail(L.err, "debug_get counts");
+        src = b.dcount;
+      }
       break;
     }
     case CE_DBG_LABEL: src = b.label; cap = K * 4; break;

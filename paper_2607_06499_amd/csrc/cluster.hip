@@ -215,7 +215,9 @@ __device__ __forceinline__ int win_bin(const Cfg& c, float2 zz) {
   return win_ring(c, zz) ? win_bucket(win_u(c, zz)) : kWinBins;
 }
 
-// What a replan's later kernels need of the totals (one thread).
+// What a replan's later kernels need of the totals (one thread).  WIN: the
+// labels come from the angular windows.
+template <bool WIN>
 __device__ __forceinline__ void publish_totals(const Bufs& b, const Totals& T, const float* tot) {
   Ctrl* ct = b.ctrl;
   ct->n_col = T.ncol;
@@ -229,6 +231,7 @@ __device__ __forceinline__ void publish_totals(const Bufs& b, const Totals& T, c
   ct->n_trees = 0;
   ct->tree_overflow = 0;
   ct->stat_direct = 0;
+  if (T.branch == 0) ct->open_V = WIN ? T.nfeas : 0;
   ct->sel = -1;
   for (int i = 0; i < 3; ++i) ct->ref[i] = T.ref[i];
 }
@@ -314,7 +317,7 @@ __device__ __forceinline__ void compact_body(const Cfg& c, const Bufs& b, int bx
   const Totals T = decide(c, s_tot, bad);
   if (pub) {
     dyn_load(c, b, T.branch, dyn);
-    publish_totals(b, T, s_tot);
+    publish_totals<BIN>(b, T, s_tot);
     if (T.branch != 0) dyn_publish(c, b, dyn);
   }
   if (T.branch != 0) return;
@@ -362,6 +365,7 @@ __global__ __launch_bounds__(kFinThreads) void k_compact(Cfg c, Bufs b) {
 __global__ void k_init_points(Bufs b, int V) {
   const int a = blockIdx.x * 256 + threadIdx.x;
   if (a >= V) return;
+  if (a == 0) b.ctrl->open_V = 0;
   b.ncount[a] = 0;
   b.mcn[a] = kInt32Max;
   b.root[a] = -1;
@@ -1447,8 +1451,9 @@ __global__ __launch_bounds__(kFinThreads) void k_tree_cc(Cfg c, Bufs b, const fl
 //  between the two bounds, many open or off-ring points, many clusters) take
 //  the general form in the same launch: each block counts its own points
 //  exactly and the last block to finish forms the components and labels.
-//  Stage calls and the neighbour-count diagnostics, which report exact counts
-//  of every point, use the sorted count-and-place pass (wcount_body).
+//  Stage calls, which report exact counts of every point, use the sorted
+//  count-and-place pass (wcount_body); those of a replan are made when a
+//  diagnostic read asks for them (k_open_counts).
 // Work: O(V) bucket lookups and O(V * points of the boundary buckets) tests
 // at most, against V^2 / 2 pair tests for the bitmap; one launch instead of
 // four.
@@ -1498,7 +1503,7 @@ __device__ __forceinline__ bool win_in(int j, int lo, int hi) { return hi >= lo 
 
 constexpr int kWinZone = 4096;    // zone points a count block keeps in LDS
 
-// Counts and the sorted order (stage calls and diagnostics).  Block i takes the sorted positions
+// Counts and the sorted order (stage calls).  Block i takes the sorted positions
 // [i POS, i POS + POS) (sorted by bucket, then slot; off-ring points last),
 // two threads per position.
 //  - every block scans the bucket counts into LDS (block 0 publishes them);
@@ -2303,27 +2308,42 @@ __global__ __launch_bounds__(kFinThreads) void k_wdbscan(Cfg c, Bufs b, const fl
 }
 
 // bucket and slot of every point: the slot is its arrival order in the bucket
-// (any order serves: no result depends on it); zin null: the features of the
-// last replan
-__global__ __launch_bounds__(256) void k_wbin(Cfg c, Bufs b, const float* __restrict__ zin, int Vin) {
+// (any order serves: no result depends on it)
+__global__ __launch_bounds__(256) void k_wbin(Cfg c, Bufs b, const float* __restrict__ zin, int V) {
   const int a = (int)blockIdx.x * 256 + (int)threadIdx.x;
-  if (a >= dbscan_V(b, zin, Vin)) return;
-  const int bkt = win_bin(c, reinterpret_cast<const float2*>(zin ? zin : b.z)[a]);
+  if (a >= V) return;
+  const int bkt = win_bin(c, reinterpret_cast<const float2*>(zin)[a]);
   const int slot = atomicAdd(&b.wcnt[bkt], 1);
   b.wkey[a] = (bkt << kWinShift) | slot;
 }
 
-// exact counts of the last replan's features, and the cleared bucket arrays
-// (diagnostics)
-__global__ __launch_bounds__(kFinThreads) void k_wcount(Cfg c, Bufs b) {
-  const int V = dbscan_V(b, nullptr, 0);
-  if ((int)blockIdx.x * kWinPos >= V) return;
-  wcount_body(c, b, nullptr, V, (int)blockIdx.x);
-}
-__global__ __launch_bounds__(256) void k_wclear(Bufs b) {
-  const int i = (int)blockIdx.x * 256 + (int)threadIdx.x;
-  if (i <= kWinBins) b.wcnt[i] = 0;
-  if (i < kWinBins) b.wbmin[i] = 0;
+// Neighbour counts for a diagnostic read: exact ones of the points whose counts
+// the window labelling left open, as stored for the others.  Every pair of
+// features, a column tile at a time from LDS.  It reads what the last call left
+// and writes only dcount, so a replan before, beside or after it is not affected.
+// (One thread reads the number of points: a replan beside it may change the word,
+// and the barriers need one value in the block.)
+__global__ __launch_bounds__(256) void k_open_counts(Cfg c, Bufs b) {
+  __shared__ float2 s_z[256];
+  __shared__ int s_V;
+  const int t = (int)threadIdx.x, a = (int)blockIdx.x * 256 + t;
+  if (t == 0) s_V = min(b.ctrl->open_V, c.K);
+  __syncthreads();
+  const int V = s_V;
+  const float2* z = reinterpret_cast<const float2*>(b.z);
+  if ((int)blockIdx.x * 256 < V) {
+    const float2 za = a < V ? z[a] : ZVec<2>::none();
+    int n = 0;
+    for (int l0 = 0; l0 < V; l0 += 256) {
+      __syncthreads();
+      s_z[t] = l0 + t < V ? z[l0 + t] : ZVec<2>::none();
+      __syncthreads();
+#pragma unroll 16
+      for (int l = 0; l < 256; ++l) n += ZVec<2>::d2(za, s_z[l]) <= c.eps2 ? 1 : 0;
+    }
+    if (a < V) b.dcount[a] = n;
+  }
+  if (a >= V && a < c.K) b.dcount[a] = b.ncount[a];
 }
 
 // ---------------------------------------------------------------------------
@@ -2879,7 +2899,7 @@ __device__ __forceinline__ void wlabel_body(const Cfg& c, const Bufs& b, int bx,
     const Totals T = decide(c, s_tot, bad);
     if (pub) {
       dyn_load(c, b, T.branch, dyn);
-      publish_totals(b, T, s_tot);
+      publish_totals<true>(b, T, s_tot);
       if (T.branch != 0) dyn_publish(c, b, dyn);
     }
     V = T.branch == 0 ? T.nfeas : 0;
@@ -3017,7 +3037,7 @@ __device__ __forceinline__ void small_body(const Cfg& c, const Bufs& b, SmallLds
   const Totals T = decide(c, s_tot, bad);
   if (pub) {
     dyn_load(c, b, T.branch, dyn);
-    publish_totals(b, T, s_tot);
+    publish_totals<false>(b, T, s_tot);
     if (T.branch != 0) dyn_publish(c, b, dyn);
   }
   if (T.branch != 0) return;
@@ -3881,14 +3901,11 @@ void launch_stage_dbscan(Launcher& L, const Cfg& c, const Bufs& b, const float* 
 }
 
 
-// Exact neighbour counts of the last replan's features on the window path
-// (diagnostics: a replan only needs the core flags, and leaves the counts of
-// core points anywhere between minPts and the count).
-void launch_window_counts(Launcher& L, const Cfg& c, const Bufs& b) {
-  if (!use_window(c, b)) return;
-  L(k_wbin, dim3((c.K + 255) / 256), dim3(256), c, b, (const float*)nullptr, 0);
-  L(k_wcount, dim3((c.K + kWinPos - 1) / kWinPos), dim3(kFinThreads), c, b);
-  L(k_wclear, dim3((kWinBins + 256) / 256), dim3(256), b);
+// Neighbour counts of a planner that has the window path, into dcount
+// (diagnostics: a replan there only needs the core flags, and leaves the counts
+// of core points anywhere between minPts and the count).
+void launch_open_counts(Launcher& L, const Cfg& c, const Bufs& b) {
+  L(k_open_counts, dim3((c.K + 255) / 256), dim3(256), c, b);
 }
 
 template <int P>

@@ -115,6 +115,7 @@ struct Ctrl {
   uint32_t status;
   uint32_t step_used;
   int32_t stat_direct;  // the cluster arrays hold the final statistics (more than kStatClusters clusters)
+  int32_t open_V;  // points whose counts in ncount the window labelling left open above minPts (0: none)
   // completion ticket of the window DBSCAN launch (zero between calls), on a
   // line of its own: blocks take tickets while block 0 stores the words above
   alignas(128) int32_t wticket;
@@ -213,6 +214,7 @@ struct Bufs {
   int* wuf;        // [3][kWinMaxRuns + K] union-find parents, component minima, off-ring labels
   int* wzone;      // [ceil(K / kWinPos)][K] indices of a count block's zone when it exceeds LDS; in
                    // replans, a labelling block's point list in bucket order (16-bit, K per block)
+  int* dcount;     // [K] exact counts for a diagnostic read (window planners); no replan or stage call uses it
   float* upart;    // [nblk_upd][NM + 1]
   float* Unew;     // [N][m] updated sequence before the shift
 };
