@@ -466,7 +466,8 @@ ce_status ce_mppi_batch_get_tuning(const ce_mppi_batch* batch, ce_mppi_batch_tun
 
 /* Project-written autotuner: times `reps` batch replans on io per candidate
  * shape, first the rollout shape (rollouts per wave in {1,2,4,8} x rollout
- * blocks per CU in {2,4}), then the DBSCAN shape (colg in {2,4,8} x tile
+ * blocks per CU in {2,4}; kept as set in a batch without arms, whose replans do
+ * not depend on it), then the DBSCAN shape (colg in {2,4,8} x tile
  * blocks per CU in {4,8,16}); keeps the fastest and returns it with its mean
  * time per batch replan.  Results do not depend on the shape: every member's
  * output is bitwise the same under every tuning.  The members' states are saved before and

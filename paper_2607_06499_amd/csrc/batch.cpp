@@ -504,10 +504,14 @@ ce_status ce_mppi_batch_autotune(ce_mppi_batch* B, const ce_mppi_batch_io* io, i
   double win_ms = 1e300;
   ce_status result = CE_OK;
   // stage 1: rollout shape with the current DBSCAN shape; stage 2: DBSCAN
-  // shape with the best rollout shape
+  // shape with the best rollout shape.  (A full replan gives every unicycle
+  // item a block of its own, so without arms there is nothing to choose from:
+  // the times would differ by noise alone, and the blocks per CU picked by it
+  // would act on subset launches.)
   std::vector<ce_mppi_batch_tuning> cand;
-  for (int r : {1, 2, 4, 8})
-    for (int rb : {2, 4}) cand.push_back({start.colg, start.tile_blocks_per_cu, rb, r});
+  if (B->has_roll[1])
+    for (int r : {1, 2, 4, 8})
+      for (int rb : {2, 4}) cand.push_back({start.colg, start.tile_blocks_per_cu, rb, r});
   for (int stage = 0; stage < 2 && result == CE_OK; ++stage) {
     if (stage == 1) {
       cand.clear();

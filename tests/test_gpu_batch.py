@@ -230,3 +230,21 @@ def test_batch_large_window_members_match_single():
             fields[i].step(scenes[i].spec.dt)
     assert clustered >= 2
     batch.close()
+
+
+def test_autotune_without_arms_keeps_the_rollout_shape():
+    """A full replan of unicycles does not depend on the rollout shape, so the
+    tuner has nothing to choose it by: what the caller set (here outside the
+    shapes it tries) stays in force for the subset launches."""
+    from paper_2607_06499_amd import binding as B
+
+    scenes = [m() for m in (MEMBERS[0], MEMBERS[2], MEMBERS[8])]
+    pls = [B.Planner(s.spec) for s in scenes]
+    batch = B.Batch(pls)
+    batch.set_io([H.to_dev(np.asarray(s.x0, np.float32)) for s in scenes],
+                 [H.to_dev(np.asarray(s.obstacles, np.float32)) for s in scenes])
+    batch.set_tuning(4, 16, 3, 2)
+    best, ms = batch.autotune(reps=2)
+    assert (best["roll_blocks_per_cu"], best["roll_per_wave"]) == (3, 2) and ms > 0.0
+    assert batch.get_tuning() == best
+    batch.close()
