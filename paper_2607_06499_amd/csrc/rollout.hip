@@ -648,6 +648,12 @@ __global__ __launch_bounds__(kUniThreads + kWave) void k_rollout_unicycle(Cfg c,
 // obstacles, N = 32); this takes 12.5 and 33.0 us.  Bound by VALU issue in large
 // launches (half of it the contacts), by one wave's chain in small ones.
 constexpr int kArmSpheres = 8;
+// Up to this many blocks (two on each of the 256 CUs) a launch has a wave of its
+// own for the prologue; in larger ones three blocks of eight waves on a CU are
+// worth more than two of nine.  Measured with / without, us: K = 4,096 12.8 / 13.7,
+// 8,192 16.1 / 16.5, 12,000 24.9 / 21.3, 65,536 123 / 87.  (The rollouts are the
+// same work in both, so on a part with fewer CUs the line only costs time.)
+constexpr int kArmExtraBlocks = 512;
 template <int SEG, int R, bool EXTRA>
 __device__ __forceinline__ void rollout_arm_body(const Cfg& c, const Bufs& b, int bx,
                                                  const float* __restrict__ x_t,
@@ -950,11 +956,7 @@ void launch_rollout(Launcher& L, const Cfg& c, const Bufs& b, const float* x_t, 
 #undef CEMPPI_UNI
     }
   } else {
-    // A wave of its own for the prologue while the blocks fit the chip twice;
-    // in larger launches three blocks of eight waves on a CU are worth more
-    // than two of nine.  Measured with / without, us: K = 4,096 12.8 / 13.7,
-    // 8,192 16.1 / 16.5, 12,000 24.9 / 21.3, 65,536 123 / 87.
-    if (c.nblk_roll <= 512)
+    if (c.nblk_roll <= kArmExtraBlocks)
       L(c.seg == 32 ? k_rollout_arm<32, true> : k_rollout_arm<64, true>, grid, dim3(kRollThreads + kWave), c, b, x_t, obs,
         n_obs);
     else

@@ -97,3 +97,16 @@ def test_arm_sphere_groups_match_oracle(ns, n_obs, N, K, pose):
     o = oracle.replan(s.spec, s.x0, s.U0, obs, hist)
     P._compare_rollouts(r, o, s.spec)
     pl.close()
+
+
+# either side of the number of blocks up to which the prologue has a wave of its
+# own, for both segment widths (16 rollouts a block for N <= 32, 8 beyond)
+@pytest.mark.parametrize("N,K", [(12, 8192), (12, 8193), (32, 8201), (33, 4096), (33, 4097), (63, 4111)])
+def test_arm_launch_sizes_match_oracle(N, K):
+    s = W.random_scene(500 + N, dynamics=W.ARM6, num_samples=K, horizon=N, n_obs=9)
+    pl = P._planner(s.spec)
+    P._set_U(pl, s.U0)
+    r = H.gpu_replan(pl, s.x0, s.obstacles)
+    o = oracle.replan(s.spec, s.x0, s.U0, s.obstacles)
+    P._compare_rollouts(r, o, s.spec)
+    pl.close()
