@@ -580,7 +580,8 @@ namespace {
 // branch at 8,192, 33.7 and 36.1 with clusters, 78 and 83.5 at 65,536).  The seven
 // kernels of the other chains cost the host as much either way (36-41 us, 37 and
 // 36 us a replan at K = 50) and are replayed.  So is every chain on a stream that
-// is being captured.
+// is being captured (the replay goes out at once; only CE_LAUNCH_DIRECT is
+// captured).
 bool replay_by_default(const ce_mppi_planner* P, hipStream_t s) {
   if (!short_chain(P->c, P->b)) return true;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

@@ -51,3 +51,54 @@ def test_unset_mode_agrees(mk, bitmap):
         for a, b in zip(out[0], r):
             for q in range(3):
                 assert np.array_equal(a[q], b[q])
+
+
+@pytest.mark.parametrize("mk", [lambda: W.unicycle_static_ahead(3, num_samples=1024), lambda: W.arm6_dynamic(3, 700)],
+                         ids=["short_chain", "long_chain"])
+def test_replan_on_a_capturing_stream(mk):
+    """A planner without a set mode does on a stream under capture what it does
+    in graph mode, on chains on either side of the rule; in direct mode the
+    kernels are captured, and every replay is the next step.  Eager replans and
+    synchronisations between the replays, each result against a planner that was
+    never captured."""
+    from paper_2607_06499_amd import binding as B
+
+    torch = H.torch_mod()
+    s = mk()
+    x, obs = H.to_dev(np.asarray(s.x0, np.float32)), H.to_dev(np.asarray(s.obstacles, np.float32))
+    steps = {}
+    ref = B.Planner(s.spec)
+    ref.set_nominal(torch.as_tensor(s.U0).cuda())
+    want = []
+    for _ in range(8):
+        ref.replan(x, obs)
+        torch.cuda.synchronize()
+        want.append((ref.u_out.cpu().numpy().copy(), ref.U_out.cpu().numpy().copy(), ref.info_buf.cpu().numpy().copy()))
+    ref.close()
+    for mode in (None, B.LAUNCH_GRAPH, B.LAUNCH_DIRECT):
+        pl = B.Planner(s.spec)
+        if mode is not None:
+            pl.set_launch_mode(mode)
+        pl.set_nominal(torch.as_tensor(s.U0).cuda())
+        torch.cuda.synchronize()
+        st, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.stream(st):
+            g.capture_begin()
+            pl.replan(x, obs, stream=st)
+            g.capture_end()
+        torch.cuda.synchronize()
+        seen = []
+        for call in range(5):
+            if call % 2 == 0:
+                g.replay()
+            else:
+                pl.replan(x, obs, stream=st)
+            torch.cuda.synchronize()
+            step = pl.info()["step"]
+            seen.append(step)
+            for a, b in zip((pl.u_out, pl.U_out, pl.info_buf), want[step]):
+                assert np.array_equal(a.cpu().numpy(), b), (mode, call, step)
+        steps[mode] = seen
+        pl.close()
+    assert steps[None] == steps[B.LAUNCH_GRAPH], steps
+    assert steps[B.LAUNCH_DIRECT] == [0, 1, 2, 3, 4], steps
