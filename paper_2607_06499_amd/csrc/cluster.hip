@@ -230,7 +230,6 @@ __device__ __forceinline__ void publish_totals(const Bufs& b, const Totals& T, c
   ct->M = 0;
   ct->n_trees = 0;
   ct->tree_overflow = 0;
-  ct->stat_direct = 0;
   if (T.branch == 0) ct->open_V = WIN ? T.nfeas : 0;
   ct->sel = -1;
   for (int i = 0; i < 3; ++i) ct->ref[i] = T.ref[i];
@@ -1377,7 +1376,6 @@ __device__ __forceinline__ void tree_cc_body(const Cfg& c, const Bufs& b, int bx
     ct->n_trees = R;
     ct->tree_overflow = overflow ? 1 : 0;
     ct->M = M;
-    ct->stat_direct = direct ? 1 : 0;
     if (mout) *mout = M;
   }
   // labels: core -> cluster of its tree (or component), border -> cluster of
@@ -2179,7 +2177,6 @@ __device__ __forceinline__ void wcc_body(const Cfg& c, const Bufs& b, const floa
     ct->n_trees = nR;
     ct->tree_overflow = 0;
     ct->M = M;
-    ct->stat_direct = direct ? 1 : 0;
     if (mout) *mout = M;
   }
   __syncthreads();
@@ -2388,14 +2385,6 @@ struct WinLds {
     WccLds cc;
   };
 };
-
-__device__ __forceinline__ int lds_find(int* parent, int x) {
-  while (true) {
-    const int p = ld_wg(&parent[x]);
-    if (p == x) return x;
-    x = p;
-  }
-}
 
 // ring points of the buckets lo..hi (unwrapped, at most kWinBins of them)
 __device__ __forceinline__ int win_npts(const int* start, int lo, int hi) {
@@ -2851,7 +2840,6 @@ __device__ __forceinline__ bool win_fast(const Cfg& c, const Bufs& b, int V, int
     ct->n_trees = nR;
     ct->tree_overflow = 0;
     ct->M = M;
-    ct->stat_direct = 0;
   }
   if (M > 0) chunk_stats<2, true>(b, bx, M, lab, Sa, ga, F.red);
   if (own) {
@@ -3156,7 +3144,6 @@ __device__ __forceinline__ void small_body(const Cfg& c, const Bufs& b, SmallLds
     ct->n_trees = R;
     ct->tree_overflow = R > kMaxTrees ? 1 : 0;
     ct->M = M;
-    ct->stat_direct = direct ? 1 : 0;
     dyn_publish(c, b, dyn);
   }
   if (row) {
@@ -3197,7 +3184,7 @@ __device__ __forceinline__ ClusterStat cluster_stats(const Cfg& c, const Bufs& b
   r.cost = r.smin = INFINITY;
   r.dir = make_float4(0.f, 0.f, 0.f, 0.f);
   const int t = item_thread();
-  if (M > kStatClusters) {  // b.ctrl->stat_direct
+  if (M > kStatClusters) {  // summed by one block
     r.cost = b.c_cost[t < M ? t : 0];
     r.smin = b.c_smin[t < M ? t : 0];
     r.dir = reinterpret_cast<const float4*>(b.c_dir)[t < M ? t : 0];

@@ -114,7 +114,6 @@ struct Ctrl {
   int32_t dyn_h, dyn_ok;  // Eq. (17) estimate of this replan: H' and whether the dynamic rule applies
   uint32_t status;
   uint32_t step_used;
-  int32_t stat_direct;  // the cluster arrays hold the final statistics (more than kStatClusters clusters)
   int32_t open_V;  // points whose counts in ncount the window labelling left open above minPts (0: none)
   // completion ticket of the window DBSCAN launch (zero between calls), on a
   // line of its own: blocks take tickets while block 0 stores the words above
@@ -439,13 +438,6 @@ __device__ __forceinline__ float seg_bcast(float v, int src) {
   const float b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src + 32));
   return (__lane_id() < 32) ? a : b;
 }
-template <int SEG>
-__device__ __forceinline__ int seg_bcast_i(int v, int src) {
-  if (SEG == 64) return __builtin_amdgcn_readlane(v, src);
-  const int a = __builtin_amdgcn_readlane(v, src);
-  const int b = __builtin_amdgcn_readlane(v, src + 32);
-  return (__lane_id() < 32) ? a : b;
-}
 
 // value of lane src0 (segment 0) / src1 (segment 1), both wave-uniform
 template <int SEG>
@@ -482,11 +474,6 @@ __device__ __forceinline__ float dist2_2(float ax, float ay, float bx, float by)
 __device__ __forceinline__ float dist2_3(float ax, float ay, float az, float bx, float by, float bz) {
   const float dx = ax - bx, dy = ay - by, dz = az - bz;
   return __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
-}
-
-// agent-scope atomics for data shared between workgroups inside one kernel
-__device__ __forceinline__ int ld_acquire(const int* p) {
-  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // wave-wide inclusive sums and maxima (identity -1) on DPP lane moves: row
