@@ -400,12 +400,14 @@ ce_status ce_mppi_time_rollout(ce_mppi_planner* planner, const float* x_t, const
  *
  * A batch runs one replan of each of its planners (Alg. 1 for every member,
  * each exactly as ce_mppi_replan would run it) as one graph launch.  Every
- * phase of the replan is one persistent kernel per planner kind (rollout
- * kind: unicycle, arm; DBSCAN kind: 2-D on the angular
- * windows, 2-D on sorted distance passes, 3-D) whose fixed grid loops over
- * the work items of all members; the DBSCAN work tables are sized on the
- * device from each member's feasible count.  The results of a member are
- * bitwise those of ce_mppi_replan on the same inputs and state.
+ * phase of the replan is one kernel per planner kind (rollout kind: unicycle,
+ * arm; DBSCAN kind: 2-D on the angular windows, 2-D on sorted distance passes,
+ * 3-D) over the work items of all members.  The labelling on the angular
+ * windows, the update and (when every member is replanned) the unicycle
+ * rollouts have one block per item; the other phases are fixed grids that loop
+ * over the items.  The DBSCAN work tables are sized on the device from each
+ * member's feasible count.  The results of a member are bitwise those of
+ * ce_mppi_replan on the same inputs and state.
  *
  * Ownership: the batch holds references to its planners, which must outlive
  * it, stay on the batch's device, and must not run a replan concurrently with

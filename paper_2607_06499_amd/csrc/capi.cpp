@@ -179,12 +179,10 @@ void build_cfg(const ce_mppi_config* u, Cfg& c) {
   if (c.dyn == CE_DYN_UNICYCLE) {
     // More lanes of fewer steps shorten the one wave that a small launch is
     // bound by; fewer lanes of more steps take fewer instructions, which bound
-    // a large one.  Measured, us a launch with 8 / 16 / 32 lanes: N = 30
-    // K = 1,024 5.9 / 5.2 / -, K = 16,384 6.7 / 6.4 / -, K = 65,536 12.4 / 14.1
-    // / -; N = 50 K = 1,024 6.3 / 5.4 / 4.8, K = 8,192 6.9 / 6.0 / 5.8,
-    // K = 65,536 20.2 / 17.0 / 20.7.  The line for N > 32 lies at 4,096 because
-    // from there on a batch, which takes its members' layouts, loses more to
-    // the extra instructions than a single launch gains.
+    // a large one.  Measured, us a launch back to back with 8 / 16 / 32 lanes:
+    // N = 30 K = 1,024 4.9 / 4.3 / 4.3, 8,192 5.0 / 4.4 / 5.4, 16,384 5.4 / 5.4 /
+    // 8.3, 65,536 11.6 / 14.1 / 23.5; N = 50 (16 / 32 lanes) K = 1,024 4.5 / 4.4,
+    // 4,096 4.7 / 4.6, 8,192 5.1 / 5.5, 65,536 17.4 / 23.9.
     const int lanes = c.N <= 32 ? (c.K <= 16384 ? 16 : 8) : (c.K <= 4096 ? 32 : 16);
     const int steps = 2 * ((c.N + 2 * lanes - 1) / (2 * lanes));
     c.seg = uni_code(lanes, steps);

@@ -3535,7 +3535,7 @@ __device__ __forceinline__ void update_body(const Cfg& c, const Bufs& b, UpdLds&
   const float u_own = b.U[t < NM ? t : 0];
   const Ctrl cv = *b.ctrl;
   if (nrows > 1) {
-    // wave w sums the rows w, w + 16, ... in increasing order, lane l the
+    // wave w sums the rows w, w + NW, ... in increasing order, lane l the
     // elements l, l + 64, ...; kFinRows rows per wave are requested at once (the
     // chunks past a row's end read the next row; those sums are never used)
     constexpr int NW = kUpdThreads / kWave;

@@ -4,7 +4,8 @@
 // point of Eq. (9)-(11)); the next kernel reduces those records.
 //
 // Layout: a rollout's steps are spread over lanes of a wavefront (the unicycle:
-// 8 lanes of a few steps each; the arm: one step per lane, 32 or 64 lanes).  A
+// 8, 16 or 32 lanes of 2 or 4 steps each, by horizon and rollout count; the arm:
+// one step per lane, 32 or 64 lanes).  A
 // lane owns the controls u_j of its steps and the states x_{j+1} they lead to:
 // it draws their noise, the linear parts of the dynamics are prefix sums across
 // lanes (the heading and position of the unicycle, the joint angles of the
@@ -343,8 +344,10 @@ __device__ __forceinline__ void perturb_clamp(const Cfg& c, float2 n, float g0, 
 // of one wave in small ones (the layout is chosen for each planner).  Measured
 // against one step per lane, where a scan took six adds per lane and sum, a
 // contact test its LDS read per state and N = 50 left 14 of 64 lanes idle:
-// N = 50, K = 8,192 7.2 -> 4.9 us a launch back to back, K = 65,536 27.4 ->
-// 17.5 us; the 64 planners of a batch 119 -> 58 us.
+// N = 50, K = 8,192 7.2 -> 5.0 us a launch back to back, K = 65,536 27.4 ->
+// 17.4 us; the 64 planners of a batch 119 -> 60 us.  The sums of a rollout
+// associate by layout, so its states and cost are the same to rounding, not bit
+// for bit, in planners whose layouts differ.
 template <int G>
 constexpr int uni_per_block() {
   return kUniThreads / G;
@@ -824,9 +827,9 @@ __device__ __forceinline__ void rollout_unicycle_slot(CSlotStatic st, CSlotIO io
 }
 
 // Unicycle items with a block each (the full member set, whose items the host
-// knows): 64 planners of a batch, 15,000 items, 68 us where persistent blocks
-// took 76-78 us, whose registers leave too few waves to cover an item's
-// latency.
+// knows): the 64 planners of a batch, 15,000 items, take 60 us where persistent
+// blocks, whose registers leave too few waves to cover an item's latency, take 88
+// (the same members as a subset launch).
 __global__ __launch_bounds__(kUniThreads) void kb_rollout_unicycle(CSlotStatic st, CSlotIO io, Tab t) {
   __shared__ UniLds sh;
   int local;
