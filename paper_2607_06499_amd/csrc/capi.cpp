@@ -793,7 +793,7 @@ ce_status ce_mppi_tune_launch(ce_mppi_planner* P, const float* x_t, const float*
   if (st != CE_OK) return st;
   DeviceGuard guard(P->cfg.device);
   hipStream_t s = S(stream);
-  const int keep_cap = P->t.cap;
+  const int keep_cap = P->t.cap, keep_mode = P->launch_mode;
   P->t.cap = 0;  // the timed mode would bypass the launch mode under test
   double us[2] = {0.0, 0.0};
   const int32_t modes[2] = {CE_LAUNCH_GRAPH, CE_LAUNCH_DIRECT};
@@ -813,6 +813,7 @@ ce_status ce_mppi_tune_launch(ce_mppi_planner* P, const float* x_t, const float*
     if (st == CE_OK) st = ce_mppi_set_state(P, saved.data(), need, stream);
   }
   P->t.cap = keep_cap;
+  P->launch_mode = keep_mode;  // (a call that fails chooses nothing)
   if (st != CE_OK) return st;
   P->launch_mode = us[1] < us[0] ? CE_LAUNCH_DIRECT : CE_LAUNCH_GRAPH;
   if (us_graph) *us_graph = us[0];

@@ -102,3 +102,35 @@ def test_replan_on_a_capturing_stream(mk):
         pl.close()
     assert steps[None] == steps[B.LAUNCH_GRAPH], steps
     assert steps[B.LAUNCH_DIRECT] == [0, 1, 2, 3, 4], steps
+
+
+def test_failed_tuning_leaves_the_mode():
+    """A tuning call that fails (the planner is busy on another stream) leaves the
+    launch mode as it was: a planner in direct mode is still captured kernel by
+    kernel afterwards."""
+    from paper_2607_06499_amd import binding as B
+
+    torch = H.torch_mod()
+    s = W.unicycle_static_ahead(3, num_samples=512)
+    pl = B.Planner(s.spec)
+    pl.set_nominal(torch.as_tensor(s.U0).cuda())
+    pl.set_launch_mode(B.LAUNCH_DIRECT)
+    x, obs = H.to_dev(np.asarray(s.x0, np.float32)), H.to_dev(np.asarray(s.obstacles, np.float32))
+    sa, sb, g = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(sa):
+        torch.cuda._sleep(200_000_000)  # bounded busy wait
+        pl.replan(x, obs, stream=sa)
+    with pytest.raises(B.CeMppiError) as e:
+        pl.tune_launch(x, obs, reps=2, stream=sb)
+    assert e.value.status == B.CE_EBUSY
+    torch.cuda.synchronize()
+    with torch.cuda.stream(sa):
+        g.capture_begin()
+        pl.replan(x, obs, stream=sa)
+        g.capture_end()
+    for step in (1, 2):
+        g.replay()
+        torch.cuda.synchronize()
+        assert pl.info()["step"] == step
+    pl.close()
